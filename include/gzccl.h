@@ -76,13 +76,14 @@ typedef struct gz_graph gz_graph;
  * it or a size whose LDS staging exceeds the device's per-workgroup limit gives
  * GZ_EUNSUPPORTED) and grid (persistent workgroups, 0 = default) never change
  * the bytes.  threads 64 selects the per-wave kernels, in which each wave
- * codes whole 4096-element superblocks on its own (grid ignored): 1D
- * decompression of either type (also batched and scatter), fp32 1D
- * compression, the fused step and decode-and-accumulate; GZ_EUNSUPPORTED
- * elsewhere.  With no shape given or tuned, decompression (single and
+ * codes superblocks of 4096 elements or units of 2048 on its own (grid
+ * ignored): 1D decompression of either type (also batched and scatter), fp32
+ * 1D compression, the fused step and decode-and-accumulate; GZ_EUNSUPPORTED
+ * elsewhere.  With no shape given or tuned, 1D compression of either type
+ * (single, batched and fp64 scatter chunks), decompression (single and
  * batched; scatter decompression of fp32 chunks) and the fused step take
- * them; compression, decode-and-accumulate and fp64 scatter decompression
- * take strips.  mode 0 = 1D blocks, 1 = 8x8 tiles (block_len 64,
+ * them; decode-and-accumulate, fp32 scatter compression and fp64 scatter
+ * decompression take strips.  mode 0 = 1D blocks, 1 = 8x8 tiles (block_len 64,
  * nx = row length, multiple of 8, n a multiple of 8*nx); select (mode 1):
  * 0 = int8 MLP selector, 1 = exhaustive trial, 2 = always L1D. */
 typedef struct {
@@ -246,7 +247,7 @@ gz_status gz_scatter_decompress(gz_ctx* ctx, const void* d_packed,
  * kernels: for any decompress or decode-and-accumulate batch whose jobs
  * each hold at least one element, and for a compress or fused batch whose
  * jobs are all fp32 with the same block length and superblock count
- * (GZ_EUNSUPPORTED for other batches).  By default decompress and fused
+ * (GZ_EUNSUPPORTED for other batches).  By default compress, decompress and fused
  * batches run on them where they can. */
 gz_status gz_batch(gz_ctx* ctx, gz_op op, const gz_request* h_reqs,
                    uint32_t nreq, const gz_params* p, gz_stream_t stream);
@@ -277,7 +278,8 @@ void gz_graph_destroy(gz_graph* graph);
  * (threads, grid; threads 64 = the per-wave kernels) of compress and
  * decompress for (dtype, block_len)
  * on the caller's sample d_sample[0..n) (read only) and stores the fastest
- * in the context; with block_len 0 it tries 32, 64 and 128 and stores the
+ * in the context (*best names the fastest strips of compression, for callers
+ * that pass a shape); with block_len 0 it tries 32, 64 and 128 and stores the
  * fastest as the block length of requests that give 0.  d_work is a
  * caller-owned device buffer of at least
  *   roundup256(n * sizeof(T)) + roundup256(gz_compress_bound(n, dtype, 32)) + 8
@@ -294,7 +296,8 @@ gz_status gz_tune(gz_ctx* ctx, gz_dtype dtype, uint32_t block_len, const void* d
  * threads {128..1024} x grid {1, 2, occupancy, 2 x occupancy} x CUs, plus
  * the per-wave kernels where the batch qualifies (as gz_batch), and
  * stores the fastest shape for (op, batch holds fp64) in the context, where
- * gz_batch and gz_plan_create take it.  Runs the batch 4 times per shape in
+ * gz_batch and gz_plan_create take it (*best names the fastest that the batch
+ * may ask for).  Runs the batch 4 times per shape in
  * place on `stream` (outputs are rewritten with the same bytes) and waits
  * for it; allocates nothing.  Synchronous. */
 gz_status gz_tune_batch(gz_ctx* ctx, gz_op op, const gz_request* h_reqs, uint32_t nreq,

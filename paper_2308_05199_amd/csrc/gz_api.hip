@@ -109,11 +109,11 @@ struct gz_plan {
   uint32_t njobs = 0;  // uniform batch: the kernels derive (job, strip)
   uint32_t tpb = 0, grid = 0;
   bool wide = false;
-  bool wave = false;  // per-wave encoding kernels (total = njobs x rounds)
+  uint32_t unit_w = 0;  // unit encoding: workers per workgroup (total = rounds); 0: not used
+  uint32_t wave_log2L = 0;  // per-wave fused batch: its block length (total = rounds); 0: not used
   bool wave_dec = false;  // per-wave decoding kernels (total = superblocks)
   bool has_map = false;   // wave_dec: d_map lists (job, superblock) pairs
   uint32_t jw = 0;        // wave_dec: d_map holds jw per-wave job shares
-  uint32_t log2L = 5;
 };
 
 struct gz_graph {
@@ -155,7 +155,8 @@ bool set_bound(Job& J, uint32_t dtype, double eb) {
     if (!isfinite(two) || two == 0.0) return false;
     J.t64 = two;
     J.t32 = 0;
-    J.rinv = 0;
+    // 0: the kernels divide (steps whose quotients' remainders could underflow)
+    J.rinv = two >= ldexp(1.0, -900) && two <= ldexp(1.0, 900) ? 1.0 / two : 0.0;
     J.eblo = 0;
   }
   return true;
@@ -254,21 +255,25 @@ bool params_ok(const gz_params* p, uint32_t& L) {
 
 bool tile_mode(const gz_params* p) { return p && p->mode == 1; }
 
-// Per-wave kernels exist for 1D decoding of either type (op 1), fp32 1D
-// encoding, the fused step and decode-and-accumulate (ops 0, 2, 3), and
-// need their LDS.
+// Whether a caller may ask for the per-wave kernels (threads 64): 1D decoding
+// of either type (op 1), fp32 1D encoding, the fused step and
+// decode-and-accumulate (ops 0, 2, 3), which need their LDS.
+bool unit_fits(const gz_ctx* c, uint32_t op) {
+  return gzk::unit_lds(op == 2, op == 2 ? gzk::UNIT_WORKERS_FUSED : gzk::UNIT_WORKERS) <=
+         c->lds_max;
+}
+
 bool wave_fits(const gz_ctx* c, uint32_t op, uint32_t dt) {
   if (op == 1) return gzk::wave_decode_lds(dt) <= c->lds_max;
   if (op == 3) return dt == GZ_F32 && gzk::wave_decode_lds(GZ_F32) <= c->lds_max;
-  return (op == 0 || op == 2) && dt == GZ_F32 && gzk::wave_encode_lds() <= c->lds_max;
+  return (op == 0 || op == 2) && dt == GZ_F32 && unit_fits(c, op);
 }
 
-// Measured defaults: the per-wave kernels for decoding (single streams and
-// batches) and the fused step; strips for compression and decode-and-
-// accumulate (1 GiB: 417 vs 455 us and 436 vs 478 us; there four waves per
-// SIMD hide the input and accumulator loads, where the per-wave kernels
-// have two) and for scatter decoding (an offset read per superblock).
-bool wave_default(uint32_t op) { return op == 1 || op == 2; }
+// Measured defaults: the unit and per-wave kernels for encoding, the fused
+// step and decoding (single streams and batches); strips for decode-and-
+// accumulate (1 GiB: 436 vs 478 us: there four waves per SIMD hide the
+// accumulator loads, where the per-wave kernel has two).
+bool wave_default(uint32_t op) { return op <= 2; }
 
 // Whether a single 1D call takes the per-wave kernel: asked for (threads
 // 64), tuned, or by default (no threads, grid or tuned shape).
@@ -277,6 +282,70 @@ bool wave_wanted(const gz_ctx* c, uint32_t op, uint32_t dt, uint32_t L, const gz
   if (p && p->grid) return false;
   const Tuned& t = c->tuned[tune_op(op)][dt][log2_of(L) - 5];
   return t.tpb ? t.tpb == WAVE_TPB : wave_default(op);
+}
+
+// Workers per workgroup of a unit-encoding launch over `units` units: the
+// fewest that leave at most 192 rounds.  Short streams gain from more CUs (2^14
+// to 2^20 elements in rounds of 3 rather than 15: compression 10.6-11.0 against
+// 10.9-12.2 us, the fused step 12.5-15.1 against 14.3-17.6); from about 200
+// rounds on the look-back over many short rounds costs more (2^22 elements in
+// rounds of 3, 7 and 15: 25, 17 and 14 us).
+uint32_t unit_workers(uint32_t op, uint64_t units) {
+  const uint32_t most = op == 2 ? gzk::UNIT_WORKERS_FUSED : gzk::UNIT_WORKERS;
+  for (uint32_t W = 3; W < most; W = 2 * W + 1)
+    if (cdiv(units, W) <= 192) return W;
+  return most;
+}
+
+// Lays out single job J (n, dtype, L set by set_geom) for unit encoding:
+// workers per workgroup, J.nstrips rounds.  False if the workspace has too
+// few look-back words for that.
+bool unit_single(const gz_ctx* c, uint32_t op, Job& J, uint32_t& W) {
+  const uint64_t most = op == 2 ? gzk::UNIT_WORKERS_FUSED : gzk::UNIT_WORKERS;
+  W = unit_workers(op, cdiv(J.n, gzk::UNIT_ELEMS));
+  if (gzk::unit_rounds(J.n, W) > c->max_strips) W = (uint32_t)most;
+  const uint64_t rounds = gzk::unit_rounds(J.n, W);
+  J.nstrips = (uint32_t)rounds;
+  return rounds <= c->max_strips;
+}
+
+// A fused batch that the per-wave kernel codes faster than the unit kernel:
+// jobs of equal block length and superblock count (`uniform`), more units than
+// one pass of the unit kernel's workers (256 CUs x 11 = 2816: 8 jobs of 2^20
+// elements 27 against 35 us a launch, 8 of 2^21 50 against 53; 8 of 2^19, one
+// pass, 22 against 19).  Returns its rounds, 0 if units are to code it.
+uint64_t wave_fused_rounds(const gz_ctx* c, gz_op op, const std::vector<Job>& jobs,
+                           bool uniform) {
+  if (op != GZ_OP_FUSED || !uniform || gzk::wave_fused_lds() > c->lds_max) return 0;
+  const uint64_t units = jobs.size() * gzk::unit_rounds(jobs[0].n, 1);
+  return units > (uint64_t)c->cus * gzk::UNIT_WORKERS_FUSED
+             ? jobs.size() * gzk::wave_rounds(jobs[0].NS)
+             : 0;
+}
+
+// Lays out a batch's jobs for unit encoding (strip0/nstrips in rounds; one
+// chain through all jobs if `chained`); returns the workers per workgroup, 0
+// (jobs as they were) if the workspace has too few look-back words.
+uint32_t unit_batch(const gz_ctx* c, uint32_t op, std::vector<Job>& jobs, bool chained) {
+  const uint32_t most = op == 2 ? gzk::UNIT_WORKERS_FUSED : gzk::UNIT_WORKERS;
+  uint64_t units = 0;
+  for (const Job& J : jobs) units += gzk::unit_rounds(J.n, 1);
+  auto rounds = [&](uint32_t W) {
+    uint64_t t = 0;
+    for (const Job& J : jobs) t += gzk::unit_rounds(J.n, W);
+    return t;
+  };
+  uint32_t W = unit_workers(op, units);
+  if (rounds(W) > c->max_strips) W = most;
+  if (rounds(W) > c->max_strips) return 0;
+  uint64_t at = 0;
+  for (Job& J : jobs) {
+    J.strip0 = at;
+    J.chain0 = chained ? 0 : at;
+    J.nstrips = (uint32_t)gzk::unit_rounds(J.n, W);
+    at += J.nstrips;
+  }
+  return W;
 }
 
 gz_status hip_status(hipError_t e) { return e == hipSuccess ? GZ_OK : GZ_EHIP; }
@@ -436,8 +505,9 @@ uint32_t batch_tpb(const gz_ctx* c, gz_op op, const gz_request* r, uint32_t nreq
   return pick_tpb(c, op, wide ? GZ_F64 : GZ_F32, 32, nullptr);
 }
 
-// A batch the per-wave encoding kernels take: compression or the fused
-// step, every job fp32 with the same block length and superblock count.
+// A batch for which a caller may ask for the unit kernels (threads 64):
+// compression or the fused step, every job fp32 with the same block length
+// and superblock count.  By default they take any batch of these operations.
 bool batch_wave_ok(const gz_ctx* c, gz_op op, const std::vector<Job>& jobs) {
   if ((op != GZ_OP_COMPRESS && op != GZ_OP_FUSED) || jobs.empty() || !wave_fits(c, op, GZ_F32))
     return false;
@@ -488,6 +558,16 @@ bool batch_decode_wave_ok(const gz_ctx* c, gz_op op, const std::vector<Job>& job
   for (const Job& J : jobs)
     if (J.NS == 0) return false;
   return total > 0 && total <= c->max_strips && total < (1ull << 32);
+}
+
+// Whether a compression or fused batch is encoded by units: asked for and
+// allowed, or by default or tuned (any: whatever the batch).
+bool batch_unit(const gz_ctx* c, gz_op op, const std::vector<Job>& jobs, bool wide,
+                const gz_params* p, bool any) {
+  if ((op != GZ_OP_COMPRESS && op != GZ_OP_FUSED) || !unit_fits(c, op)) return false;
+  if (any) return true;
+  if (p && p->threads) return p->threads == WAVE_TPB && !wide && batch_wave_ok(c, op, jobs);
+  return batch_wave_wanted(c, op, p, wide);
 }
 
 uint32_t batch_grid(const gz_ctx* c, gz_op op, bool wide, uint32_t tpb, uint64_t total,
@@ -661,7 +741,7 @@ namespace {
 // gz_compress_noalloc).
 gz_status compress_impl(gz_ctx* c, const void* d_in, uint64_t n, gz_dtype dtype, double eb,
                         const gz_params* p, void* d_out, uint64_t out_cap,
-                        uint64_t* d_out_bytes, gz_stream_t stream) {
+                        uint64_t* d_out_bytes, gz_stream_t stream, bool unit = false) {
   uint32_t L;
   if (!c || !d_out || (dtype != GZ_F32 && dtype != GZ_F64) || !params_ok(p, L))
     return GZ_EINVAL;
@@ -673,27 +753,26 @@ gz_status compress_impl(gz_ctx* c, const void* d_in, uint64_t n, gz_dtype dtype,
   memset(&J, 0, sizeof J);
   J.dtype = dtype;
   if (!set_bound(J, dtype, eb)) return GZ_EINVAL;
-  // per-wave encoding takes one look-back word per round of 8 superblocks; a
-  // stream with more rounds than the workspace has words falls back to
-  // strips unless the caller asked for waves
-  if (!tile_mode(p) && n && wave_wanted(c, 0, dtype, L, p) && wave_fits(c, 0, dtype)) {
-    set_geom(J, n, L, gzk::MAX_TPB);
-    if (gzk::wave_rounds(J.NS) <= c->max_strips) {
+  gz_params q;  // waves asked for: the default strips' geometry, should units not fit
+  if (!tile_mode(p) && unit_fits(c, 0) &&
+      (unit || (wave_wanted(c, 0, dtype, L, p) &&
+                !(p && p->threads == WAVE_TPB && !wave_fits(c, 0, dtype))))) {
+    if (p && p->threads) {
+      q = *p;
+      q.threads = q.grid = 0;
+      p = &q;
+    }
+    // the limit on n is that of the strips a call takes by default
+    set_geom(J, n, L, pick_tpb(c, 0, dtype, L, p));
+    if (J.nstrips > c->max_strips) return GZ_ENOSPC;
+    uint32_t W;
+    if (unit_single(c, 0, J, W)) {
       J.in = job_ptr(d_in);
       J.out = job_ptr(d_out);
       J.out_bytes = job_ptr((unsigned long long*)d_out_bytes);
-      return hip_status(gzk::launch_encode_wave(0, nullptr, J, 1,
-                                                (uint32_t)gzk::wave_rounds(J.NS), J.log2L,
-                                                c->ctl(), (uint32_t)c->cus,
-                                                (hipStream_t)stream));
+      return hip_status(
+          gzk::launch_unit(0, J, c->ctl(), W, (uint32_t)c->cus, (hipStream_t)stream));
     }
-    if (p && p->threads == WAVE_TPB) return GZ_ENOSPC;
-  }
-  gz_params q;  // an empty stream asked for waves: one default strip writes its header
-  if (!n && p && p->threads == WAVE_TPB && !tile_mode(p) && wave_fits(c, 0, dtype)) {
-    q = *p;
-    q.threads = q.grid = 0;
-    p = &q;
   }
   const uint32_t tpb = pick_tpb(c, 0, dtype, L, p);
   if (!tpb_fits(c, dtype == GZ_F64, tile_mode(p), tpb)) return GZ_EUNSUPPORTED;
@@ -784,20 +863,19 @@ gz_status gz_fused_reduce_step(gz_ctx* c, const void* d_cmp_in, uint64_t in_byte
   J.local = job_ptr(d_local);
   J.out = job_ptr(d_cmp_out);
   J.out_bytes = job_ptr((unsigned long long*)d_out_bytes);
-  if (n && wave_wanted(c, 2, GZ_F32, L, p) && wave_fits(c, 2, GZ_F32)) {
+  gz_params q;  // waves asked for: the default strips' geometry, should units not fit
+  if (wave_wanted(c, 2, GZ_F32, L, p) && unit_fits(c, 2)) {
+    if (p && p->threads) {
+      q = *p;
+      q.threads = q.grid = 0;
+      p = &q;
+    }
     set_geom(J, n, L, gzk::MAX_TPB);
-    if (gzk::wave_rounds(J.NS) <= c->max_strips)
-      return hip_status(gzk::launch_encode_wave(2, nullptr, J, 1,
-                                                (uint32_t)gzk::wave_rounds(J.NS), J.log2L,
-                                                c->ctl(), (uint32_t)c->cus,
-                                                (hipStream_t)stream));
-    if (p && p->threads == WAVE_TPB) return GZ_ENOSPC;
-  }
-  gz_params q;  // an empty stream asked for waves: one default strip writes its header
-  if (!n && p && p->threads == WAVE_TPB) {
-    q = *p;
-    q.threads = q.grid = 0;
-    p = &q;
+    if (J.nstrips > c->max_strips) return GZ_ENOSPC;
+    uint32_t W;
+    if (unit_single(c, 2, J, W))
+      return hip_status(
+          gzk::launch_unit(2, J, c->ctl(), W, (uint32_t)c->cus, (hipStream_t)stream));
   }
   const uint32_t tpb = pick_tpb(c, 2, GZ_F32, L, p);
   if (!tpb_fits(c, false, false, tpb)) return GZ_EUNSUPPORTED;
@@ -874,11 +952,20 @@ gz_status gz_scatter_compress(gz_ctx* c, const void* d_root, gz_dtype dtype,
   if (pay > MAX_CHAIN_DW) return GZ_EINVAL;
   if (strip > c->max_strips) return GZ_ENOSPC;
   if (overlaps(d_root, span * esize(dtype), d_out, out_cap)) return GZ_EINVAL;
+  // fp64 chunks by units (40 chunks of 2^25 values, both ways: 263 against 300
+  // us), fp32 ones by strips (64 chunks of 2^27, ratio 2: 490 against 493-534 us)
+  const uint32_t W = dtype == GZ_F64 && unit_fits(c, 0) && wave_wanted(c, 0, dtype, L, p)
+                         ? unit_batch(c, 0, jobs, true)
+                         : 0;
   std::vector<uint32_t> map;
   fill_map(jobs, false, map);  // one chain through all chunks
   hipStream_t st = (hipStream_t)stream;
   gz_status r = stage_upload(c, jobs, map, st);
   if (r != GZ_OK) return r;
+  if (W)
+    return hip_status(gzk::launch_batch_unit(0, c->d_jobs, c->d_map, 0,
+                                             (uint32_t)(map.size() / 2), dtype == GZ_F64,
+                                             c->ctl(), W, (uint32_t)c->cus, st));
   const uint32_t grid = pick_grid(c, 0, dtype, L, tpb, strip, p);
   return hip_status(gzk::launch_batch(0, c->d_jobs, c->d_map, 0, (uint32_t)strip, c->ctl(), tpb,
                                       grid, dtype == GZ_F64, st));
@@ -957,8 +1044,13 @@ gz_status gz_scatter_decompress(gz_ctx* c, const void* d_packed, uint64_t packed
                                       grid, dtype == GZ_F64, st));
 }
 
-gz_status gz_batch(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t nreq,
-                   const gz_params* p, gz_stream_t stream) {
+}  // extern "C"
+
+namespace {
+
+// gz_batch; any: encode by units whatever the batch (the tuner's candidate).
+gz_status batch_impl(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t nreq,
+                     const gz_params* p, gz_stream_t stream, bool any = false) {
   if (!c || op > GZ_OP_ACCUMULATE) return GZ_EINVAL;
   if (p && !tpb_ok(p->threads)) return GZ_EINVAL;
   if (!h_reqs || nreq == 0) return GZ_EINVAL;
@@ -984,19 +1076,35 @@ gz_status gz_batch(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t nreq,
     }
     if (p && p->threads == WAVE_TPB) return GZ_EUNSUPPORTED;
   }
-  const bool wave = !wide && batch_wave_wanted(c, op, p) && batch_wave_ok(c, op, jobs);
-  if (p && p->threads == WAVE_TPB && !wave) return GZ_EUNSUPPORTED;
+  const bool unit = batch_unit(c, op, jobs, wide, p, any);
+  if (p && p->threads == WAVE_TPB && !unit) return GZ_EUNSUPPORTED;
+  const uint64_t fw =
+      unit ? wave_fused_rounds(c, op, jobs, !wide && batch_wave_ok(c, op, jobs)) : 0;
+  uint32_t W = 0;
+  if (unit && !fw) W = unit_batch(c, op, jobs, false);
+  if (W) fill_map(jobs, true, map);
   r = stage_upload(c, jobs, map, st);
   if (r != GZ_OK) return r;
-  if (wave)
-    return hip_status(gzk::launch_encode_wave(
-        (uint32_t)op, c->d_jobs, Job(), (uint32_t)jobs.size(),
-        (uint32_t)(jobs.size() * gzk::wave_rounds(jobs[0].NS)), jobs[0].log2L, c->ctl(),
-        (uint32_t)c->cus, st));
+  if (fw)
+    return hip_status(gzk::launch_fused_wave(c->d_jobs, (uint32_t)jobs.size(), (uint32_t)fw,
+                                             jobs[0].log2L, c->ctl(), (uint32_t)c->cus, st));
+  if (W)
+    return hip_status(gzk::launch_batch_unit((uint32_t)op, c->d_jobs, c->d_map,
+                                             uniform_jobs(jobs), (uint32_t)(map.size() / 2),
+                                             wide, c->ctl(), W, (uint32_t)c->cus, st));
   const uint64_t total = map.size() / 2;
   const uint32_t g = batch_grid(c, op, wide, tpb, total, p);
   return hip_status(gzk::launch_batch((uint32_t)op, c->d_jobs, c->d_map, uniform_jobs(jobs),
                                       (uint32_t)total, c->ctl(), tpb, g, wide, st));
+}
+
+}  // namespace
+
+extern "C" {
+
+gz_status gz_batch(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t nreq,
+                   const gz_params* p, gz_stream_t stream) {
+  return batch_impl(c, op, h_reqs, nreq, p, stream);
 }
 
 gz_status gz_plan_create(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t nreq,
@@ -1027,8 +1135,13 @@ gz_status gz_plan_create(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t
       return GZ_EUNSUPPORTED;
     }
   }
-  const bool wave = !wave_dec && !wide && batch_wave_wanted(c, op, p) && batch_wave_ok(c, op, jobs);
-  if (p && p->threads == WAVE_TPB && !wave && !wave_dec) return GZ_EUNSUPPORTED;
+  const bool unit = !wave_dec && batch_unit(c, op, jobs, wide, p, false);
+  if (p && p->threads == WAVE_TPB && !unit && !wave_dec) return GZ_EUNSUPPORTED;
+  const uint64_t fw =
+      unit ? wave_fused_rounds(c, op, jobs, !wide && batch_wave_ok(c, op, jobs)) : 0;
+  uint32_t unit_w = 0;
+  if (unit && !fw) unit_w = unit_batch(c, op, jobs, false);
+  if (unit_w) fill_map(jobs, true, map);
   // a range released by gz_plan_destroy may still be read by a launch in
   // flight: the device finishes its work before the arena is written
   if (hipDeviceSynchronize() != hipSuccess) return GZ_EHIP;
@@ -1055,11 +1168,11 @@ gz_status gz_plan_create(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t
   pl->tpb = tpb;
   pl->wide = wide;
   pl->grid = batch_grid(c, op, wide, tpb, pl->total, p);
-  if (wave) {
-    pl->wave = true;
+  pl->unit_w = unit_w;
+  if (fw) {
+    pl->wave_log2L = jobs[0].log2L;
     pl->njobs = (uint32_t)jobs.size();
-    pl->total = (uint32_t)(jobs.size() * gzk::wave_rounds(jobs[0].NS));
-    pl->log2L = jobs[0].log2L;
+    pl->total = (uint32_t)fw;
   }
   if (wave_dec) {
     pl->wave_dec = true;
@@ -1082,10 +1195,14 @@ gz_status gz_plan_create(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t
 
 gz_status gz_plan_launch(gz_plan* pl, gz_stream_t stream) {
   if (!pl || !pl->ctx) return GZ_EINVAL;
-  if (pl->wave)
-    return hip_status(gzk::launch_encode_wave(pl->op, pl->d_jobs, Job(), pl->njobs, pl->total,
-                                              pl->log2L, pl->ctx->ctl(),
-                                              (uint32_t)pl->ctx->cus, (hipStream_t)stream));
+  if (pl->wave_log2L)
+    return hip_status(gzk::launch_fused_wave(pl->d_jobs, pl->njobs, pl->total, pl->wave_log2L,
+                                             pl->ctx->ctl(), (uint32_t)pl->ctx->cus,
+                                             (hipStream_t)stream));
+  if (pl->unit_w)
+    return hip_status(gzk::launch_batch_unit(pl->op, pl->d_jobs, pl->d_map, pl->njobs, pl->total,
+                                             pl->wide, pl->ctx->ctl(), pl->unit_w,
+                                             (uint32_t)pl->ctx->cus, (hipStream_t)stream));
   if (pl->wave_dec)
     return hip_status(gzk::launch_decode_wave_batch(
         pl->op, pl->d_jobs, pl->has_map ? pl->d_map : nullptr, pl->njobs, pl->total, pl->wide,
@@ -1193,7 +1310,8 @@ static gz_status time_op(gz_ctx* c, uint32_t op, const void* x, void* y, void* s
                          hipEvent_t e0, hipEvent_t e1, float& ms) {
   gz_params p = {L, tpb, grid, 0, 0, 0};
   auto run = [&]() -> gz_status {
-    return op == 0 ? gz_compress(c, x, n, dt, 1e-3, &p, s, cap, (uint64_t*)nb, st)
+    return op == 0 ? compress_impl(c, x, n, dt, 1e-3, &p, s, cap, (uint64_t*)nb, st,
+                                   tpb == WAVE_TPB)
                    : gz_decompress(c, s, cap, n, dt, &p, y, st);
   };
   gz_status r = run();
@@ -1232,6 +1350,7 @@ gz_status gz_tune(gz_ctx* c, gz_dtype dt, uint32_t block_len, const void* d_samp
   gz_status r = GZ_OK;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) r = GZ_EHIP;
   float best_total = 1e30f;
+  Tuned strips[3];  // per block length: compression's fastest strips
   uint32_t best_L = block_len ? block_len : 32;
   for (int li = 0; r == GZ_OK && li < 3; ++li) {
     const uint32_t L = Ls[li];
@@ -1241,20 +1360,19 @@ gz_status gz_tune(gz_ctx* c, gz_dtype dt, uint32_t block_len, const void* d_samp
       char keyb[128];
       snprintf(keyb, sizeof keyb, "gfx950/cus%d/op%u/dt%u/L%u/n%llu", c->cus, op, (unsigned)dt,
                L, (unsigned long long)n);
-      uint32_t tpb = 0, grid = 0;
+      uint32_t tpb = 0, grid = 0, stpb = 0, sgrid = 0;  // fastest; fastest strips
       float ms = 0;
-      const bool wave_ok = wave_fits(c, op, dt);
+      const bool wave_ok = op == 0 ? unit_fits(c, 0) : wave_fits(c, op, dt);
+      const std::string skey = std::string(keyb) + "/strips";
       if (cache_lookup(cache_path, keyb, tpb, grid) &&
+          cache_lookup(cache_path, skey, stpb, sgrid) && tpb_fits(c, dt == GZ_F64, false, stpb) &&
           (tpb_fits(c, dt == GZ_F64, false, tpb) || (tpb == WAVE_TPB && wave_ok))) {
         r = time_op(c, op, d_sample, y, s, cap, nb, n, dt, L, tpb, grid, st, e0, e1, ms);
       } else {
-        float bms = 1e30f;
-        if (wave_ok) {  // the per-wave kernel (its grid is its own)
+        float bms = 1e30f, wms = 1e30f;
+        if (wave_ok)  // the unit or per-wave kernel (its grid is its own)
           r = time_op(c, op, d_sample, y, s, cap, nb, n, dt, L, WAVE_TPB, (uint32_t)c->cus, st,
-                      e0, e1, bms);
-          tpb = WAVE_TPB;
-          grid = (uint32_t)c->cus;
-        }
+                      e0, e1, wms);
         const uint32_t tpbs[4] = {128, 256, 512, 1024};
         for (uint32_t ti = 0; r == GZ_OK && ti < 4; ++ti) {
           if (!tpb_fits(c, dt == GZ_F64, false, tpbs[ti])) continue;
@@ -1267,17 +1385,24 @@ gz_status gz_tune(gz_ctx* c, gz_dtype dt, uint32_t block_len, const void* d_samp
                         e1, t);
             if (r == GZ_OK && t < bms) {
               bms = t;
-              tpb = tpbs[ti];
-              grid = grids[gi];
+              stpb = tpbs[ti];
+              sgrid = grids[gi];
             }
           }
         }
-        ms = bms;
-        if (r == GZ_OK) cache_store(cache_path, keyb, tpb, grid, ms);
+        const bool wv = wms < bms;
+        tpb = wv ? WAVE_TPB : stpb;
+        grid = wv ? (uint32_t)c->cus : sgrid;
+        ms = wv ? wms : bms;
+        if (r == GZ_OK) {
+          cache_store(cache_path, keyb, tpb, grid, ms);
+          cache_store(cache_path, skey, stpb, sgrid, bms);
+        }
       }
       if (r == GZ_OK) {
         c->tuned[op][dt][log2_of(L) - 5].tpb = tpb;
         c->tuned[op][dt][log2_of(L) - 5].grid = grid;
+        if (op == 0) strips[li] = Tuned{stpb, sgrid};
         total += ms;
       }
     }
@@ -1289,7 +1414,7 @@ gz_status gz_tune(gz_ctx* c, gz_dtype dt, uint32_t block_len, const void* d_samp
   if (r == GZ_OK && hipStreamSynchronize(st) != hipSuccess) r = GZ_EHIP;
   if (r == GZ_OK && block_len == 0) c->best_L[dt] = best_L;  // for requests of length 0
   if (r == GZ_OK && best) {
-    const Tuned& t = c->tuned[0][dt][log2_of(best_L) - 5];
+    const Tuned& t = strips[log2_of(best_L) - 5];
     *best = gz_params{best_L, t.tpb, t.grid, 0, 0, 0};
   }
   if (e0) (void)hipEventDestroy(e0);
@@ -1309,10 +1434,11 @@ gz_status gz_tune_batch(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t 
   char keyb[160];
   snprintf(keyb, sizeof keyb, "gfx950/cus%d/batch/op%u/wide%u/nreq%u/elems%llu", c->cus,
            (unsigned)op, wide ? 1u : 0u, nreq, (unsigned long long)elems);
-  uint32_t tpb = 0, grid = 0;
+  uint32_t tpb = 0, grid = 0, stpb = 0, sgrid = 0;  // fastest; fastest strips
+  const std::string skey = std::string(keyb) + "/strips";
   gz_status r = GZ_OK;
   // the per-wave kernels are a candidate where the batch qualifies
-  bool wave_ok = false;
+  bool wave_ok = false, wave_ask = true;  // may be taken; may be asked for by callers
   {
     std::vector<Job> jobs;
     std::vector<uint32_t> map;
@@ -1321,16 +1447,18 @@ gz_status gz_tune_batch(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t 
     if (op == GZ_OP_DECOMPRESS) {
       std::vector<uint32_t> smap;
       wave_ok = batch_decode_wave_ok(c, op, jobs, wide, wave_decode_map(jobs, smap));
-    } else if (!wide) {
-      wave_ok = batch_wave_ok(c, op, jobs);
+    } else {
+      wave_ok = unit_fits(c, op);
+      wave_ask = !wide && batch_wave_ok(c, op, jobs);
     }
   }
   if (!(cache_lookup(cache_path, keyb, tpb, grid) &&
+        cache_lookup(cache_path, skey, stpb, sgrid) && tpb_fits(c, wide, false, stpb) &&
         (tpb_fits(c, wide, false, tpb) || (tpb == WAVE_TPB && wave_ok)))) {
     hipStream_t st = (hipStream_t)stream;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) r = GZ_EHIP;
-    float bms = 1e30f;
+    float bms = 1e30f, sms = 1e30f;
     const uint32_t tpbs[5] = {WAVE_TPB, 128, 256, 512, 1024};
     for (uint32_t ti = 0; r == GZ_OK && ti < 5; ++ti) {
       const bool wv = tpbs[ti] == WAVE_TPB;
@@ -1341,9 +1469,11 @@ gz_status gz_tune_batch(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t 
                                  (uint32_t)(c->cus * occ * 2)};
       for (uint32_t gi = 0; r == GZ_OK && gi < (wv ? 1u : 4u); ++gi) {
         const gz_params p = {0, tpbs[ti], grids[gi], 0, 0, 0};
-        r = gz_batch(c, op, h_reqs, nreq, &p, st);  // warm-up
+        const bool unit = wv && op != GZ_OP_DECOMPRESS;
+        r = batch_impl(c, op, h_reqs, nreq, &p, st, unit);  // warm-up
         if (r == GZ_OK && hipEventRecord(e0, st) != hipSuccess) r = GZ_EHIP;
-        for (int k = 0; k < 3 && r == GZ_OK; ++k) r = gz_batch(c, op, h_reqs, nreq, &p, st);
+        for (int k = 0; k < 3 && r == GZ_OK; ++k) 
+          r = batch_impl(c, op, h_reqs, nreq, &p, st, unit);
         float ms = 0;
         if (r == GZ_OK && (hipEventRecord(e1, st) != hipSuccess ||
                            hipEventSynchronize(e1) != hipSuccess ||
@@ -1354,16 +1484,24 @@ gz_status gz_tune_batch(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t 
           tpb = tpbs[ti];
           grid = grids[gi];
         }
+        if (r == GZ_OK && !wv && ms < sms) {
+          sms = ms;
+          stpb = tpbs[ti];
+          sgrid = grids[gi];
+        }
       }
     }
     if (r == GZ_OK && hipStreamSynchronize(st) != hipSuccess) r = GZ_EHIP;
-    if (r == GZ_OK) cache_store(cache_path, keyb, tpb, grid, bms / 3);
+    if (r == GZ_OK) {
+      cache_store(cache_path, keyb, tpb, grid, bms / 3);
+      cache_store(cache_path, skey, stpb, sgrid, sms / 3);
+    }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
   }
   if (r != GZ_OK) return r;
   c->batch_tuned[op][wide ? 1 : 0] = Tuned{tpb, grid};
-  if (best) *best = gz_params{0, tpb, grid, 0, 0, 0};
+  if (best) *best = wave_ask ? gz_params{0, tpb, grid, 0, 0, 0} : gz_params{0, stpb, sgrid, 0, 0, 0};
   return GZ_OK;
 }
 

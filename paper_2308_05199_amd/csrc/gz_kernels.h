@@ -34,19 +34,35 @@ hipError_t launch_accum_wave(const Job& J, const Ctl& C, uint32_t cus, hipStream
 hipError_t launch_decode_wave_batch(uint32_t op, const Job* d_jobs, const uint32_t* d_map,
                                     uint32_t njobs, uint32_t total, bool wide, uint32_t jw,
                                     uint32_t cus, const Ctl& C, hipStream_t st);
-// Per-wave fp32 1D encoding (op 0) or fused step (op 2): every wave encodes
-// whole superblocks, a workgroup's waves the 8 of a round (one chain
-// element).  d_jobs null: the one job J, total = rounds_of(J.NS); else njobs
-// jobs of the same superblock count and block length 2^log2L in device
-// memory, total = njobs * rounds_of(NS), round ticket t = round t / njobs
-// of job t % njobs.
-hipError_t launch_encode_wave(uint32_t op, const Job* d_jobs, const Job& J, uint32_t njobs,
-                              uint32_t total, uint32_t log2L, const Ctl& C, uint32_t cus,
-                              hipStream_t st);
-size_t wave_encode_lds();  // its workgroup's LDS bytes
-constexpr uint64_t WAVE_ROUND = 8;  // superblocks per round of the per-wave encoder
-constexpr uint64_t DEC_WAVES_F32 = 8;  // waves per workgroup of the fp32 per-wave decoders
+// Per-wave fused step of njobs fp32 jobs of the same superblock count and
+// block length: every wave codes whole superblocks, a workgroup's waves the 8
+// of a round (one look-back word); total = njobs * wave_rounds(NS), round
+// ticket t = round t / njobs of job t % njobs.
+hipError_t launch_fused_wave(const Job* d_jobs, uint32_t njobs, uint32_t total, uint32_t log2L,
+                             const Ctl& C, uint32_t cus, hipStream_t st);
+constexpr uint64_t WAVE_ROUND = 8;  // superblocks per round
+size_t wave_fused_lds();            // its workgroup's LDS bytes
 inline uint64_t wave_rounds(uint64_t NS) { return (NS + WAVE_ROUND - 1) / WAVE_ROUND; }
+// Unit encoding (op 0 compression of either type, op 2 the fp32 fused step),
+// mode 0: every working wave codes units of 2048 elements, the `workers` of a
+// workgroup (which has one wave more, the scheduler) a round of that many
+// units (one look-back word).  J.nstrips = total rounds (unit_rounds).
+hipError_t launch_unit(uint32_t op, const Job& J, const Ctl& C, uint32_t workers, uint32_t cus,
+                       hipStream_t st);
+// total rounds of njobs jobs of equal round counts (njobs > 0: round t is
+// round t / njobs of job t % njobs) or of the (job, round) pairs of d_map.
+hipError_t launch_batch_unit(uint32_t op, const Job* d_jobs, const uint32_t* d_map,
+                             uint32_t njobs, uint32_t total, bool wide, const Ctl& C,
+                             uint32_t workers, uint32_t cus, hipStream_t st);
+constexpr uint32_t UNIT_WORKERS = 15;        // most workers of a workgroup: compression
+constexpr uint32_t UNIT_WORKERS_FUSED = 11;  // the fused step
+constexpr uint64_t UNIT_ELEMS = 2048;
+size_t unit_lds(bool fused, uint32_t workers);  // its workgroup's LDS bytes
+inline uint64_t unit_rounds(uint64_t n, uint32_t workers) {  // an empty stream is one unit
+  const uint64_t units = n ? (n + UNIT_ELEMS - 1) / UNIT_ELEMS : 1;
+  return (units + workers - 1) / workers;
+}
+constexpr uint64_t DEC_WAVES_F32 = 8;  // waves per workgroup of the fp32 per-wave decoders
 hipError_t launch_quantize(const void* x, uint64_t n, const Job& J, int32_t* q, uint8_t* fail,
                            hipStream_t st);
 // mode 1 (8x8 tiles, fp32): op 0 compress, 1 decompress

@@ -133,41 +133,103 @@ __device__ __forceinline__ int32_t cvt_sat(double f) {
   return r;
 }
 
+// FAIL over a run of elements.  fp32: the largest |rr| and |x - xh| seen, with
+// NaN kept (v_maximum3_f32 takes two elements an instruction), tested once at
+// the end; a compare per condition and element would issue two compares and
+// two or three scalar mask operations instead of one instruction.  fp64 has no
+// such maximum and keeps the compares.
+template <typename T>
+struct QBad;
+template <>
+struct QBad<float> {
+  float r = 0.0f, d = 0.0f;
+  // |rr| < 2^29 exactly when |r| < 2^29 (floats from 2^23 up are integers,
+  // which rint leaves alone; below, both hold)
+  __device__ __forceinline__ bool any(float eblo) const {
+    return !(r < 536870912.0f) || !(d <= eblo);
+  }
+};
+template <>
+struct QBad<double> {
+  bool bad = false;
+  __device__ __forceinline__ bool any(double) const { return bad; }
+};
+
 // When |r| < 2^29 the rounded value rr is an integer held exactly, so
 // (T)q == rr and xh is formed from rr directly.
-__device__ __forceinline__ int32_t quant(float x, double rinv, float t, float eblo,
-                                         bool& bad) {
-  float r = (float)((double)x * rinv);
-  float rr = __builtin_rintf(r);
-  // |rr| < 2^29 exactly when |r| < 2^29 (floats from 2^23 up are integers,
-  // which rint leaves alone; below, both hold), so r dies here; NaN fails
-  bool inr = fabsf(rr) < 536870912.0f;
-  int32_t q = cvt_sat(rr);
-  float d = x - rr * t;
-  bad = !inr || !(fabsf(d) <= eblo);
-  return q;
+__device__ __forceinline__ int32_t quant(float x, double rinv, float t, QBad<float>& b) {
+  const float r = (float)((double)x * rinv);
+  const float rr = __builtin_rintf(r);
+  const float d = x - rr * t;
+  b.r = __builtin_elementwise_maximum(b.r, fabsf(rr));
+  b.d = __builtin_elementwise_maximum(b.d, fabsf(d));
+  return cvt_sat(rr);
 }
 
-__device__ __forceinline__ int32_t quant(double x, double t, double eb, bool& bad) {
-  double r = x / t;
+// fp64: r = x/t correctly rounded.  With y = 1/t correctly rounded (rinv), q0
+// = x y is within 2 ulp of x/t; one correction with the remainder brings it
+// within 1 ulp, and a second one from there gives the correctly rounded
+// quotient (Markstein: y correctly rounded, q faithful, remainder exact).
+// The host sets rinv only for steps t in [2^-900, 2^900]: then remainders of
+// quotients of 2^-2 and more are normal, smaller quotients round to q = 0
+// whatever their last bits, and overflowing ones end as NaN or infinity, which
+// fail.  Other steps take the division.
+__device__ __forceinline__ double quot(double x, double t, double y) {
+  const double q0 = x * y;
+  const double q1 = __builtin_fma(__builtin_fma(-q0, t, x), y, q0);
+  return __builtin_fma(__builtin_fma(-q1, t, x), y, q1);
+}
+
+__device__ __forceinline__ int32_t quant(double x, double r, double t, double eb,
+                                         QBad<double>& b) {
   double rr = __builtin_rint(r);
   bool inr = fabs(r) <= 536870911.0;
   int32_t q = cvt_sat(rr);
   double d = x - rr * t;
-  bad = !inr || !(fabs(d) <= eb);
+  b.bad |= !inr || !(fabs(d) <= eb);
   return q;
 }
 
+// Quantises v[0..N) into q (!FULL: elements past vcnt give 0 and never fail).
+template <int N, bool FULL>
+__device__ __forceinline__ void quant_run(const float* v, const Job& J, uint32_t vcnt, uint32_t* q,
+                                          QBad<float>& b) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const float x = FULL || i < (int)vcnt ? v[i] : 0.0f;
+    q[i] = (uint32_t)quant(x, J.rinv, J.t32, b);
+    // four elements at a time: interleaving more of them costs registers
+    if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+  }
+}
+template <int N, bool FULL>
+__device__ __forceinline__ void quant_run(const double* v, const Job& J, uint32_t vcnt,
+                                          uint32_t* q, QBad<double>& b) {
+  if (J.rinv != 0.0) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const double x = FULL || i < (int)vcnt ? v[i] : 0.0;
+      q[i] = (uint32_t)quant(x, quot(x, J.t64, J.rinv), J.t64, J.eb, b);
+    }
+  } else {
+#pragma unroll 1
+    for (int i = 0; i < N; ++i) {
+      // (a rolled loop over registers would put them in memory)
+      double x = 0.0;
+#pragma unroll
+      for (int k = 0; k < N; ++k) x = k == i && (FULL || k < (int)vcnt) ? v[k] : x;
+      const uint32_t z = (uint32_t)quant(x, x / J.t64, J.t64, J.eb, b);
+#pragma unroll
+      for (int k = 0; k < N; ++k) q[k] = k == i ? z : q[k];
+    }
+  }
+}
 template <typename T>
-__device__ __forceinline__ int32_t quant_t(T x, const Job& J, bool& bad);
+__device__ __forceinline__ T bad_bound(const Job& J);
 template <>
-__device__ __forceinline__ int32_t quant_t<float>(float x, const Job& J, bool& bad) {
-  return quant(x, J.rinv, J.t32, J.eblo, bad);
-}
+__device__ __forceinline__ float bad_bound<float>(const Job& J) { return J.eblo; }
 template <>
-__device__ __forceinline__ int32_t quant_t<double>(double x, const Job& J, bool& bad) {
-  return quant(x, J.t64, J.eb, bad);
-}
+__device__ __forceinline__ double bad_bound<double>(const Job& J) { return J.eb; }
 
 // ------------------------------------------------------------ load/store
 template <typename T>
@@ -750,33 +812,19 @@ struct LaneCode {
   bool exists;
 };
 
-// Mode 0: 1D blocks of L consecutive elements, L1D prediction.  KEEP (fp32
+// Mode 0: 1D blocks of L consecutive elements, L1D prediction, from the
+// quantised values in lc.a (bad: one of the lane's failed).  KEEP (fp32
 // fused step): a block whose quantisation fails puts its values' bits in a[]
 // for the RAW payload, from the lane's LDS segment, where the fused step
 // stored them (they are not in global memory); keep_row: that segment, if
 // not the strip layout's.
-template <typename T, int L, bool FULL, bool KEEP = false>
-__device__ __forceinline__ void analyze_1d(const Job& J, uint64_t seg, uint32_t w,
-                                           const T (&v)[32], uint32_t vcnt, LaneCode& lc,
-                                           const uint32_t* keep_row = nullptr) {
+template <uint32_t EW, int L, bool FULL, bool KEEP = false>
+__device__ __forceinline__ void analyze_q(const Job& J, uint64_t seg, uint32_t w, bool bad,
+                                          uint32_t vcnt, LaneCode& lc,
+                                          const uint32_t* keep_row = nullptr) {
   constexpr int LPB = L / 32;
-  constexpr uint32_t EW = sizeof(T) / 4;
   const uint64_t b = seg / LPB;
   uint32_t (&a)[32] = lc.a;
-  bool bad = false;
-#pragma unroll
-  for (int i = 0; i < 32; ++i) {
-    bool bi = false;
-    int32_t qi = quant_t<T>(v[i], J, bi);
-    if (FULL) {
-      a[i] = (uint32_t)qi;
-      bad |= bi;
-    } else {
-      const bool valid = i < (int)vcnt;
-      a[i] = valid ? (uint32_t)qi : 0u;
-      bad |= valid && bi;
-    }
-  }
   const int32_t base = (int32_t)a[0];
   const int32_t prev = (int32_t)lane_below(a[31]);
   const uint32_t badb = grp_or<LPB>(bad ? 1u : 0u);
@@ -839,6 +887,16 @@ __device__ __forceinline__ void analyze_1d(const Job& J, uint64_t seg, uint32_t 
   lc.F = F;
   lc.size_dw = size_dw;
   lc.exists = exists;
+}
+
+// The same from the lane's values v.
+template <typename T, int L, bool FULL, bool KEEP = false>
+__device__ __forceinline__ void analyze_1d(const Job& J, uint64_t seg, uint32_t w,
+                                           const T (&v)[32], uint32_t vcnt, LaneCode& lc,
+                                           const uint32_t* keep_row = nullptr) {
+  QBad<T> qb;
+  quant_run<32, FULL>(v, J, vcnt, lc.a, qb);
+  analyze_q<sizeof(T) / 4, L, FULL, KEEP>(J, seg, w, qb.any(bad_bound<T>(J)), vcnt, lc, keep_row);
 }
 
 // ---- mode 1: 8x8 tiles, two lanes per tile (lane w owns rows 4w..4w+3).
@@ -973,14 +1031,9 @@ __device__ __forceinline__ uint32_t size_of(uint32_t kind, uint32_t F) {
 // Quantised tile values of the lane (used by the trial kernel and mode 1).
 __device__ __forceinline__ void tile_quant(const Job& J, const float (&v)[32], int32_t (&q)[32],
                                            bool& bad) {
-  bad = false;
-#pragma unroll
-  for (int i = 0; i < 32; ++i) {
-    bool bi = false;
-    q[i] = quant_t<float>(v[i], J, bi);
-    bad |= bi;
-  }
-  bad = grp_or<2>(bad ? 1u : 0u) != 0;
+  QBad<float> qb;
+  quant_run<32, true>(v, J, 32, (uint32_t*)q, qb);
+  bad = grp_or<2>(qb.any(J.eblo) ? 1u : 0u) != 0;
 }
 
 // Mode 1 analysis: exhaustive trial (select 1), MLP (select 0) or L1D only.
@@ -2272,53 +2325,89 @@ __attribute__((amdgpu_waves_per_eu(WIDE ? 1 : 2, 2))) void k_batch_decode_w(
   if (bad && __lane_id() == 0) atomicOr(&C.ctrl->err, ERRF_CORRUPT);
 }
 
-// ---------------------------------------------------------- per-wave encode
-// fp32 1D encoding (compression and the fused step) by single waves.  A wave
-// claims a superblock, builds its payload in LDS in two halves of 64
+// ---- shared by the per-wave encoders
+__device__ __forceinline__ uint32_t lds_load_acq(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void lds_store_rel(uint32_t* p, uint32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Bounded wait until *p >= want (lane 0 polls); false on timeout.
+__device__ __forceinline__ bool lds_wait_ge(const Ctl& C, const uint32_t* p, uint32_t want) {
+  uint32_t ok = 1;
+  if (__lane_id() == 0) {
+    uint32_t spins = 0;
+    uint64_t t0 = 0;
+    while (lds_load_acq(p) < want) {
+      if (wait_over(C, ++spins, t0)) {
+        atomicOr(&C.ctrl->err, ERRF_TIMEOUT);
+        ok = 0;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+  }
+  return read_lane(ok, 0) != 0;
+}
+
+// The lane's share of its block's payload at st (the block's first word):
+// base, sign word and planes of an L1D block, or the values of a RAW block
+// (from registers, re-derived by the fused step, or re-read from J.in).
+template <typename T, int L, bool FUSED, bool FULL>
+__device__ __forceinline__ void wave_pack(const Job& J, uint64_t seg, uint32_t w, uint32_t vcnt,
+                                          const LaneCode& lc, const FusedSrc& fs, uint32_t* st) {
+  constexpr uint32_t LPB = L / 32, EW = sizeof(T) / 4;
+  if (lc.kind == K_L1D) {
+    if (w == 0) st[0] = (uint32_t)lc.base;
+    if (lc.F) {
+      st[1 + w] = lc.sg;
+      put_planes(lc.a, lc.F, st + 1 + LPB + w, LPB);
+    }
+  }
+  if (FUSED && lc.kind == K_RAW && lc.rawregs) {
+#pragma unroll
+    for (int i = 0; i < 32; ++i)  // unrolled: a[] stays in registers
+      if (FULL || i < (int)vcnt) st[w * 32 + i] = lc.a[i];
+  } else if (lc.kind == K_RAW) {  // blocks too wide to code (rare)
+    if (FUSED) {
+      fused_raw_stage<LPB>(J, fs, seg, w, vcnt, st);
+    } else {
+      const T* src = (const T*)J.in + seg * SEG;
+      for (int i = 0; i < (int)vcnt; ++i) {
+        uint32_t wd[2];
+        raw_words(src[i], wd);
+        st[(w * 32 + i) * EW] = wd[0];
+        if (EW == 2) st[(w * 32 + i) * EW + 1] = wd[1];
+      }
+    }
+  }
+}
+
+// ------------------------------------------------- per-wave fused batches
+// The fused step of large uniform fp32 batches (more units than one pass of
+// the unit kernel below codes) by single waves, a whole superblock each: eight
+// waves a CU with two units' work per claim.  On an 8-rank ring of 256^3 (2048
+// waves, two superblocks each) 376 us against 407 us by units, whose 2816
+// workers pass over the 8192 units three times; from one pass down the unit
+// kernel is the faster (6 ranks of 4 M elements: 166 against 211 us).
+// A wave claims a superblock, builds its payload in LDS in two halves of 64
 // segments (lane l codes segment 64h + l), learns its offset and writes
-// payload, table word and header bytes.  There is no workgroup barrier, so
-// the waves of a CU are in different phases (loads, arithmetic, waits,
-// stores) at once.  Offsets come from a two-level scan: a workgroup claims
-// rounds of WAVES consecutive superblocks with one global ticket; inside a
-// round the waves combine their sizes through LDS, and the round is one
-// element of the decoupled look-back (a look-back per superblock measured
-// slower than strips: eight times as many chain elements published eight
-// times as fast outrun a 64-word probe within one memory round trip).
+// payload, table word and header bytes, with no workgroup barrier.  Offsets
+// come from a two-level scan: a workgroup claims rounds of WAVES consecutive
+// superblocks with one global ticket; inside a round the waves combine their
+// sizes through LDS, and the round is one element of the decoupled look-back.
 // Wave region (dwords): X and A, each 64 padded segments, and HB, the
-// superblock's header bytes.  Compression: input values through X, first
-// half's payload in A, second half's in X.  Fused step: the incoming payload
-// staged in X (whole, or half by half if it does not fit); each lane loads
-// its own addend row; the first half's sums (kept for RAW blocks) and then
-// payload in A, the second half's sums and payload in X.
+// superblock's header bytes.  The incoming payload is staged in X (whole, or
+// half by half if it does not fit); each lane loads its own addend row; the
+// first half's sums (kept for RAW blocks) and then payload in A, the second
+// half's sums and payload in X.
 struct WaveEnc {
   static constexpr uint32_t WAVES = 8;  // per workgroup
   static constexpr uint32_t STR = 36;   // seg_stride<float>()
   static constexpr uint32_t XW = 64 * STR, AW = 64 * STR, HBW = SUPER / 32 / 4;
   static constexpr uint32_t REGION = XW + AW + HBW + 4;
 };
-
-// One half's 2048 values src[0 .. hval) into registers, 16-byte loads, eight
-// per lane in flight (positions past hval read as 0).
-__device__ __forceinline__ void wave_half_load(const uint32_t* src, uint32_t hval, u4u (&r)[8]) {
-  const uint32_t lane = __lane_id();
-  if (hval == 64 * SEG) {
-#pragma unroll
-    for (uint32_t u = 0; u < 8; ++u) r[u] = ((const u4u*)src)[u * 64 + lane];
-    return;
-  }
-#pragma unroll
-  for (uint32_t u = 0; u < 8; ++u) {
-    const uint32_t dw = 4 * (u * 64 + lane);
-    if (dw + 4 <= hval) {
-      r[u] = *(const u4u*)(src + dw);
-    } else {
-      r[u].x = dw + 0 < hval ? src[dw + 0] : 0u;
-      r[u].y = dw + 1 < hval ? src[dw + 1] : 0u;
-      r[u].z = dw + 2 < hval ? src[dw + 2] : 0u;
-      r[u].w = 0u;
-    }
-  }
-}
 
 // The lane's own row of 32 values at src (vcnt valid, the rest 0): eight
 // 16-byte loads, each instruction touching a line per lane, nearly all L1
@@ -2343,25 +2432,6 @@ __device__ __forceinline__ void wave_row_load(const uint32_t* src, uint32_t vcnt
   }
 }
 
-// Registers of wave_half_load into X's padded segment layout.
-__device__ __forceinline__ void wave_regs_to_x(const u4u (&r)[8], uint32_t* X) {
-  const uint32_t lane = __lane_id();
-#pragma unroll
-  for (uint32_t u = 0; u < 8; ++u) {
-    const uint32_t dw = 4 * (u * 64 + lane);
-    *(u4u*)(X + (dw / SEG) * WaveEnc::STR + dw % SEG) = r[u];
-  }
-}
-
-__device__ __forceinline__ void wave_row_get(const uint32_t* X, float (&v)[32]) {
-  const f4u* p = (const f4u*)(X + __lane_id() * WaveEnc::STR);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const f4u r = p[k];
-    v[4 * k] = r.x; v[4 * k + 1] = r.y; v[4 * k + 2] = r.z; v[4 * k + 3] = r.w;
-  }
-}
-
 __device__ __forceinline__ void wave_row_put(uint32_t* X, const float (&v)[32]) {
   f4u* p = (f4u*)(X + __lane_id() * WaveEnc::STR);
 #pragma unroll
@@ -2369,34 +2439,6 @@ __device__ __forceinline__ void wave_row_put(uint32_t* X, const float (&v)[32]) 
     f4u r;
     r.x = v[4 * k]; r.y = v[4 * k + 1]; r.z = v[4 * k + 2]; r.w = v[4 * k + 3];
     p[k] = r;
-  }
-}
-
-// The lane's share of its block's payload at st (the block's first word):
-// base, sign word and planes of an L1D block, or the values of a RAW block
-// (from registers, re-derived by the fused step, or re-read from J.in).
-template <int L, bool FUSED, bool FULL>
-__device__ __forceinline__ void wave_pack(const Job& J, uint64_t seg, uint32_t w, uint32_t vcnt,
-                                          const LaneCode& lc, const FusedSrc& fs, uint32_t* st) {
-  constexpr uint32_t LPB = L / 32;
-  if (lc.kind == K_L1D) {
-    if (w == 0) st[0] = (uint32_t)lc.base;
-    if (lc.F) {
-      st[1 + w] = lc.sg;
-      put_planes(lc.a, lc.F, st + 1 + LPB + w, LPB);
-    }
-  }
-  if (FUSED && lc.kind == K_RAW && lc.rawregs) {
-#pragma unroll
-    for (int i = 0; i < 32; ++i)  // unrolled: a[] stays in registers
-      if (FULL || i < (int)vcnt) st[w * 32 + i] = lc.a[i];
-  } else if (lc.kind == K_RAW) {  // blocks too wide to code (rare)
-    if (FUSED) {
-      fused_raw_stage<LPB>(J, fs, seg, w, vcnt, st);
-    } else {
-      const float* src = (const float*)J.in + seg * SEG;
-      for (int i = 0; i < (int)vcnt; ++i) st[w * 32 + i] = __float_as_uint(src[i]);
-    }
   }
 }
 
@@ -2420,7 +2462,7 @@ __device__ __forceinline__ void wave_unit_preload(const Job& J, uint64_t u, Unit
 // tot[0] payload dwords in A, tot[1] in X, header bytes in HB; good is false
 // for a malformed incoming superblock.  pub(size) is called with the whole
 // size as soon as it is known, before the second half is packed.
-template <int L, bool FUSED, bool FULL, class Pub>
+template <int L, bool FULL, class Pub>
 __device__ __forceinline__ void wave_encode_unit(const Job& J, uint64_t u, uint32_t* R,
                                                  uint32_t (&tot)[2], bool& good,
                                                  const UnitPre& ahead, const Pub& pub) {
@@ -2433,18 +2475,13 @@ __device__ __forceinline__ void wave_encode_unit(const Job& J, uint64_t u, uint3
   const uint64_t e0 = u * SUPER;
   const uint32_t nval = FULL ? SUPER : (uint32_t)min((uint64_t)SUPER, J.n - e0);
   const uint8_t* in = (const uint8_t*)J.in;
-  u4u pre[8];  // compression: the input half in flight
-  if (!FUSED)
-    wave_half_load((const uint32_t*)((const float*)J.in + e0),
-                   FULL ? HALF : (uint32_t)min((uint32_t)HALF, nval), pre);
-
   // the incoming superblock's layout (fused step)
   good = true;
   WaveBlocks wb = {};
   FusedSrc fs;
   fs.pay = (const uint32_t*)(in + J.pay_off);
   fs.t = 0.0f;
-  if (FUSED) {
+  {
     uint64_t paydw = 0;
     UnitPre p = ahead;
     if (!p.valid) wave_unit_preload<L>(J, u, p);  // table words with the header's
@@ -2454,7 +2491,7 @@ __device__ __forceinline__ void wave_encode_unit(const Job& J, uint64_t u, uint3
   // the whole incoming payload is staged at once when its realigned copy
   // fits X (always, at any ratio above about 1.8)
   const uint32_t Ptot = good ? (uint32_t)(wb.En - wb.E) : 0u;
-  const bool whole = FUSED && Ptot + 8 <= WaveEnc::XW;
+  const bool whole = Ptot + 8 <= WaveEnc::XW;
   const uint32_t* S = X;
 
 #pragma unroll
@@ -2464,55 +2501,41 @@ __device__ __forceinline__ void wave_encode_unit(const Job& J, uint64_t u, uint3
     const uint64_t seg = e0 / SEG + 64 * h + lane;
     const uint32_t vcnt = FULL ? 32u : (uint32_t)min(32, max(0, (int)hval - 32 * (int)lane));
     float v[32];
-    if (FUSED) {
-      uint32_t* AD = h ? X : A;  // the sums' rows
-      const uint32_t hoff = (h && !whole) ? wb.half0 : 0u;
-      if (good && (h == 0 || !whole)) {
-        const uint32_t P = whole ? Ptot : (h ? Ptot - wb.half0 : wb.half0);
-        S = wave_stage_payload<SUPER, false>(fs.pay + wb.E + hoff, P, X);
-      }
-      // the lane's own 32 addend values, in flight during the decode (a
-      // coalesced load transposed through LDS measured slower here)
-      u4u lr[8];
-      wave_row_load<FULL>((const uint32_t*)(J.local + e0 + h * HALF) + 32 * lane, vcnt, lr);
-      if (good) {
-        wave_lds_sync();
-        unpack_seg<float, LPB, FULL>(S + (wb.boff[h] - hoff), wb.kind[h], wb.F[h], w, vcnt,
-                                     wb.ex[h], fs.t, v);
-        fs.di.off_dw = (uint32_t)wb.E + wb.boff[h];
-        fs.di.kind = wb.kind[h];
-        fs.di.F = wb.F[h];
-      } else {
-#pragma unroll
-        for (int i = 0; i < 32; ++i) v[i] = 0.0f;
-        fs.di.off_dw = 0;
-        fs.di.kind = K_ZERO;
-        fs.di.F = 0;
-      }
-      wave_lds_sync();  // payload words read before X takes the sums
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {  // incoming + local, fp32
-        v[4 * k] = v[4 * k] + __uint_as_float(lr[k].x);
-        v[4 * k + 1] = v[4 * k + 1] + __uint_as_float(lr[k].y);
-        v[4 * k + 2] = v[4 * k + 2] + __uint_as_float(lr[k].z);
-        v[4 * k + 3] = v[4 * k + 3] + __uint_as_float(lr[k].w);
-      }
-      wave_row_put(AD, v);  // the sums, for a RAW block (own row)
-    } else {
-      // the first half's loads were issued by the caller (pre); the second
-      // half's go out as soon as the first half's registers are free
-      wave_regs_to_x(pre, X);
-      wave_lds_sync();
-      wave_row_get(X, v);
-      if (h == 0) {
-        const uint32_t h1 =
-            FULL ? HALF : (uint32_t)min((int)HALF, max(0, (int)nval - (int)HALF));
-        wave_half_load((const uint32_t*)((const float*)J.in + e0 + HALF), h1, pre);
-      }
+    uint32_t* AD = h ? X : A;  // the sums' rows
+    const uint32_t hoff = (h && !whole) ? wb.half0 : 0u;
+    if (good && (h == 0 || !whole)) {
+      const uint32_t P = whole ? Ptot : (h ? Ptot - wb.half0 : wb.half0);
+      S = wave_stage_payload<SUPER, false>(fs.pay + wb.E + hoff, P, X);
     }
+    // the lane's own 32 addend values, in flight during the decode (a
+    // coalesced load transposed through LDS measured slower here)
+    u4u lr[8];
+    wave_row_load<FULL>((const uint32_t*)(J.local + e0 + h * HALF) + 32 * lane, vcnt, lr);
+    if (good) {
+      wave_lds_sync();
+      unpack_seg<float, LPB, FULL>(S + (wb.boff[h] - hoff), wb.kind[h], wb.F[h], w, vcnt,
+                                   wb.ex[h], fs.t, v);
+      fs.di.off_dw = (uint32_t)wb.E + wb.boff[h];
+      fs.di.kind = wb.kind[h];
+      fs.di.F = wb.F[h];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 32; ++i) v[i] = 0.0f;
+      fs.di.off_dw = 0;
+      fs.di.kind = K_ZERO;
+      fs.di.F = 0;
+    }
+    wave_lds_sync();  // payload words read before X takes the sums
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {  // incoming + local, fp32
+      v[4 * k] = v[4 * k] + __uint_as_float(lr[k].x);
+      v[4 * k + 1] = v[4 * k + 1] + __uint_as_float(lr[k].y);
+      v[4 * k + 2] = v[4 * k + 2] + __uint_as_float(lr[k].z);
+      v[4 * k + 3] = v[4 * k + 3] + __uint_as_float(lr[k].w);
+    }
+    wave_row_put(AD, v);  // the sums, for a RAW block (own row)
     LaneCode lc;
-    analyze_1d<float, L, FULL, FUSED>(J, seg, w, v, vcnt, lc,
-                                      FUSED ? (h ? X : A) + lane * WaveEnc::STR : nullptr);
+    analyze_1d<float, L, FULL, true>(J, seg, w, v, vcnt, lc, AD + lane * WaveEnc::STR);
     const uint32_t contrib = w == 0 ? lc.size_dw : 0u;
     const uint32_t incl = wave_incl_scan(contrib);
     const uint32_t boff = w == 0 ? incl - contrib : incl - lc.size_dw;
@@ -2522,7 +2545,7 @@ __device__ __forceinline__ void wave_encode_unit(const Job& J, uint64_t u, uint3
       ((uint8_t*)HB)[(64 * h + lane) / LPB] =
           (uint8_t)(lc.exists ? ((lc.kind << 5) | lc.F) : 0u);
     wave_lds_sync();  // every row of X is read before the second half's payload goes there
-    wave_pack<L, FUSED, FULL>(J, seg, w, vcnt, lc, fs, (h ? X : A) + boff);
+    wave_pack<float, L, true, FULL>(J, seg, w, vcnt, lc, fs, (h ? X : A) + boff);
   }
   wave_lds_sync();  // A, X and HB are complete
 }
@@ -2561,7 +2584,7 @@ __device__ __forceinline__ void wave_write_unit(const Job& J, uint64_t u, uint64
 // claim again, so the ticket is held for about one write-out and the
 // round's first claimer need not wait for the atomic (a round past the end
 // hands on a ticket past the end; round 0's first claimer takes its own).
-// Slot s of the round is superblock WAVES * (T's round within its job) + s.  Per round (a ring of RING
+// Slot s of the round is superblock WAVES * (T's round within its job) + s.  Per round (a ring of WRING
 // entries in LDS): the slots' sizes, a count of them, and the round's
 // exclusive prefix, fetched by one elected wave with the look-back over
 // rounds.  The wave that completes the count publishes the round's
@@ -2573,10 +2596,10 @@ __device__ __forceinline__ void wave_write_unit(const Job& J, uint64_t u, uint64
 // Deadlock freedom: every wait is on earlier rounds (tickets handed to
 // running workgroups) or on earlier slots of the same round (claimed
 // before, by waves of the same workgroup); the first claimer of a round
-// waits for the round RING earlier in the same entry to be released by all
+// waits for the round WRING earlier in the same entry to be released by all
 // its claimers, each of which releases it once.  Nothing assumes that the
 // grid's workgroups are resident together, and every wait is bounded.
-constexpr uint32_t RING = 4;
+constexpr uint32_t WRING = 4;
 constexpr uint32_t SIZE_NONE = 0xFFFFFFFFu;
 
 struct RoundState {
@@ -2593,7 +2616,7 @@ struct RoundState {
 };
 struct WaveSched {
   uint32_t claim;
-  RoundState rs[RING];
+  RoundState rs[WRING];
 };
 
 // Clears the schedule (before the workgroup's first barrier).
@@ -2601,38 +2624,13 @@ __device__ __forceinline__ void wave_sched_init(WaveSched& ws) {
   if (threadIdx.x == 0) {
     ws.claim = 0;
 #pragma unroll
-    for (uint32_t i = 0; i < RING; ++i) {
+    for (uint32_t i = 0; i < WRING; ++i) {
       ws.rs[i].ready = 0;
       ws.rs[i].pflag = 0;
       ws.rs[i].released = WaveEnc::WAVES;
     }
   }
   __syncthreads();
-}
-
-__device__ __forceinline__ uint32_t lds_load_acq(const uint32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-__device__ __forceinline__ void lds_store_rel(uint32_t* p, uint32_t v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// Bounded wait until *p >= want (lane 0 polls); false on timeout.
-__device__ __forceinline__ bool lds_wait_ge(const Ctl& C, const uint32_t* p, uint32_t want) {
-  uint32_t ok = 1;
-  if (__lane_id() == 0) {
-    uint32_t spins = 0;
-    uint64_t t0 = 0;
-    while (lds_load_acq(p) < want) {
-      if (wait_over(C, ++spins, t0)) {
-        atomicOr(&C.ctrl->err, ERRF_TIMEOUT);
-        ok = 0;
-        break;
-      }
-      __builtin_amdgcn_s_sleep(1);
-    }
-  }
-  return read_lane(ok, 0) != 0;
 }
 
 struct Claim {
@@ -2673,7 +2671,7 @@ __device__ __forceinline__ Claim wave_claim_try(const Ctl& C, WaveSched& ws) {
   c.slot = k % WaveEnc::WAVES;
   c.ticket = 0xFFFFFFFFu;
   c.done = false;
-  RoundState& rs = ws.rs[c.round % RING];
+  RoundState& rs = ws.rs[c.round % WRING];
   uint32_t ok = 0;
   if (lane == 0)
     ok = c.slot == 0
@@ -2691,7 +2689,7 @@ __device__ __forceinline__ Claim wave_claim_try(const Ctl& C, WaveSched& ws) {
 __device__ __forceinline__ void wave_claim_finish(const Ctl& C, WaveSched& ws, Claim& c) {
   if (c.done) return;
   c.done = true;
-  RoundState& rs = ws.rs[c.round % RING];
+  RoundState& rs = ws.rs[c.round % WRING];
   if (c.slot == 0) {
     // the entry's previous round has been released by all its claimers, and
     // the round's ticket has been handed on by the previous round
@@ -2714,7 +2712,7 @@ __device__ __forceinline__ Claim wave_claim(const Ctl& C, WaveSched& ws) {
 // Hands round r + 1 its ticket (lane 0): a fresh one, or t past the end.
 __device__ __forceinline__ void wave_hand_on(const Ctl& C, WaveSched& ws, uint32_t r,
                                              uint32_t t, bool fresh) {
-  RoundState& nx = ws.rs[(r + 1) % RING];
+  RoundState& nx = ws.rs[(r + 1) % WRING];
   nx.pticket = fresh ? atomicAdd(&C.ctrl->ticket, 1u) : t;
   lds_store_rel(&nx.pflag, r + 2);
 }
@@ -2737,13 +2735,13 @@ __device__ __forceinline__ uint32_t round_sum(const RoundState& rs) {
 // encodes it into the wave's region and finds its offset (off, dwords).
 // True if the unit is to be written out (wave_write_unit); the caller then
 // releases the slot.
-template <int L, bool FUSED>
+template <int L>
 __device__ __forceinline__ bool wave_round_begin(const Job& J, uint64_t u, const Claim& cl,
                                                  WaveSched& ws, uint64_t gs, uint64_t chain0,
                                                  const Ctl& C, uint32_t ep, uint32_t* R,
                                                  const UnitPre& pre, uint32_t (&tot)[2],
                                                  uint64_t& off) {
-  RoundState& rs = ws.rs[cl.round % RING];
+  RoundState& rs = ws.rs[cl.round % WRING];
   const uint32_t lane = __lane_id();
   const bool live = u < J.NS;
   tot[0] = tot[1] = 0u;
@@ -2768,8 +2766,8 @@ __device__ __forceinline__ bool wave_round_begin(const Job& J, uint64_t u, const
     }
   };
   if (live) {
-    if ((u + 1) * SUPER <= J.n) wave_encode_unit<L, FUSED, true>(J, u, R, tot, good, pre, pub);
-    else wave_encode_unit<L, FUSED, false>(J, u, R, tot, good, pre, pub);
+    if ((u + 1) * SUPER <= J.n) wave_encode_unit<L, true>(J, u, R, tot, good, pre, pub);
+    else wave_encode_unit<L, false>(J, u, R, tot, good, pre, pub);
   } else {
     pub(0u);
     return false;
@@ -2825,48 +2823,11 @@ __device__ __forceinline__ uint64_t rounds_of(uint64_t NS) {
   return (NS + WaveEnc::WAVES - 1) / WaveEnc::WAVES;
 }
 
-// One stream: round ticket T covers superblocks WAVES * T + slot, look-back
-// word T.
-template <int L, bool FUSED>
-__global__ GZ_WAVE_ATTR void k_encode_w(Job J, Ctl C) {
-  __shared__ WaveSched ws;
-  wave_sched_init(ws);
-  uint32_t* R = g_stage + (threadIdx.x >> 6) * WaveEnc::REGION;
-  const uint32_t ep = ld_agent32(&C.ctrl->epoch);
-  const uint64_t NR = rounds_of(J.NS);
-  Claim cl = wave_claim(C, ws);
-  UnitPre pre;
-  pre.valid = false;
-  for (;;) {
-    RoundState& rs = ws.rs[cl.round % RING];
-    if (cl.ticket >= NR) {  // past the end (or timed out)
-      if (cl.slot == 0 && __lane_id() == 0) wave_hand_on(C, ws, cl.round, cl.ticket, false);
-      wave_release(rs);
-      break;
-    }
-    const uint64_t u = (uint64_t)cl.ticket * WaveEnc::WAVES + cl.slot;
-    uint32_t tot[2];
-    uint64_t off = 0;
-    const bool wr = wave_round_begin<L, FUSED>(J, u, cl, ws, cl.ticket, 0, C, ep, R, pre, tot, off);
-    // the next slot, and its first words ahead of this unit's stores
-    Claim nx = wave_claim_try(C, ws);
-    pre.valid = false;
-    if (FUSED && nx.done && nx.ticket < NR) {
-      const uint64_t v = (uint64_t)nx.ticket * WaveEnc::WAVES + nx.slot;
-      if (v < J.NS) wave_unit_preload<L>(J, v, pre);
-    }
-    if (wr) wave_write_unit<L>(J, u, off, tot, R);
-    wave_release(rs);
-    wave_claim_finish(C, ws, nx);
-    cl = nx;
-  }
-  epilogue(C);
-}
 // njobs streams of NS superblocks each (total = njobs x rounds per job),
 // every one its own chain: round ticket T is round T / njobs of job
 // T % njobs, look-back word j x rounds + round.
-template <int L, bool FUSED>
-__global__ GZ_WAVE_ATTR void k_batch_encode_w(const Job* __restrict__ jobs, uint32_t njobs,
+template <int L>
+__global__ GZ_WAVE_ATTR void k_batch_fused_w(const Job* __restrict__ jobs, uint32_t njobs,
                                               uint32_t total, Ctl C) {
   __shared__ WaveSched ws;
   wave_sched_init(ws);
@@ -2876,7 +2837,7 @@ __global__ GZ_WAVE_ATTR void k_batch_encode_w(const Job* __restrict__ jobs, uint
   UnitPre pre;
   pre.valid = false;
   for (;;) {
-    RoundState& rs = ws.rs[cl.round % RING];
+    RoundState& rs = ws.rs[cl.round % WRING];
     if (cl.ticket >= total) {  // past the end (or timed out)
       if (cl.slot == 0 && __lane_id() == 0) wave_hand_on(C, ws, cl.round, cl.ticket, false);
       wave_release(rs);
@@ -2889,11 +2850,11 @@ __global__ GZ_WAVE_ATTR void k_batch_encode_w(const Job* __restrict__ jobs, uint
     uint32_t tot[2];
     uint64_t off = 0;
     const bool wr =
-        wave_round_begin<L, FUSED>(J, u, cl, ws, j * NR + r, j * NR, C, ep, R, pre, tot, off);
+        wave_round_begin<L>(J, u, cl, ws, j * NR + r, j * NR, C, ep, R, pre, tot, off);
     // the next slot, and its first words ahead of this unit's stores
     Claim nx = wave_claim_try(C, ws);
     pre.valid = false;
-    if (FUSED && nx.done && nx.ticket < total) {
+    if (nx.done && nx.ticket < total) {
       const Job& K = jobs[nx.ticket % njobs];
       const uint64_t v = (uint64_t)(nx.ticket / njobs) * WaveEnc::WAVES + nx.slot;
       if (v < K.NS) wave_unit_preload<L>(K, v, pre);
@@ -2904,6 +2865,606 @@ __global__ GZ_WAVE_ATTR void k_batch_encode_w(const Job* __restrict__ jobs, uint
     cl = nx;
   }
   epilogue(C);
+}
+
+// ------------------------------------------------------------ unit encode
+// 1D encoding (compression of either type, and the fp32 fused step) by
+// single waves.  A wave codes a unit of 64 segments (2048 elements, half a
+// superblock; lane l owns segment l): it builds the unit's payload in LDS,
+// and writes it, its table word (first half of a superblock) and its header
+// bytes once its offset is known.  There is no workgroup barrier, so the waves
+// of a CU are in different phases (loads, arithmetic, stores) at once, and a
+// short stream spreads over many CUs.
+//
+// Offsets come from a two-level scan: the W working waves of a workgroup
+// code W consecutive units, a round (wave w: unit W r + w); inside a round
+// sizes are combined through LDS, and the round is one element of the
+// decoupled look-back, which the workgroup's last wave, the scheduler, runs.
+// A worker does not wait for its offset: small payloads are held in LDS, up
+// to two of them, while the wave analyses its next units, and written later.
+// (A prefix is known once the slowest of the ~4000 units in flight before it
+// has published: 4-9 us after a round's own sizes, more than the 6 us a unit
+// takes.)  Payloads too large to be held twice are written at once, after a
+// wait: holding one of them made the next wait as long and delayed the next
+// ticket (2^27 fp32 values at ratio 2: 246 us held, 229 written at once).
+//
+// Bound by VALU and scalar issue behind the latency of loads and stores, not
+// by the prefix: a copy that did not wait for offsets took the same time.
+// Before (strips; the fused step by superblocks) and after: 2^14 fp32 values
+// 13.9 -> 9.6 us, 1 GiB 408 -> 386 us, 20 M fp64 values 85 -> 55 us, a batch
+// of 512 mixed requests compressed and decompressed 317 -> 270 us, one fused
+// step of 2 M values 24.1 -> 17.4 us, a ring Allreduce of 6 x 4 M 215 -> 175 us.
+template <bool FUSED>
+struct UnitEnc {
+  static constexpr uint32_t SEGS = 64;
+  // rows of 32 dwords (the fused step's incoming payload, then its addend and
+  // sums); compression stages half rows of 16 at a time
+  static constexpr uint32_t STR = FUSED ? 36 : 20;
+  static constexpr uint32_t XW = SEGS * STR;            // staging (dwords)
+  static constexpr uint32_t QW = FUSED ? 1344 : 1392;   // payloads held
+  static constexpr uint32_t HELD = FUSED ? QW : QW / 2; // largest payload held
+  static constexpr uint32_t HBW = SEGS / 4;             // header bytes
+  static constexpr uint32_t PACKW = FUSED ? XW : XW + QW;  // payloads not held
+  static constexpr uint32_t REGION = XW + QW + HBW;     // per worker
+  static constexpr uint32_t MAXW = FUSED ? UNIT_WORKERS_FUSED : UNIT_WORKERS;
+};
+
+// 16-byte chunk i = 64 k + lane, k < 8, of 64 rows of 32 dwords that lie
+// stride dwords apart at src: row i / 8, chunk i % 8.  vdw: valid dwords from
+// src; the rest read as 0.
+template <uint32_t STRIDE, bool FULL>
+__device__ __forceinline__ void unit_rows_load(const uint32_t* src, uint32_t vdw, u4u (&r)[8]) {
+  const uint32_t lane = __lane_id();
+#pragma unroll
+  for (uint32_t k = 0; k < 8; ++k) {
+    const uint32_t i = 64 * k + lane;
+    const uint32_t dw = STRIDE == 32 ? 4 * i : (i / 8) * STRIDE + 4 * (i % 8);
+    if (FULL || dw + 4 <= vdw) {
+      r[k] = *(const u4u*)(src + dw);
+    } else {
+      r[k].x = dw + 0 < vdw ? src[dw + 0] : 0u;
+      r[k].y = dw + 1 < vdw ? src[dw + 1] : 0u;
+      r[k].z = dw + 2 < vdw ? src[dw + 2] : 0u;
+      r[k].w = 0u;
+    }
+  }
+}
+
+// Those chunks into rows STR dwords apart in LDS: the whole rows, or half h
+// of each (by the lanes that hold it).
+template <uint32_t STR>
+__device__ __forceinline__ void unit_rows_put(const u4u (&r)[8], uint32_t* X) {
+  const uint32_t lane = __lane_id();
+#pragma unroll
+  for (uint32_t k = 0; k < 8; ++k) *(u4u*)(X + (8 * k + lane / 8) * STR + 4 * (lane % 8)) = r[k];
+}
+template <uint32_t STR>
+__device__ __forceinline__ void unit_halves_put(const u4u (&r)[8], uint32_t h, uint32_t* X) {
+  const uint32_t lane = __lane_id();
+  if (((lane >> 2) & 1) == h) {
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) *(u4u*)(X + (8 * k + lane / 8) * STR + 4 * (lane % 4)) = r[k];
+  }
+}
+
+// The lane's block of unit 2 sb + h of an incoming fp32 stream (fused step):
+// kind, width and offset inside the unit's payload, P dwords at off0 from
+// the payload's start.  False if superblock sb is malformed.
+struct UnitIn {
+  uint32_t off0, P, kind, F, boff;
+  bool ex;
+};
+
+template <int L>
+__device__ __forceinline__ bool unit_in_eval(const Job& J, uint64_t sb, uint32_t h,
+                                             uint64_t paydw, uint32_t nval,
+                                             const uint32_t (&raw)[3], UnitIn& ui) {
+  WaveBlocks wb;
+  const bool good = wave_blocks_eval<float, L>(J, sb, paydw, nval, raw, wb);
+  ui.kind = h ? wb.kind[1] : wb.kind[0];
+  ui.F = h ? wb.F[1] : wb.F[0];
+  ui.ex = h ? wb.ex[1] : wb.ex[0];
+  ui.boff = h ? wb.boff[1] - wb.half0 : wb.boff[0];
+  ui.off0 = (uint32_t)wb.E + (h ? wb.half0 : 0u);
+  ui.P = h ? (uint32_t)(wb.En - wb.E) - wb.half0 : wb.half0;
+  return good;
+}
+
+// Loads and analyses unit u of job J (fused: incoming stream J.in plus
+// addend J.local): the lane's code lc and, for RAW blocks of the fused step,
+// its source fs.  X is free for the payload afterwards.
+template <typename T, int L, bool FUSED, bool FULL>
+__device__ __forceinline__ void unit_analyse(const Job& J, uint64_t u, uint32_t w, uint32_t vcnt,
+                                             uint32_t* X, LaneCode& lc, FusedSrc& fs,
+                                             bool& good) {
+  constexpr uint32_t LPB = L / 32, EW = sizeof(T) / 4, STR = UnitEnc<FUSED>::STR;
+  const uint32_t lane = __lane_id();
+  const uint64_t e0 = u * (uint32_t)UNIT_ELEMS, seg = u * 64 + lane;
+  const uint32_t hval = FULL ? (uint32_t)UNIT_ELEMS : (uint32_t)min((uint64_t)(uint32_t)UNIT_ELEMS, J.n - e0);
+  good = true;
+  if constexpr (FUSED) {
+    const uint8_t* in = (const uint8_t*)J.in;
+    const uint64_t sb = u >> 1;
+    uint32_t raw[3];
+    const uint32_t hdr = wave_header_load(J, in);
+    wave_blocks_load<L, true>(J, in, sb, raw);  // table words with the header's
+    u4u lr[8];  // the unit's addend, in flight until the add
+    unit_rows_load<32, FULL>((const uint32_t*)(J.local + e0), hval, lr);
+    uint64_t paydw = 0;
+    good = wave_header_eval<float>(J, hdr, paydw, fs.t);
+    UnitIn ui;
+    if (good)
+      good = unit_in_eval<L>(J, sb, (uint32_t)(u & 1), paydw,
+                             (uint32_t)min((uint64_t)SUPER, J.n - sb * SUPER), raw, ui);
+    fs.pay = (const uint32_t*)(in + J.pay_off);
+    float v[32];
+    if (good) {
+      const uint32_t* S = wave_stage_payload<(uint32_t)UNIT_ELEMS, false>(fs.pay + ui.off0, ui.P, X);
+      wave_lds_sync();
+      unpack_seg<float, LPB, FULL>(S + ui.boff, ui.kind, ui.F, w, vcnt, ui.ex, fs.t, v);
+      fs.di.off_dw = ui.off0 + ui.boff;
+      fs.di.kind = ui.kind;
+      fs.di.F = ui.F;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 32; ++i) v[i] = 0.0f;
+      fs.di.off_dw = 0;
+      fs.di.kind = K_ZERO;
+      fs.di.F = 0;
+    }
+    // the addend through X (each lane reading its own row from memory touches
+    // 64 lines per load, and at 12 waves a CU the L1 does not hold them until
+    // the row's last load: a ring step 62 -> 51 us)
+    wave_lds_sync();  // payload words read before X takes the addend
+    unit_rows_put<STR>(lr, X);
+    wave_lds_sync();
+    {
+      f4u* p = (f4u*)(X + lane * STR);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {  // incoming + local, fp32; the sum stays for RAW blocks
+        f4u r = p[k];
+        r.x = v[4 * k] = v[4 * k] + r.x;
+        r.y = v[4 * k + 1] = v[4 * k + 1] + r.y;
+        r.z = v[4 * k + 2] = v[4 * k + 2] + r.z;
+        r.w = v[4 * k + 3] = v[4 * k + 3] + r.w;
+        p[k] = r;
+      }
+    }
+    analyze_1d<float, L, FULL, true>(J, seg, w, v, vcnt, lc, X + lane * STR);
+  } else {
+    // half rows of 16 dwords at a time through LDS (16 fp32 or 8 fp64 values),
+    // so that payloads of earlier units can be held there; fp64's second 32
+    // dwords of each row are loaded while the first are quantised
+    const uint32_t* src = (const uint32_t*)((const T*)J.in + e0);
+    const uint32_t vdw = hval * EW;
+    u4u r[8];
+    unit_rows_load<32 * EW, FULL>(src, vdw, r);
+    QBad<T> qb;
+#pragma unroll
+    for (uint32_t p = 0; p < 2 * EW; ++p) {
+      constexpr uint32_t HV = 16 / EW;  // values per half row
+      unit_halves_put<STR>(r, p & 1, X);
+      if (EW == 2 && p == 1) unit_rows_load<32 * EW, FULL>(src + 32, vdw > 32 ? vdw - 32 : 0u, r);
+      wave_lds_sync();
+      T val[HV];
+      const u4u* row = (const u4u*)(X + lane * STR);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const u4u d = row[k];
+        const uint32_t wd[4] = {d.x, d.y, d.z, d.w};
+#pragma unroll
+        for (uint32_t i = 0; i < 4 / EW; ++i) val[4 / EW * k + i] = from_raw(wd + EW * i, T());
+      }
+      wave_lds_sync();  // read before the next half rows go there
+      quant_run<HV, FULL>(val, J, vcnt > HV * p ? vcnt - HV * p : 0u, lc.a + HV * p, qb);
+    }
+    analyze_q<EW, L, FULL, false>(J, seg, w, qb.any(bad_bound<T>(J)), vcnt, lc);
+  }
+}
+
+// ---- rounds.  A workgroup's state: a ring of RING rounds in LDS and the
+// launch's epoch.  Round k of the workgroup (k = 0, 1, ...) sits in entry
+// k % RING.  The worker that publishes first in round k takes the ticket of
+// round k + 1, after it has written what it held (in flight while it packs),
+// and opens that round's entry: a ticket held during a wait for a prefix would
+// delay every later round's prefix (taken at the first publication: 852 us per
+// GiB).  The worker that publishes last also publishes the round's sum; the
+// scheduler then runs the look-back and puts the round's prefix into the entry.
+// Round k + 1 is opened once every worker has published round k - 1; a worker
+// that has holds nothing older than round k - 3, whose entry is reused four
+// rounds later still.
+// Deadlock freedom: a worker waits for the offset of a round only after
+// publishing it, and prefixes depend on earlier tickets only; tickets are
+// handed only to running workgroups, nothing assumes that the grid's
+// workgroups are resident together, and every wait is bounded.
+// Every workgroup takes exactly one ticket past the end, so the last of them
+// (total + workgroups - 1) ends the launch's use of the counter: its taker
+// resets counter and epoch for the next launch.
+constexpr uint32_t RING = 8;
+
+struct URound {
+  unsigned long long prefix;  // exclusive prefix of the round (dwords)
+  unsigned long long pj;      // the chain's prefix at the job's first round
+  uint32_t ticket;
+  uint32_t ready;   // 1 + round number once ticket (and the reset) is done
+  uint32_t cnt;     // sizes written
+  uint32_t pready;  // 1 + round number once prefix is set
+  uint32_t bad;     // 1: the prefix is not to be used (a wait expired)
+  uint32_t agg;     // 1 + round number once its aggregate's store has completed
+  uint32_t size[16];
+};
+struct USched {
+  uint32_t epoch;
+  uint32_t over;  // 1 once this workgroup has taken a ticket past the end
+  URound rs[RING];
+};
+
+// Ticket t has been taken (lane 0): the launch's last one resets the counter.
+__device__ __forceinline__ void unit_taken(const Ctl& C, USched& us, uint32_t t, uint32_t total) {
+  if (t < total) return;
+  us.over = 1;
+  if (t == total + gridDim.x - 1) {
+    atomicExch(&C.ctrl->ticket, 0u);
+    atomicAdd(&C.ctrl->epoch, 1u);
+  }
+}
+
+// Opens round k with ticket t (lane 0).
+__device__ __forceinline__ void unit_open(const Ctl& C, USched& us, uint32_t k, uint32_t t,
+                                          uint32_t total) {
+  unit_taken(C, us, t, total);
+  URound& e = us.rs[k % RING];
+  e.cnt = 0;
+  e.bad = 0;
+  e.ticket = t;
+  lds_store_rel(&e.ready, k + 1);
+}
+
+__device__ __forceinline__ void unit_begin(const Ctl& C, USched& us, uint32_t total) {
+  if (threadIdx.x == 0) {
+    us.epoch = ld_agent32(&C.ctrl->epoch);  // in hand before this workgroup's last ticket
+    us.over = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < RING; ++i) us.rs[i].ready = us.rs[i].pready = us.rs[i].agg = 0;
+    unit_open(C, us, 0, atomicAdd(&C.ctrl->ticket, 1u), total);
+  }
+  __syncthreads();
+}
+
+__device__ __forceinline__ void unit_end(const Ctl& C, USched& us, uint32_t total) {
+  __syncthreads();
+  if (threadIdx.x == 0)
+    while (!us.over) unit_taken(C, us, atomicAdd(&C.ctrl->ticket, 1u), total);  // after a timeout
+}
+
+// A round's place in its chain.
+struct UChain {
+  uint64_t gs, chain0;  // look-back words of the round and the chain's start
+  uint64_t r;           // round of the job
+  uint32_t job;
+  bool packed;          // the chain runs through several jobs
+};
+
+// The scheduler's step for round k: sizes, look-back, prefix.  False once a
+// wait expired.
+__device__ __forceinline__ bool unit_sched(const Ctl& C, USched& us, uint32_t k, uint32_t W,
+                                           const UChain& ch) {
+  URound& e = us.rs[k % RING];
+  const uint32_t lane = __lane_id(), ep = us.epoch;
+  if (!lds_wait_ge(C, &e.cnt, W)) return false;
+  const uint64_t agg = wave_sum64(lane < W ? e.size[lane] : 0u);
+  bool to = false;
+  const uint64_t prefix = lookback<LB_SUB, false>(C, ch.gs, ch.chain0, ep, agg, to);
+  uint64_t pj = 0;
+  if (ch.packed) {
+    if (ch.r == 0) {
+      if (lane == 0 && !to) st_agent(C.jobbase + ch.job, sw_pack(2, ep, prefix));
+      pj = prefix;
+    } else if (!to) {
+      pj = job_base_wait(C, ch.job, ep, to);
+    }
+  }
+  if (lane == 0) {
+    if (to) atomicOr(&C.ctrl->err, ERRF_TIMEOUT);
+    e.bad = to ? 1u : 0u;
+    e.prefix = prefix;
+    e.pj = pj;
+    lds_store_rel(&e.pready, k + 1);
+  }
+  // the inclusive prefix, once the aggregate cannot land after it (the head
+  // of a chain publishes its inclusive prefix as its aggregate)
+  if (ch.gs != ch.chain0 && !to && lds_wait_ge(C, &e.agg, k + 1) && lane == 0)
+    st_agent(C.status + ch.gs, sw_pack(2, ep, prefix + agg));
+  return true;
+}
+
+// A coded unit whose payload is held (size dwords at Q + at) until its offset
+// is known.
+struct UnitHeld {
+  uint32_t hb;                  // header-byte word `lane`
+  uint32_t at, size, k, job;    // k: round of the workgroup
+  uint64_t u;                   // unit of the job
+};
+// Up to two of them, h0 the older.
+struct UnitQueue {
+  UnitHeld h0, h1;
+  uint32_t n;
+};
+
+// Unit u's offset in its job's payload (dwords); pj: the chain's prefix at
+// the job's first round.  False if a wait expired.
+__device__ __forceinline__ bool unit_offset(const Ctl& C, USched& us, uint32_t k, uint32_t wid,
+                                            uint64_t& off, uint64_t& pj) {
+  URound& e = us.rs[k % RING];
+  const uint32_t lane = __lane_id();
+  if (!lds_wait_ge(C, &e.pready, k + 1) || e.bad) return false;
+  pj = e.pj;
+  // plus the round's earlier units (all sizes are there once the prefix is)
+  off = e.prefix - pj + wave_sum64(lane < wid ? e.size[lane] : 0u);
+  return true;
+}
+
+// Table word, header bytes and, for the job's last unit, stream header and
+// size outputs of unit u (size dwords at off); returns where its payload goes.
+template <int L>
+__device__ __forceinline__ uint32_t* unit_meta(const Job& J, uint64_t u, uint64_t off, uint64_t pj,
+                                               uint32_t size, uint32_t hb) {
+  constexpr uint32_t BPU = UNIT_ELEMS / L;
+  const uint32_t lane = __lane_id();
+  uint8_t* base8 = (uint8_t*)J.out + J.fixed_off + 4 * pj;
+  if (lane == 0 && !(u & 1) && (u >> 1) < J.NS) ((uint32_t*)(base8 + HDR))[u >> 1] = (uint32_t)off;
+  const uint64_t b0 = u * BPU;
+  if (lane < BPU / 4 && b0 + 4 * lane < J.B)
+    *(uint32_t*)(base8 + J.hdr_off + b0 + 4 * lane) = hb;
+  if ((u + 1) * UNIT_ELEMS >= J.n && lane < 16) {  // the last unit
+    const uint64_t payload = 4 * (off + size);
+    ((uint32_t*)base8)[lane] = hdr_word(J, lane, payload);
+    if (lane == 0) {
+      if (J.out_bytes) *J.out_bytes = J.pay_off + payload;
+      if (J.chunk_off) *J.chunk_off = J.fixed_off + 4 * pj;
+    }
+  }
+  return (uint32_t*)(base8 + J.pay_off) + off;
+}
+
+// Writes the oldest held unit (of job J).
+__device__ __forceinline__ void unit_flush(const Job& J, const Ctl& C, USched& us, uint32_t wid,
+                                           const uint32_t* Q, UnitQueue& q) {
+  const UnitHeld h = q.h0;
+  q.h0 = q.h1;
+  --q.n;
+  uint64_t off, pj;
+  if (!unit_offset(C, us, h.k, wid, off, pj)) return;
+  uint32_t* dst = J.log2L == 5   ? unit_meta<32>(J, h.u, off, pj, h.size, h.hb)
+                  : J.log2L == 6 ? unit_meta<64>(J, h.u, off, pj, h.size, h.hb)
+                                 : unit_meta<128>(J, h.u, off, pj, h.size, h.hb);
+  for (uint32_t i = __lane_id(); i < h.size; i += 64) dst[i] = Q[h.at + i];
+}
+
+// One unit: round k of the workgroup is round r of job J (index job); worker
+// wid codes unit u = W r + wid (past the job's end: an empty slot).  flush(q)
+// writes the oldest unit held.
+template <typename T, int L, bool FUSED, bool FULL, class Flush>
+__device__ __forceinline__ void unit_code(const Job& J, uint32_t job, uint64_t gs, uint64_t u,
+                                          bool live, uint32_t k, uint32_t wid, uint32_t W,
+                                          uint32_t total, USched& us, const Ctl& C,
+                                          uint32_t* X, UnitQueue& q, const Flush& flush) {
+  using U = UnitEnc<FUSED>;
+  constexpr uint32_t LPB = L / 32;
+  const uint32_t lane = __lane_id(), w = lane & (LPB - 1);
+  uint32_t* Q = X + U::XW;
+  uint32_t* HB = Q + U::QW;
+  const uint64_t e0 = u * UNIT_ELEMS, seg = u * U::SEGS + lane;
+  LaneCode lc;
+  FusedSrc fs;
+  uint32_t size = 0, boff = 0, vcnt = 32;
+  bool good = true;
+  // a unit's size is on every later round's way: it goes before packing and
+  // writing on the same SIMD (ring Reduce_scatter by units 423 -> 402 us)
+  __builtin_amdgcn_s_setprio(2);
+  if (live) {
+    if (!FULL)
+      vcnt = (uint32_t)min((int64_t)32, max((int64_t)0, (int64_t)(J.n - e0) - 32 * (int64_t)lane));
+    unit_analyse<T, L, FUSED, FULL>(J, u, w, vcnt, X, lc, fs, good);
+    const uint32_t contrib = w == 0 ? lc.size_dw : 0u;
+    const uint32_t incl = wave_incl_scan(contrib);
+    boff = w == 0 ? incl - contrib : incl - lc.size_dw;
+    size = read_lane(incl, 63);
+  }
+  __builtin_amdgcn_s_setprio(0);
+  URound& e = us.rs[k % RING];
+  uint32_t c = 0;
+  if (lane == 0) {
+    e.size[wid] = size;
+    c = 1 + __hip_atomic_fetch_add(&e.cnt, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  // the round's last size: publish their sum at once (the scheduler may still
+  // be in the look-back of the round before, which must not hold it up)
+  c = read_lane(c, 0);
+  const bool held = size <= U::HELD, first = c == 1;
+  if (c == W) {
+    const uint64_t agg = wave_sum64(lane < W ? e.size[lane] : 0u);
+    if (lane == 0) {
+      publish_agg(C, gs, J.chain0, us.epoch, agg);
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): that store has completed
+      lds_store_rel(&e.agg, k + 1);
+    }
+  }
+  // the next round's entry is free once every worker has published round k - 1
+  auto open = [&](uint32_t t) {
+    const bool free = k == 0 || lds_wait_ge(C, &us.rs[(k - 1) % RING].cnt, W);
+    if (lane == 0) {
+      if (free) unit_open(C, us, k + 1, t, total);
+      else unit_taken(C, us, t, total);
+    }
+  };
+  // room for this unit's payload: beside the newest one held, or where the
+  // oldest ones were.  Units of two rounds ago and older are written whatever
+  // the room (a worker may be past the end of many short jobs in a row, and
+  // their rounds' entries are reused)
+  uint32_t at = 0;
+  if (!held) {
+    while (q.n) flush(q);
+  } else {
+    while (q.n && (q.n == 2 || q.h0.k + 1 < k)) flush(q);
+    if (q.n) {
+      const uint32_t end = q.h0.at + q.h0.size;
+      if (end + size <= U::QW) at = end;
+      else if (size > q.h0.at) flush(q);
+    }
+  }
+  uint32_t tk = 0;
+  if (first && held) {
+    if (lane == 0) tk = atomicAdd(&C.ctrl->ticket, 1u);  // in flight while packing
+    if (!live) open(tk);
+  }
+  if (!live) return;
+  if (!good && lane == 0) atomicOr(&C.ctrl->err, ERRF_CORRUPT);
+  if (w == 0)
+    ((uint8_t*)HB)[lane / LPB] = (uint8_t)(lc.exists ? ((lc.kind << 5) | lc.F) : 0u);
+  wave_lds_sync();  // every row of X is read before the payload goes there
+  if (held) {
+    wave_pack<T, L, FUSED, FULL>(J, seg, w, vcnt, lc, fs, Q + at + boff);
+    if (first) open(tk);
+    wave_lds_sync();  // payload and header bytes are complete
+    if (good) {
+      const UnitHeld h = {HB[lane & (U::HBW - 1)], at, size, k, job, u};
+      if (q.n) q.h1 = h;  // (not an indexed array: that would live in memory)
+      else q.h0 = h;
+      ++q.n;
+    }
+    return;
+  }
+  // too large to hold: written at once.  An fp64 payload may exceed X: then
+  // it is packed in two halves of 32 lanes (no block crosses them).
+  const uint32_t lo = sizeof(T) == 8 ? read_lane(boff, 32) : 0u;
+  const bool two = sizeof(T) == 8 && size > U::PACKW;
+  if (!two) wave_pack<T, L, FUSED, FULL>(J, seg, w, vcnt, lc, fs, X + boff);
+  wave_lds_sync();
+  uint64_t off, pj;
+  const bool known = unit_offset(C, us, k, wid, off, pj);
+  if (first) {  // a ticket taken before the wait would be held as long as it
+    if (lane == 0) tk = atomicAdd(&C.ctrl->ticket, 1u);
+    open(tk);
+  }
+  if (!known || !good) return;
+  uint32_t* dst = unit_meta<L>(J, u, off, pj, size, HB[lane & (U::HBW - 1)]);
+  if (!two) {
+    for (uint32_t i = lane; i < size; i += 64) dst[i] = X[i];
+  } else {
+#pragma unroll 1
+    for (uint32_t p = 0; p < 2; ++p) {
+      const uint32_t o = p ? lo : 0u, m = p ? size - lo : lo;
+      if ((lane >> 5) == p) wave_pack<T, L, FUSED, FULL>(J, seg, w, vcnt, lc, fs, X + boff - o);
+      wave_lds_sync();
+      for (uint32_t i = lane; i < m; i += 64) dst[o + i] = X[i];
+      wave_lds_sync();
+    }
+  }
+  wave_lds_sync();  // the region is read before the next unit reuses it
+}
+
+template <typename T, int L, bool FUSED, class Flush>
+__device__ __forceinline__ void unit_one(const Job& J, uint32_t job, uint64_t r, uint32_t k,
+                                         uint32_t wid, uint32_t W, uint32_t total, USched& us,
+                                         const Ctl& C, uint32_t* X, UnitQueue& q,
+                                         const Flush& flush) {
+  const uint64_t u = r * W + wid;
+  // an empty stream is one unit of no values
+  const bool live = u == 0 || u * UNIT_ELEMS < J.n;
+  if ((u + 1) * UNIT_ELEMS <= J.n)
+    unit_code<T, L, FUSED, true>(J, job, J.strip0 + r, u, live, k, wid, W, total, us, C, X, q, flush);
+  else
+    unit_code<T, L, FUSED, false>(J, job, J.strip0 + r, u, live, k, wid, W, total, us, C, X, q, flush);
+}
+
+// Registers for four waves per SIMD (the fused step: three), as the LDS allows.
+#define GZ_UNIT_ATTR(FUSED)                                        \
+  __launch_bounds__((UnitEnc<FUSED>::MAXW + 1) * 64)               \
+      __attribute__((amdgpu_waves_per_eu((FUSED) ? 3 : 4, (FUSED) ? 3 : 4)))
+
+// One stream: round ticket t is round t of the job.
+template <typename T, int L, bool FUSED>
+__global__ GZ_UNIT_ATTR(FUSED) void k_unit(Job J, Ctl C) {
+  __shared__ USched us;
+  const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t W = (blockDim.x >> 6) - 1, total = J.nstrips;
+  unit_begin(C, us, total);
+  if (wid == W) {
+    __builtin_amdgcn_s_setprio(3);
+    for (uint32_t k = 0;; ++k) {
+      if (!lds_wait_ge(C, &us.rs[k % RING].ready, k + 1)) break;
+      const uint32_t t = __builtin_amdgcn_readfirstlane(us.rs[k % RING].ticket);
+      if (t >= total) break;
+      if (!unit_sched(C, us, k, W, UChain{t, 0, t, 0, false})) break;
+    }
+  } else {
+    uint32_t* X = g_stage + wid * UnitEnc<FUSED>::REGION;
+    UnitQueue q;
+    q.n = 0;
+    auto flush = [&](UnitQueue& x) { unit_flush(J, C, us, wid, X + UnitEnc<FUSED>::XW, x); };
+    for (uint32_t k = 0;; ++k) {
+      if (!lds_wait_ge(C, &us.rs[k % RING].ready, k + 1)) break;
+      const uint32_t t = __builtin_amdgcn_readfirstlane(us.rs[k % RING].ticket);
+      if (t >= total) break;
+      unit_one<T, L, FUSED>(J, 0, t, k, wid, W, total, us, C, X, q, flush);
+    }
+    while (q.n) flush(q);
+  }
+  unit_end(C, us, total);
+}
+
+// A batch: ticket t is round map[2t + 1] of job map[2t], or, for jobs of the
+// same number of rounds (njobs > 0), round t / njobs of job t % njobs.
+template <uint32_t OP, bool WIDE>
+__global__ GZ_UNIT_ATTR(OP == 2) void k_batch_unit(const Job* __restrict__ jobs,
+                                                   const uint32_t* __restrict__ map,
+                                                   uint32_t njobs, uint32_t total, Ctl C) {
+  constexpr bool FUSED = OP == 2;
+  __shared__ USched us;
+  const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t W = (blockDim.x >> 6) - 1;
+  unit_begin(C, us, total);
+  if (wid == W) {
+    __builtin_amdgcn_s_setprio(3);
+    for (uint32_t k = 0;; ++k) {
+      if (!lds_wait_ge(C, &us.rs[k % RING].ready, k + 1)) break;
+      const uint32_t t = __builtin_amdgcn_readfirstlane(us.rs[k % RING].ticket);
+      if (t >= total) break;
+      const uint32_t j = njobs ? t % njobs : map[2 * (uint64_t)t];
+      const uint64_t r = njobs ? t / njobs : map[2 * (uint64_t)t + 1];
+      const Job& J = jobs[j];
+      if (!unit_sched(C, us, k, W,
+                      UChain{J.strip0 + r, J.chain0, r, j, J.chain0 != J.strip0}))
+        break;
+    }
+  } else {
+    uint32_t* X = g_stage + wid * UnitEnc<FUSED>::REGION;
+    UnitQueue q;
+    q.n = 0;
+    auto flush = [&](UnitQueue& x) {
+      unit_flush(jobs[x.h0.job], C, us, wid, X + UnitEnc<FUSED>::XW, x);
+    };
+    for (uint32_t k = 0;; ++k) {
+      if (!lds_wait_ge(C, &us.rs[k % RING].ready, k + 1)) break;
+      const uint32_t t = __builtin_amdgcn_readfirstlane(us.rs[k % RING].ticket);
+      if (t >= total) break;
+      const uint32_t j = njobs ? t % njobs : map[2 * (uint64_t)t];
+      const uint64_t r = njobs ? t / njobs : map[2 * (uint64_t)t + 1];
+      const Job J = jobs[j];
+      switch ((J.dtype << 3) | J.log2L) {
+        case 5: unit_one<float, 32, FUSED>(J, j, r, k, wid, W, total, us, C, X, q, flush); break;
+        case 6: unit_one<float, 64, FUSED>(J, j, r, k, wid, W, total, us, C, X, q, flush); break;
+        case 7: unit_one<float, 128, FUSED>(J, j, r, k, wid, W, total, us, C, X, q, flush); break;
+        case 13: if constexpr (WIDE) unit_one<double, 32, FUSED>(J, j, r, k, wid, W, total, us, C, X, q, flush); break;
+        case 14: if constexpr (WIDE) unit_one<double, 64, FUSED>(J, j, r, k, wid, W, total, us, C, X, q, flush); break;
+        case 15: if constexpr (WIDE) unit_one<double, 128, FUSED>(J, j, r, k, wid, W, total, us, C, X, q, flush); break;
+        default: break;
+      }
+    }
+    while (q.n) flush(q);
+  }
+  unit_end(C, us, total);
 }
 
 template <int L, bool FULL>
@@ -3199,9 +3760,11 @@ __global__ void k_quantize(const T* __restrict__ x, uint64_t n, Job J, int32_t* 
                            uint8_t* __restrict__ fail) {
   for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n;
        i += (uint64_t)gridDim.x * blockDim.x) {
-    bool bad = false;
-    int32_t qi = quant_t<T>(x[i], J, bad);
-    q[i] = bad ? 0 : qi;
+    QBad<T> qb;
+    uint32_t qi;
+    quant_run<1, true>(x + i, J, 1, &qi, qb);
+    const bool bad = qb.any(bad_bound<T>(J));
+    q[i] = bad ? 0 : (int32_t)qi;
     fail[i] = bad ? 1 : 0;
   }
 }
@@ -3271,37 +3834,90 @@ hipError_t launch_decompress_wave(const Job& J, const Ctl& C, uint32_t cus, hipS
   return hipErrorInvalidValue;
 }
 
-size_t wave_encode_lds() {
+size_t wave_fused_lds() {
   return (size_t)WaveEnc::WAVES * WaveEnc::REGION * 4 + sizeof(WaveSched);
 }
 
-template <int L, bool FUSED>
-static hipError_t launch_ew(const Job* d_jobs, const Job& J, uint32_t njobs, uint32_t total,
-                            const Ctl& C, uint32_t cus, hipStream_t st) {
+template <int L>
+static hipError_t launch_fw(const Job* d_jobs, uint32_t njobs, uint32_t total, const Ctl& C,
+                            uint32_t cus, hipStream_t st) {
   // one workgroup per round in flight, at most one per CU (the LDS allows one)
   const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(cus, total));
-  const size_t lds = (size_t)WaveEnc::WAVES * WaveEnc::REGION * 4;
-  if (d_jobs)
-    hipLaunchKernelGGL((k_batch_encode_w<L, FUSED>), dim3(grid), dim3(WaveEnc::WAVES * 64), lds,
-                       st, d_jobs, njobs, total, C);
-  else
-    hipLaunchKernelGGL((k_encode_w<L, FUSED>), dim3(grid), dim3(WaveEnc::WAVES * 64), lds, st,
-                       J, C);
+  hipLaunchKernelGGL((k_batch_fused_w<L>), dim3(grid), dim3(WaveEnc::WAVES * 64),
+                     (size_t)WaveEnc::WAVES * WaveEnc::REGION * 4, st, d_jobs, njobs, total, C);
   return hipGetLastError();
 }
 
-hipError_t launch_encode_wave(uint32_t op, const Job* d_jobs, const Job& J, uint32_t njobs,
-                              uint32_t total, uint32_t log2L, const Ctl& C, uint32_t cus,
-                              hipStream_t st) {
-  const bool fused = op == 2;
+hipError_t launch_fused_wave(const Job* d_jobs, uint32_t njobs, uint32_t total, uint32_t log2L,
+                             const Ctl& C, uint32_t cus, hipStream_t st) {
   switch (log2L) {
-    case 5: return fused ? launch_ew<32, true>(d_jobs, J, njobs, total, C, cus, st)
-                         : launch_ew<32, false>(d_jobs, J, njobs, total, C, cus, st);
-    case 6: return fused ? launch_ew<64, true>(d_jobs, J, njobs, total, C, cus, st)
-                         : launch_ew<64, false>(d_jobs, J, njobs, total, C, cus, st);
-    case 7: return fused ? launch_ew<128, true>(d_jobs, J, njobs, total, C, cus, st)
-                         : launch_ew<128, false>(d_jobs, J, njobs, total, C, cus, st);
+    case 5: return launch_fw<32>(d_jobs, njobs, total, C, cus, st);
+    case 6: return launch_fw<64>(d_jobs, njobs, total, C, cus, st);
+    case 7: return launch_fw<128>(d_jobs, njobs, total, C, cus, st);
   }
+  return hipErrorInvalidValue;
+}
+
+size_t unit_lds(bool fused, uint32_t workers) {
+  return (size_t)workers * (fused ? UnitEnc<true>::REGION : UnitEnc<false>::REGION) * 4 +
+         sizeof(USched);
+}
+
+template <typename T, int L, bool FUSED>
+static hipError_t launch_u(const Job& J, const Ctl& C, uint32_t workers, uint32_t grid,
+                           hipStream_t st) {
+  hipLaunchKernelGGL((k_unit<T, L, FUSED>), dim3(grid), dim3((workers + 1) * 64),
+                     (size_t)workers * UnitEnc<FUSED>::REGION * 4, st, J, C);
+  return hipGetLastError();
+}
+
+template <uint32_t OP, bool WIDE>
+static hipError_t launch_bu(const Job* d_jobs, const uint32_t* d_map, uint32_t njobs,
+                            uint32_t total, const Ctl& C, uint32_t workers, uint32_t grid,
+                            hipStream_t st) {
+  hipLaunchKernelGGL((k_batch_unit<OP, WIDE>), dim3(grid), dim3((workers + 1) * 64),
+                     (size_t)workers * UnitEnc<OP == 2>::REGION * 4, st, d_jobs, d_map, njobs,
+                     total, C);
+  return hipGetLastError();
+}
+
+// Workgroups in flight: as many as the CUs hold (16 waves, the fused step's
+// 12), at most one per round.
+static uint32_t unit_grid(bool fused, uint32_t cus, uint32_t workers, uint32_t total) {
+  const uint32_t per_cu = ((fused ? UNIT_WORKERS_FUSED : UNIT_WORKERS) + 1) / (workers + 1);
+  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)cus * per_cu, total));
+}
+
+hipError_t launch_unit(uint32_t op, const Job& J, const Ctl& C, uint32_t workers, uint32_t cus,
+                       hipStream_t st) {
+  const bool fused = op == 2;
+  const uint32_t grid = unit_grid(fused, cus, workers, J.nstrips);
+  switch ((J.dtype << 3) | J.log2L) {
+    case 5: return fused ? launch_u<float, 32, true>(J, C, workers, grid, st)
+                         : launch_u<float, 32, false>(J, C, workers, grid, st);
+    case 6: return fused ? launch_u<float, 64, true>(J, C, workers, grid, st)
+                         : launch_u<float, 64, false>(J, C, workers, grid, st);
+    case 7: return fused ? launch_u<float, 128, true>(J, C, workers, grid, st)
+                         : launch_u<float, 128, false>(J, C, workers, grid, st);
+    case 13: return fused ? hipErrorInvalidValue
+                          : launch_u<double, 32, false>(J, C, workers, grid, st);
+    case 14: return fused ? hipErrorInvalidValue
+                          : launch_u<double, 64, false>(J, C, workers, grid, st);
+    case 15: return fused ? hipErrorInvalidValue
+                          : launch_u<double, 128, false>(J, C, workers, grid, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_batch_unit(uint32_t op, const Job* d_jobs, const uint32_t* d_map,
+                             uint32_t njobs, uint32_t total, bool wide, const Ctl& C,
+                             uint32_t workers, uint32_t cus, hipStream_t st) {
+  const uint32_t grid = unit_grid(op == 2, cus, workers, total);
+  if (op == 0)
+    return wide ? launch_bu<0, true>(d_jobs, d_map, njobs, total, C, workers, grid, st)
+                : launch_bu<0, false>(d_jobs, d_map, njobs, total, C, workers, grid, st);
+  if (op == 2 && !wide)
+    return launch_bu<2, false>(d_jobs, d_map, njobs, total, C, workers, grid, st);
   return hipErrorInvalidValue;
 }
 
