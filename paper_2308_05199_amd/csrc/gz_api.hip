@@ -264,8 +264,8 @@ bool unit_fits(const gz_ctx* c, uint32_t op) {
 }
 
 bool wave_fits(const gz_ctx* c, uint32_t op, uint32_t dt) {
-  if (op == 1) return gzk::wave_decode_lds(dt) <= c->lds_max;
-  if (op == 3) return dt == GZ_F32 && gzk::wave_decode_lds(GZ_F32) <= c->lds_max;
+  if (op == 1) return std::max(gzk::wave_decode_lds(), gzk::unit_decode_lds()) <= c->lds_max;
+  if (op == 3) return dt == GZ_F32 && gzk::wave_decode_lds() <= c->lds_max;
   return (op == 0 || op == 2) && dt == GZ_F32 && unit_fits(c, op);
 }
 
@@ -296,6 +296,12 @@ uint32_t unit_workers(uint32_t op, uint64_t units) {
     if (cdiv(units, W) <= 192) return W;
   return most;
 }
+
+// Whether one stream is decoded by units rather than superblocks: fp64, and
+// fp32 of 2^19 to 2^24 elements (10.1 against 9.3 us at 2^20, 19.5 against 18.4
+// at 2^24; below, one launch's latency either way; above, the superblocks'
+// pipeline is the faster, 68 against 75 us at 2^26).
+bool unit_decodes(const Job& J) { return J.dtype == GZ_F64 || (J.NS >= 128 && J.NS <= 4096); }
 
 // Lays out single job J (n, dtype, L set by set_geom) for unit encoding:
 // workers per workgroup, J.nstrips rounds.  False if the workspace has too
@@ -443,6 +449,17 @@ std::vector<uint32_t> wave_job_shares(const gz_ctx* c, gz_op op, const std::vect
       m.push_back((uint32_t)cnt[j]);
     }
   return m;
+}
+
+// A per-wave decoding (op 1: by shares or, without any, by units) or decode-
+// and-accumulate batch (op 3).
+hipError_t launch_decode(uint32_t op, const Job* d_jobs, const uint32_t* d_map, uint32_t njobs,
+                         uint32_t total, uint32_t jw, const gz_ctx* c, hipStream_t st) {
+  const uint32_t cus = (uint32_t)c->cus;
+  if (op == GZ_OP_ACCUMULATE)
+    return gzk::launch_accum_wave_batch(d_jobs, d_map, njobs, total, cus, c->ctl(), st);
+  if (jw) return gzk::launch_decode_shares(d_jobs, d_map, jw, cus, c->ctl(), st);
+  return gzk::launch_batch_unit_decode(d_jobs, d_map, njobs, total, cus, c->ctl(), st);
 }
 
 // Builds the jobs of a request batch; fills the strip map.
@@ -820,6 +837,9 @@ gz_status gz_decompress(gz_ctx* c, const void* d_in, uint64_t in_bytes, uint64_t
     J.in = job_ptr(d_in);
     J.in_bytes = in_bytes;
     J.out = job_ptr(d_out);
+    if (unit_decodes(J))
+      return hip_status(
+          gzk::launch_unit_decode(J, c->ctl(), (uint32_t)c->cus, (hipStream_t)stream));
     return hip_status(gzk::launch_decompress_wave(J, c->ctl(), (uint32_t)c->cus,
                                                   (hipStream_t)stream));
   }
@@ -835,6 +855,9 @@ gz_status gz_decompress(gz_ctx* c, const void* d_in, uint64_t in_bytes, uint64_t
     if (n % (8ull * p->nx) != 0) return GZ_EINVAL;
     J.mode = 1;
     J.nx = p->nx;
+    if (n && !p->threads && !p->grid && gzk::unit_decode_lds() <= c->lds_max)
+      return hip_status(
+          gzk::launch_unit_decode(J, c->ctl(), (uint32_t)c->cus, (hipStream_t)stream));
     const uint32_t grid = pick_tile_grid(c, gzk::OCC_TILE_D, tpb, J.nstrips, p);
     return hip_status(gzk::launch_tiles(1, J, c->ctl(), tpb, grid, (hipStream_t)stream));
   }
@@ -981,10 +1004,10 @@ gz_status gz_scatter_decompress(gz_ctx* c, const void* d_packed, uint64_t packed
       (dtype != GZ_F32 && dtype != GZ_F64) || !params_ok(p, L) || tile_mode(p) || nchunks == 0)
     return GZ_EINVAL;
   if (nchunks > c->max_jobs) return GZ_ENOSPC;
-  // waves when asked for, or by default for fp32 chunks where each chunk can
-  // have waves of its own (else strips)
+  // waves when asked for, or by default: fp32 chunks where each can have waves
+  // of its own, fp64 chunks by units (else strips)
   const bool asked = p && p->threads == WAVE_TPB;
-  const bool dflt = (!p || (p->threads == 0 && p->grid == 0)) && dtype == GZ_F32;
+  const bool dflt = !p || (p->threads == 0 && p->grid == 0);
   const bool want_wave = (asked || dflt) && wave_fits(c, 1, dtype);
   gz_params q;  // the strips' shape when waves were asked for (geometry, fallback)
   const gz_params* ps = p;
@@ -1022,13 +1045,12 @@ gz_status gz_scatter_decompress(gz_ctx* c, const void* d_packed, uint64_t packed
     if (batch_decode_wave_ok(c, GZ_OP_DECOMPRESS, jobs, dtype == GZ_F64, total)) {
       const std::vector<uint32_t> jm =
           wave_job_shares(c, GZ_OP_DECOMPRESS, jobs, dtype == GZ_F64, total);
-      if (asked || !jm.empty()) {
+      if (asked || !jm.empty() || dtype == GZ_F64) {
         gz_status r = stage_upload(c, jobs, jm.empty() ? smap : jm, st);
         if (r != GZ_OK) return r;
-        return hip_status(gzk::launch_decode_wave_batch(
-            1, c->d_jobs, (smap.empty() && jm.empty()) ? nullptr : c->d_map, nchunks,
-            (uint32_t)total, dtype == GZ_F64, (uint32_t)(jm.size() / 3), (uint32_t)c->cus,
-            c->ctl(), st));
+        return hip_status(launch_decode(
+            GZ_OP_DECOMPRESS, c->d_jobs, (smap.empty() && jm.empty()) ? nullptr : c->d_map,
+            nchunks, (uint32_t)total, (uint32_t)(jm.size() / 3), c, st));
       }
     }
     if (asked) return GZ_EUNSUPPORTED;
@@ -1069,10 +1091,10 @@ gz_status batch_impl(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t nre
       const std::vector<uint32_t> jm = wave_job_shares(c, op, jobs, wide, total);
       r = stage_upload(c, jobs, jm.empty() ? smap : jm, st);
       if (r != GZ_OK) return r;
-      return hip_status(gzk::launch_decode_wave_batch(
-          (uint32_t)op, c->d_jobs, (smap.empty() && jm.empty()) ? nullptr : c->d_map,
-          (uint32_t)jobs.size(), (uint32_t)total, wide, (uint32_t)(jm.size() / 3),
-          (uint32_t)c->cus, c->ctl(), st));
+      return hip_status(launch_decode((uint32_t)op, c->d_jobs,
+                                      (smap.empty() && jm.empty()) ? nullptr : c->d_map,
+                                      (uint32_t)jobs.size(), (uint32_t)total,
+                                      (uint32_t)(jm.size() / 3), c, st));
     }
     if (p && p->threads == WAVE_TPB) return GZ_EUNSUPPORTED;
   }
@@ -1204,9 +1226,8 @@ gz_status gz_plan_launch(gz_plan* pl, gz_stream_t stream) {
                                              pl->wide, pl->ctx->ctl(), pl->unit_w,
                                              (uint32_t)pl->ctx->cus, (hipStream_t)stream));
   if (pl->wave_dec)
-    return hip_status(gzk::launch_decode_wave_batch(
-        pl->op, pl->d_jobs, pl->has_map ? pl->d_map : nullptr, pl->njobs, pl->total, pl->wide,
-        pl->jw, (uint32_t)pl->ctx->cus, pl->ctx->ctl(), (hipStream_t)stream));
+    return hip_status(launch_decode(pl->op, pl->d_jobs, pl->has_map ? pl->d_map : nullptr,
+                                    pl->njobs, pl->total, pl->jw, pl->ctx, (hipStream_t)stream));
   return hip_status(gzk::launch_batch(pl->op, pl->d_jobs, pl->d_map, pl->njobs, pl->total,
                                       pl->ctx->ctl(),
                                       pl->tpb, pl->grid, pl->wide, (hipStream_t)stream));

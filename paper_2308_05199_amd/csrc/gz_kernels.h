@@ -18,22 +18,23 @@ size_t lds_bytes(uint32_t wide, uint32_t tpb);
 hipError_t launch_batch(uint32_t op, const Job* d_jobs, const uint32_t* d_strip_job,
                         uint32_t njobs, uint32_t total, const Ctl& C, uint32_t tpb,
                         uint32_t grid, bool wide, hipStream_t st);
-// Per-wave decoding of one stream (mode 0): every wave decodes whole
+// Per-wave decoding of one fp32 stream (mode 0): every wave decodes whole
 // superblocks, assigned statically; grid = min(CUs, superblocks per wave).
 hipError_t launch_decompress_wave(const Job& J, const Ctl& C, uint32_t cus, hipStream_t st);
-size_t wave_decode_lds(uint32_t dtype);  // its workgroup's LDS bytes
+size_t wave_decode_lds();  // its workgroup's LDS bytes
+size_t unit_decode_lds();
 // Per-wave decode-and-accumulate of one fp32 stream (as launch_decompress_wave).
 hipError_t launch_accum_wave(const Job& J, const Ctl& C, uint32_t cus, hipStream_t st);
-// Per-wave batched decoding (op 1) or decode-and-accumulate (op 3, fp32):
-// total superblocks, superblock i = (d_map[2i], d_map[2i+1]) as (job,
-// superblock), or without a map (jobs of equal superblock counts) superblock
-// i / njobs of job i % njobs.  wide: the batch holds fp64 jobs.  jw (op 1,
-// fp32 1D jobs): d_map holds jw (job, first superblock, stride) triples,
-// one per wave's share of a job (each job's whole superblocks decoded as a
-// pipeline); 0 otherwise.
-hipError_t launch_decode_wave_batch(uint32_t op, const Job* d_jobs, const uint32_t* d_map,
-                                    uint32_t njobs, uint32_t total, bool wide, uint32_t jw,
-                                    uint32_t cus, const Ctl& C, hipStream_t st);
+// Batched decoding of fp32 1D jobs by shares: d_map holds jw (job, first
+// superblock, stride) triples, one per wave's share of a job (its whole
+// superblocks decoded as a pipeline).
+hipError_t launch_decode_shares(const Job* d_jobs, const uint32_t* d_map, uint32_t jw,
+                                uint32_t cus, const Ctl& C, hipStream_t st);
+// Per-wave batched decode-and-accumulate (fp32): total superblocks, superblock
+// i = (d_map[2i], d_map[2i+1]) as (job, superblock), or without a map (jobs of
+// equal superblock counts) superblock i / njobs of job i % njobs.
+hipError_t launch_accum_wave_batch(const Job* d_jobs, const uint32_t* d_map, uint32_t njobs,
+                                   uint32_t total, uint32_t cus, const Ctl& C, hipStream_t st);
 // Per-wave fused step of njobs fp32 jobs of the same superblock count and
 // block length: every wave codes whole superblocks, a workgroup's waves the 8
 // of a round (one look-back word); total = njobs * wave_rounds(NS), round
@@ -62,6 +63,13 @@ inline uint64_t unit_rounds(uint64_t n, uint32_t workers) {  // an empty stream 
   const uint64_t units = n ? (n + UNIT_ELEMS - 1) / UNIT_ELEMS : 1;
   return (units + workers - 1) / workers;
 }
+// Unit decoding of one stream (mode 0, either type, or 8x8 tiles), a wave per
+// 2048 elements.
+hipError_t launch_unit_decode(const Job& J, const Ctl& C, uint32_t cus, hipStream_t st);
+// Unit decoding of a batch (mode 0, either type) of total superblocks, d_map
+// and njobs as launch_accum_wave_batch.
+hipError_t launch_batch_unit_decode(const Job* d_jobs, const uint32_t* d_map, uint32_t njobs,
+                                    uint32_t total, uint32_t cus, const Ctl& C, hipStream_t st);
 constexpr uint64_t DEC_WAVES_F32 = 8;  // waves per workgroup of the fp32 per-wave decoders
 hipError_t launch_quantize(const void* x, uint64_t n, const Job& J, int32_t* q, uint8_t* fail,
                            hipStream_t st);

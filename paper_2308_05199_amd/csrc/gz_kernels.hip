@@ -1721,7 +1721,8 @@ __device__ __forceinline__ void decompress_tp_one(const Job& J, uint64_t s, cons
 // superblocks, so this static assignment needs no co-residency.  A wave's
 // LDS region holds the superblock's payload, then its decoded values in the
 // padded segment layout for coalesced stores.  Lane l decodes segments l and
-// 64 + l of the superblock.
+// 64 + l of the superblock.  For fp32 streams of more than 2^24 elements,
+// shorter than 2^19, and batches of them (the unit decoder takes the rest).
 template <typename T>
 struct WaveDec {
   static constexpr uint32_t WAVES = sizeof(T) == 4 ? 8 : 4;               // per workgroup
@@ -1826,7 +1827,7 @@ __device__ __forceinline__ void wave_blocks_load(const Job& J, const uint8_t* in
 // False if the table entries, header bytes or block sizes are inconsistent
 // (the same checks as the strip decoder's); raw from wave_blocks_load, of a
 // stream whose header passed.
-template <typename T, int L>
+template <typename T, int L, int MODE = 0>
 __device__ bool wave_blocks_eval(const Job& J, uint64_t sb, uint64_t paydw, uint32_t nval,
                                  const uint32_t (&raw)[3], WaveBlocks& wb) {
   constexpr uint32_t EW = sizeof(T) / 4, LPB = L / 32, BPS = SUPER / L;
@@ -1859,7 +1860,8 @@ __device__ bool wave_blocks_eval(const Job& J, uint64_t sb, uint64_t paydw, uint
     bool hv = true;
     if (kd == K_ZERO) hv = f == 0;
     else if (kd == K_RAW) { hv = f == 0; size_dw = m * EW; }
-    else if (kd == K_L1D) size_dw = 1u + (f ? (f + 1u) * LPB : 0u);
+    else if (kd == K_L1D || (MODE == 1 && kd == K_L2D)) size_dw = 1u + (f ? (f + 1u) * LPB : 0u);
+    else if (MODE == 1 && kd == K_NONE) { hv = f > 0; size_dw = (f + 1u) * LPB; }
     else hv = false;
     if (!hv) size_dw = 0;
     good = good && hv;
@@ -2184,24 +2186,24 @@ __device__ __forceinline__ void wave_decode_whole(const Job& J, const uint8_t* i
   }
 }
 
-template <typename T, int L>
-__global__ __launch_bounds__(WaveDec<T>::WAVES * 64)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 2 : 1, 2))) void k_decompress_w(Job J, Ctl C) {
+template <int L>
+__global__ __launch_bounds__(WaveDec<float>::WAVES * 64)
+__attribute__((amdgpu_waves_per_eu(2, 2))) void k_decompress_w(Job J, Ctl C) {
   const uint32_t wid = threadIdx.x >> 6;
-  uint32_t* R = g_stage + wid * WaveDec<T>::REGION;
+  uint32_t* R = g_stage + wid * WaveDec<float>::REGION;
   const uint8_t* in = (const uint8_t*)J.in;
   uint64_t paydw = 0;
-  T t = 0;
-  bool bad = !wave_header<T>(J, in, paydw, t);
+  float t = 0;
+  bool bad = !wave_header<float>(J, in, paydw, t);
   if (!bad) {
     const uint64_t W = (uint64_t)gridDim.x * (blockDim.x >> 6);
     uint64_t sb = (uint64_t)blockIdx.x * (blockDim.x >> 6) + wid;
-    if constexpr (sizeof(T) == 4) wave_decode_whole<L>(J, in, paydw, t, R, W, sb, bad);
-    if (!bad) {  // the rest (fp64: all), one superblock at a time
+    wave_decode_whole<L>(J, in, paydw, t, R, W, sb, bad);
+    if (!bad) {  // the partial last superblock
       uint32_t raw[3] = {0u, 0u, 0u};
       if (sb < J.NS) wave_blocks_load<L, false>(J, in, sb, raw);
       for (; sb < J.NS; sb += W)
-        if (!wave_decode_super<T, L>(J, in, sb, paydw, t, R, raw, sb + W)) bad = true;
+        if (!wave_decode_super<float, L>(J, in, sb, paydw, t, R, raw, sb + W)) bad = true;
     }
   }
   if (bad && __lane_id() == 0) atomicOr(&C.ctrl->err, ERRF_CORRUPT);
@@ -2265,59 +2267,57 @@ __device__ __forceinline__ void wave_job_decode(const Job& J, const uint8_t* in,
     if (!wave_decode_super<float, L>(J, in, sb, paydw, t, R, raw, sb + stride)) bad = true;
 }
 
-// Batched decoding (OP 1) or decode-and-accumulate (OP 3) by waves: batch
-// superblock i is superblock map[2i + 1] of job map[2i], or, without a map
-// (jobs of equal superblock counts), superblock i / njobs of job i % njobs;
-// waves take them statically.  WIDE: the batch holds fp64 jobs (fp64-sized
-// regions, four waves per workgroup).  jw (decoding an fp32 1D batch): the
-// map holds jw (job, first superblock, stride) triples instead, one per
-// wave's share (waves take them statically): each decodes superblocks
-// first, first + stride, ... of its job with the pipelined single-stream
-// decoder.
-template <bool WIDE, uint32_t OP>
-__global__ __launch_bounds__((WIDE ? WaveDec<double>::WAVES : WaveDec<float>::WAVES) * 64)
-__attribute__((amdgpu_waves_per_eu(WIDE ? 1 : 2, 2))) void k_batch_decode_w(
-    const Job* __restrict__ jobs, const uint32_t* __restrict__ map, uint32_t njobs,
-    uint32_t total, uint32_t jw, Ctl C) {
-  constexpr uint32_t WAVES = WIDE ? WaveDec<double>::WAVES : WaveDec<float>::WAVES;
-  constexpr uint32_t REGION = WIDE ? WaveDec<double>::REGION : WaveDec<float>::REGION;
+// Batched decoding of fp32 1D jobs by shares: the map holds jw (job, first
+// superblock, stride) triples, one per wave's share (waves take them
+// statically); each wave decodes superblocks first, first + stride, ... of its
+// job with the pipelined single-stream decoder.
+__global__ __launch_bounds__(WaveDec<float>::WAVES * 64)
+__attribute__((amdgpu_waves_per_eu(2, 2))) void k_batch_decode_w(
+    const Job* __restrict__ jobs, const uint32_t* __restrict__ map, uint32_t jw, Ctl C) {
+  constexpr uint32_t WAVES = WaveDec<float>::WAVES;
   const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  uint32_t* R = g_stage + wid * REGION;
+  uint32_t* R = g_stage + wid * WaveDec<float>::REGION;
+  bool bad = false;
+  for (uint32_t w = blockIdx.x * WAVES + wid; w < jw; w += gridDim.x * WAVES) {
+    Job J = jobs[map[3 * (uint64_t)w]];
+    const uint64_t first = map[3 * (uint64_t)w + 1], stride = map[3 * (uint64_t)w + 2];
+    const uint64_t off = J.in_off ? J.in_off[J.job] : 0ull;
+    J.in_bytes = off <= J.in_bytes ? J.in_bytes - off : 0ull;
+    const uint8_t* in = (const uint8_t*)J.in + off;
+    bool jb = false;  // this share's job only
+    switch (J.log2L) {
+      case 5: wave_job_decode<32>(J, in, first, stride, R, jb); break;
+      case 6: wave_job_decode<64>(J, in, first, stride, R, jb); break;
+      case 7: wave_job_decode<128>(J, in, first, stride, R, jb); break;
+      default: jb = true; break;
+    }
+    bad = bad || jb;
+  }
+  if (bad && __lane_id() == 0) atomicOr(&C.ctrl->err, ERRF_CORRUPT);
+}
+
+// Batched decode-and-accumulate (fp32) by waves: batch superblock i is
+// superblock map[2i + 1] of job map[2i], or, without a map (jobs of equal
+// superblock counts), superblock i / njobs of job i % njobs; waves take them
+// statically.
+__global__ __launch_bounds__(WaveDec<float>::WAVES * 64)
+__attribute__((amdgpu_waves_per_eu(2, 2))) void k_batch_accum_w(
+    const Job* __restrict__ jobs, const uint32_t* __restrict__ map, uint32_t njobs,
+    uint32_t total, Ctl C) {
+  constexpr uint32_t WAVES = WaveDec<float>::WAVES;
+  const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t* R = g_stage + wid * WaveDec<float>::REGION;
   bool bad = false;
   const uint32_t W = gridDim.x * WAVES;
-  if constexpr (!WIDE && OP == 1) {
-    if (jw) {
-      for (uint32_t w = blockIdx.x * WAVES + wid; w < jw; w += W) {
-        Job J = jobs[map[3 * (uint64_t)w]];
-        const uint64_t first = map[3 * (uint64_t)w + 1], stride = map[3 * (uint64_t)w + 2];
-        const uint64_t off = J.in_off ? J.in_off[J.job] : 0ull;
-        J.in_bytes = off <= J.in_bytes ? J.in_bytes - off : 0ull;
-        const uint8_t* in = (const uint8_t*)J.in + off;
-        bool jb = false;  // this share's job only
-        switch (J.log2L) {
-          case 5: wave_job_decode<32>(J, in, first, stride, R, jb); break;
-          case 6: wave_job_decode<64>(J, in, first, stride, R, jb); break;
-          case 7: wave_job_decode<128>(J, in, first, stride, R, jb); break;
-          default: jb = true; break;
-        }
-        bad = bad || jb;
-      }
-      if (bad && __lane_id() == 0) atomicOr(&C.ctrl->err, ERRF_CORRUPT);
-      return;
-    }
-  }
   for (uint32_t i = blockIdx.x * WAVES + wid; i < total; i += W) {
     const uint32_t j = map ? map[2 * (uint64_t)i] : i % njobs;
     const uint64_t sb = map ? map[2 * (uint64_t)i + 1] : i / njobs;
     const Job J = jobs[j];
     bool ok = false;
     switch ((J.dtype << 3) | J.log2L) {
-      case 5: ok = wave_batch_super<float, 32, OP>(J, sb, R); break;
-      case 6: ok = wave_batch_super<float, 64, OP>(J, sb, R); break;
-      case 7: ok = wave_batch_super<float, 128, OP>(J, sb, R); break;
-      case 13: if constexpr (WIDE && OP == 1) ok = wave_batch_super<double, 32, 1>(J, sb, R); break;
-      case 14: if constexpr (WIDE && OP == 1) ok = wave_batch_super<double, 64, 1>(J, sb, R); break;
-      case 15: if constexpr (WIDE && OP == 1) ok = wave_batch_super<double, 128, 1>(J, sb, R); break;
+      case 5: ok = wave_batch_super<float, 32, 3>(J, sb, R); break;
+      case 6: ok = wave_batch_super<float, 64, 3>(J, sb, R); break;
+      case 7: ok = wave_batch_super<float, 128, 3>(J, sb, R); break;
       default: break;
     }
     if (!ok) bad = true;
@@ -2947,20 +2947,20 @@ __device__ __forceinline__ void unit_halves_put(const u4u (&r)[8], uint32_t h, u
   }
 }
 
-// The lane's block of unit 2 sb + h of an incoming fp32 stream (fused step):
-// kind, width and offset inside the unit's payload, P dwords at off0 from
-// the payload's start.  False if superblock sb is malformed.
+// The lane's block of unit 2 sb + h of an incoming stream: kind, width and
+// offset inside the unit's payload, P dwords at off0 from the payload's start.
+// False if superblock sb is malformed.
 struct UnitIn {
   uint32_t off0, P, kind, F, boff;
   bool ex;
 };
 
-template <int L>
+template <typename T, int L, int MODE = 0>
 __device__ __forceinline__ bool unit_in_eval(const Job& J, uint64_t sb, uint32_t h,
                                              uint64_t paydw, uint32_t nval,
                                              const uint32_t (&raw)[3], UnitIn& ui) {
   WaveBlocks wb;
-  const bool good = wave_blocks_eval<float, L>(J, sb, paydw, nval, raw, wb);
+  const bool good = wave_blocks_eval<T, L, MODE>(J, sb, paydw, nval, raw, wb);
   ui.kind = h ? wb.kind[1] : wb.kind[0];
   ui.F = h ? wb.F[1] : wb.F[0];
   ui.ex = h ? wb.ex[1] : wb.ex[0];
@@ -2994,7 +2994,7 @@ __device__ __forceinline__ void unit_analyse(const Job& J, uint64_t u, uint32_t 
     good = wave_header_eval<float>(J, hdr, paydw, fs.t);
     UnitIn ui;
     if (good)
-      good = unit_in_eval<L>(J, sb, (uint32_t)(u & 1), paydw,
+      good = unit_in_eval<float, L>(J, sb, (uint32_t)(u & 1), paydw,
                              (uint32_t)min((uint64_t)SUPER, J.n - sb * SUPER), raw, ui);
     fs.pay = (const uint32_t*)(in + J.pay_off);
     float v[32];
@@ -3467,6 +3467,222 @@ __global__ GZ_UNIT_ATTR(OP == 2) void k_batch_unit(const Job* __restrict__ jobs,
   unit_end(C, us, total);
 }
 
+// Mode 1 (fp32, 8x8 tiles, L = 64): lane w of tile seg/2 owns its rows
+// 4w..4w+3, loaded/stored as 4 rows of 8 floats.
+__device__ __forceinline__ void load_tile(const Job& J, const float* __restrict__ p, bool ex,
+                                          float (&v)[32]) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      f4u t = ex ? *(const f4u*)(p + r * (uint64_t)J.nx + 4 * h) : f4u{0, 0, 0, 0};
+      v[8 * r + 4 * h] = t.x; v[8 * r + 4 * h + 1] = t.y;
+      v[8 * r + 4 * h + 2] = t.z; v[8 * r + 4 * h + 3] = t.w;
+    }
+  }
+}
+__device__ __forceinline__ void store_tile(const Job& J, float* __restrict__ p,
+                                           const float (&v)[32]) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      f4u t;
+      t.x = v[8 * r + 4 * h]; t.y = v[8 * r + 4 * h + 1];
+      t.z = v[8 * r + 4 * h + 2]; t.w = v[8 * r + 4 * h + 3];
+      *(f4u*)(p + r * (uint64_t)J.nx + 4 * h) = t;
+    }
+  }
+}
+
+// ------------------------------------------------------------ unit decode
+// Decoding by single waves, a unit of 2048 elements each: 8x8 tiles, batches
+// that hold fp64 jobs, and short streams.  Units are independent (a
+// superblock's offset is its table entry, its second unit's follows from the
+// header bytes, which both units check whole), so waves take them statically.
+// A unit needs 9 KB of LDS (payload, then rows of values for coalesced stores;
+// fp64 rows 16 values at a time) and 128 registers: four waves per SIMD, where
+// the superblock decoder above has two (fp64, before, one; tiles, before, three
+// in 256-thread strips with barriers).  Bound by HBM for long fp64 streams,
+// by the two dependent loads of a unit for short ones.  20 M fp64 values 37.8
+// -> 30.4 us, 33 M tile values (compressed and decompressed) 188 -> 150 us, 512
+// mixed requests (both ways) 270 -> 234 us; fp32 streams of 2^20 / 2^22 / 2^24 /
+// 2^26 / 2^28 elements 10.1 / 11.2 / 19.5 / 68 / 266 us by superblocks, 9.3 /
+// 10.1 / 18.4 / 75 / 283 us by units.
+struct UnitDec {
+  static constexpr uint32_t STR = 36, XW = 64 * STR, WAVES = 4;  // region (dwords), per workgroup
+};
+
+// The lane's quantised values of a block that is not RAW, from its words at pw.
+template <int LPB>
+__device__ __forceinline__ void unpack_q(const uint32_t* pw, uint32_t kind, uint32_t F, uint32_t w,
+                                         bool exists, uint32_t (&a)[32]) {
+  const bool z = kind == K_ZERO || kind == K_RAW || !exists;
+  const uint32_t base = z ? 0u : pw[0], Fz = z ? 0u : F;
+  get_planes(pw + 1 + LPB + w, LPB, Fz, a);
+  const uint32_t sg = Fz ? pw[1 + w] : 0u;
+  uint32_t acc = 0;
+#pragma unroll
+  for (int i = 0; i < 32; ++i) {
+    const uint32_t neg = (uint32_t)__builtin_amdgcn_sbfe((int32_t)sg, i, 1);  // 0 or ~0
+    uint32_t d = (a[i] ^ neg) - neg;
+    if (i == 0 && w == 0) d = 0;
+    acc += d;
+    a[i] = acc;
+  }
+  const uint32_t carry = grp_excl_sum<LPB>(acc, w) + base;
+#pragma unroll
+  for (int i = 0; i < 32; ++i) a[i] += carry;
+}
+
+// Rows of 32 dwords in X to rows STRIDE dwords apart at dst, with 16-byte
+// stores (vdw: valid dwords from dst).
+template <uint32_t STRIDE, bool FULL>
+__device__ __forceinline__ void unit_rows_store(uint32_t* dst, uint32_t vdw, const uint32_t* X) {
+  const uint32_t lane = __lane_id();
+#pragma unroll
+  for (uint32_t k = 0; k < 8; ++k) {
+    const uint32_t row = 8 * k + lane / 8, c = 4 * (lane % 8), dw = row * STRIDE + c;
+    const u4u r = *(const u4u*)(X + row * UnitDec::STR + c);
+    if (FULL || dw + 4 <= vdw) {
+      *(u4u*)(dst + dw) = r;
+    } else {
+      if (dw + 0 < vdw) dst[dw + 0] = r.x;
+      if (dw + 1 < vdw) dst[dw + 1] = r.y;
+      if (dw + 2 < vdw) dst[dw + 2] = r.z;
+    }
+  }
+}
+
+template <typename T, int L, int MODE, bool FULL>
+__device__ __forceinline__ void unit_decode_put(const Job& J, uint64_t u, T t, const UnitIn& ui,
+                                                const uint32_t* pay, uint32_t* X) {
+  constexpr uint32_t LPB = L / 32, EW = sizeof(T) / 4;
+  const uint32_t lane = __lane_id(), w = lane & (LPB - 1);
+  const uint64_t e0 = u * UNIT_ELEMS;
+  const uint32_t hval = FULL ? (uint32_t)UNIT_ELEMS : (uint32_t)min((uint64_t)UNIT_ELEMS, J.n - e0);
+  const uint32_t vc = FULL ? 32u : (uint32_t)min(32, max(0, (int)hval - 32 * (int)lane));
+  const uint32_t* gp = pay + ui.off0;  // the unit's payload (global)
+  // fp64 payloads may exceed the region: those are read where they are
+  const bool fits = EW == 1 || ui.P + 4 <= UnitDec::XW;
+  const uint32_t* S = X;
+  if (fits) S = wave_stage_payload<UnitDec::XW - 4, true>(gp, ui.P, X);
+  wave_lds_sync();
+  if constexpr (MODE == 1) {
+    float v[32];
+    unpack_tile<float>(S + ui.boff, ui.kind, ui.F, w, ui.ex, t, v);
+    if (ui.ex) store_tile(J, (float*)J.out + seg_first<1>(J, u * 64 + lane), v);
+    wave_lds_sync();  // read before the next unit's payload goes there
+  } else if constexpr (EW == 1) {
+    float v[32];
+    unpack_seg<float, LPB, FULL>(S + ui.boff, ui.kind, ui.F, w, vc, ui.ex, t, v);
+    wave_lds_sync();  // every lane has read its payload words
+    f4u* p = (f4u*)(X + lane * UnitDec::STR);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) p[k] = f4u{v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]};
+    wave_lds_sync();
+    unit_rows_store<32, FULL>((uint32_t*)((float*)J.out + e0), hval, X);
+    wave_lds_sync();
+  } else {
+    uint32_t q[32];
+    if (fits) unpack_q<LPB>(S + ui.boff, ui.kind, ui.F, w, ui.ex, q);
+    else unpack_q<LPB>(gp + ui.boff, ui.kind, ui.F, w, ui.ex, q);
+    const uint32_t* rw = gp + ui.boff + w * 64;  // a RAW block's words of this lane
+    uint32_t* dst = (uint32_t*)((double*)J.out + e0);
+#pragma unroll
+    for (uint32_t p = 0; p < 2; ++p) {
+      wave_lds_sync();  // payload words (or the first half's rows) have been read
+      d2u* row = (d2u*)(X + lane * UnitDec::STR);
+      if (ui.kind == K_RAW && ui.ex) {
+#pragma unroll
+        for (uint32_t i = 0; i < 16; ++i) {
+          const uint32_t e = 16 * p + i;
+          if (FULL || e < vc) ((double*)row)[i] = from_raw(rw + 2 * e, 0.0);
+        }
+      } else {
+#pragma unroll
+        for (uint32_t i = 0; i < 16; i += 2)
+          row[i / 2] = d2u{(double)(int32_t)q[16 * p + i] * t, (double)(int32_t)q[16 * p + i + 1] * t};
+      }
+      wave_lds_sync();
+      const uint32_t vdw = 2 * hval > 32 * p ? 2 * hval - 32 * p : 0u;
+      unit_rows_store<64, FULL>(dst + 32 * p, vdw, X);
+    }
+    wave_lds_sync();
+  }
+}
+
+// Decodes unit u of the stream at `in` (job J, in_bytes readable); false
+// (nothing written) if its superblock is malformed.
+template <typename T, int L, int MODE>
+__device__ __forceinline__ bool unit_decode(const Job& J, const uint8_t* in, uint64_t u,
+                                            uint32_t* X) {
+  const uint64_t sb = u >> 1;
+  uint32_t raw[3];
+  const uint32_t hdr = wave_header_load(J, in);
+  wave_blocks_load<L, true>(J, in, sb, raw);  // in flight with the header's words
+  uint64_t paydw = 0;
+  T t = 0;
+  if (!wave_header_eval<T>(J, hdr, paydw, t)) return false;
+  UnitIn ui;
+  if (!unit_in_eval<T, L, MODE>(J, sb, (uint32_t)(u & 1), paydw,
+                                (uint32_t)min((uint64_t)SUPER, J.n - sb * SUPER), raw, ui))
+    return false;
+  const uint32_t* pay = (const uint32_t*)(in + J.pay_off);
+  if ((u + 1) * UNIT_ELEMS <= J.n) unit_decode_put<T, L, MODE, true>(J, u, t, ui, pay, X);
+  else if (u * UNIT_ELEMS < J.n) unit_decode_put<T, L, MODE, false>(J, u, t, ui, pay, X);
+  return true;
+}
+
+#define GZ_UNIT_DEC_ATTR \
+  __launch_bounds__(UnitDec::WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
+
+template <typename T, int L, int MODE>
+__global__ GZ_UNIT_DEC_ATTR void k_unit_decode(Job J, Ctl C) {
+  const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn = blockDim.x >> 6;
+  uint32_t* X = g_stage + wid * UnitDec::XW;
+  bool bad = false;
+  if (J.NS == 0) {  // an empty stream: its header only
+    uint64_t paydw;
+    T t;
+    bad = !wave_header<T>(J, (const uint8_t*)J.in, paydw, t);
+  }
+  for (uint64_t u = (uint64_t)blockIdx.x * wn + wid; u < 2 * J.NS; u += (uint64_t)gridDim.x * wn)
+    bad |= !unit_decode<T, L, MODE>(J, (const uint8_t*)J.in, u, X);
+  if (bad && __lane_id() == 0) atomicOr(&C.ctrl->err, ERRF_CORRUPT);
+}
+
+// A batch's superblocks as k_batch_accum_w takes them, two units each.
+__global__ GZ_UNIT_DEC_ATTR void k_batch_unit_decode(const Job* __restrict__ jobs,
+                                                     const uint32_t* __restrict__ map,
+                                                     uint32_t njobs, uint32_t total, Ctl C) {
+  const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wn = blockDim.x >> 6;
+  uint32_t* X = g_stage + wid * UnitDec::XW;
+  bool bad = false;
+  for (uint64_t i = (uint64_t)blockIdx.x * wn + wid; i < 2ull * total;
+       i += (uint64_t)gridDim.x * wn) {
+    const uint64_t s = i >> 1;
+    const uint32_t j = map ? map[2 * s] : (uint32_t)s % njobs;
+    const uint64_t u = 2 * (uint64_t)(map ? map[2 * s + 1] : (uint32_t)s / njobs) + (i & 1);
+    Job J = jobs[j];
+    const uint64_t off = J.in_off ? J.in_off[J.job] : 0ull;
+    J.in_bytes = off <= J.in_bytes ? J.in_bytes - off : 0ull;
+    const uint8_t* in = (const uint8_t*)J.in + off;
+    bool ok = false;
+    switch ((J.dtype << 3) | J.log2L) {
+      case 5: ok = unit_decode<float, 32, 0>(J, in, u, X); break;
+      case 6: ok = unit_decode<float, 64, 0>(J, in, u, X); break;
+      case 7: ok = unit_decode<float, 128, 0>(J, in, u, X); break;
+      case 13: ok = unit_decode<double, 32, 0>(J, in, u, X); break;
+      case 14: ok = unit_decode<double, 64, 0>(J, in, u, X); break;
+      case 15: ok = unit_decode<double, 128, 0>(J, in, u, X); break;
+      default: break;
+    }
+    bad |= !ok;
+  }
+  if (bad && __lane_id() == 0) atomicOr(&C.ctrl->err, ERRF_CORRUPT);
+}
+
 template <int L, bool FULL>
 __device__ __forceinline__ void fused_body(const Job& J, uint64_t s, uint64_t gs, const Ctl& C,
                                            Smem& sm, uint32_t& tk) {
@@ -3628,34 +3844,6 @@ __attribute__((amdgpu_waves_per_eu((OP == 0 && WIDE) ? 3 : 4, 8))) void k_batch(
 }
 
 // ------------------------------------------------------------ tile mode
-// Mode 1 (fp32, 8x8 tiles, L = 64): lane w of tile seg/2 owns its rows
-// 4w..4w+3, loaded/stored as 4 rows of 8 floats.
-__device__ __forceinline__ void load_tile(const Job& J, const float* __restrict__ p, bool ex,
-                                          float (&v)[32]) {
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      f4u t = ex ? *(const f4u*)(p + r * (uint64_t)J.nx + 4 * h) : f4u{0, 0, 0, 0};
-      v[8 * r + 4 * h] = t.x; v[8 * r + 4 * h + 1] = t.y;
-      v[8 * r + 4 * h + 2] = t.z; v[8 * r + 4 * h + 3] = t.w;
-    }
-  }
-}
-__device__ __forceinline__ void store_tile(const Job& J, float* __restrict__ p,
-                                           const float (&v)[32]) {
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      f4u t;
-      t.x = v[8 * r + 4 * h]; t.y = v[8 * r + 4 * h + 1];
-      t.z = v[8 * r + 4 * h + 2]; t.w = v[8 * r + 4 * h + 3];
-      *(f4u*)(p + r * (uint64_t)J.nx + 4 * h) = t;
-    }
-  }
-}
-
 template <bool FULL>
 __device__ __forceinline__ void compress_tiles_body(const Job& J, uint64_t s, uint64_t gs,
                                                     const Ctl& C, Smem& sm, uint32_t& tk) {
@@ -3811,25 +3999,20 @@ static hipError_t launch_d(const Job& J, const Ctl& C, uint32_t tpb, uint32_t gr
                      J, C);
   return hipGetLastError();
 }
-template <typename T, int L>
+template <int L>
 static hipError_t launch_dw(const Job& J, const Ctl& C, uint32_t grid, hipStream_t st) {
-  const size_t lds = (size_t)WaveDec<T>::WAVES * WaveDec<T>::REGION * 4;
-  hipLaunchKernelGGL((k_decompress_w<T, L>), dim3(grid), dim3(WaveDec<T>::WAVES * 64), lds, st, J,
-                     C);
+  hipLaunchKernelGGL((k_decompress_w<L>), dim3(grid), dim3(WaveDec<float>::WAVES * 64),
+                     wave_decode_lds(), st, J, C);
   return hipGetLastError();
 }
 
 hipError_t launch_decompress_wave(const Job& J, const Ctl& C, uint32_t cus, hipStream_t st) {
-  const uint32_t waves = J.dtype == 0 ? WaveDec<float>::WAVES : WaveDec<double>::WAVES;
-  const uint64_t need = (J.NS + waves - 1) / waves;
+  const uint64_t need = (J.NS + WaveDec<float>::WAVES - 1) / WaveDec<float>::WAVES;
   const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(cus, need));
-  switch ((J.dtype << 3) | J.log2L) {
-    case 5: return launch_dw<float, 32>(J, C, grid, st);
-    case 6: return launch_dw<float, 64>(J, C, grid, st);
-    case 7: return launch_dw<float, 128>(J, C, grid, st);
-    case 13: return launch_dw<double, 32>(J, C, grid, st);
-    case 14: return launch_dw<double, 64>(J, C, grid, st);
-    case 15: return launch_dw<double, 128>(J, C, grid, st);
+  switch (J.log2L) {
+    case 5: return launch_dw<32>(J, C, grid, st);
+    case 6: return launch_dw<64>(J, C, grid, st);
+    case 7: return launch_dw<128>(J, C, grid, st);
   }
   return hipErrorInvalidValue;
 }
@@ -3921,6 +4104,42 @@ hipError_t launch_batch_unit(uint32_t op, const Job* d_jobs, const uint32_t* d_m
   return hipErrorInvalidValue;
 }
 
+template <typename T, int L, int MODE>
+static hipError_t launch_ud(const Job& J, const Ctl& C, uint32_t grid, uint32_t waves,
+                            hipStream_t st) {
+  hipLaunchKernelGGL((k_unit_decode<T, L, MODE>), dim3(grid), dim3(waves * 64),
+                     (size_t)waves * UnitDec::XW * 4, st, J, C);
+  return hipGetLastError();
+}
+
+hipError_t launch_unit_decode(const Job& J, const Ctl& C, uint32_t cus, hipStream_t st) {
+  // short streams: a wave a workgroup, so that they spread over the CUs
+  const uint64_t units = std::max<uint64_t>(1, 2 * J.NS);
+  const uint32_t waves = units <= 2ull * cus ? 1 : UnitDec::WAVES;
+  const uint32_t grid =
+      (uint32_t)std::min<uint64_t>((uint64_t)cus * 16 / waves, (units + waves - 1) / waves);
+  if (J.mode == 1) return launch_ud<float, 64, 1>(J, C, grid, waves, st);
+  switch ((J.dtype << 3) | J.log2L) {
+    case 5: return launch_ud<float, 32, 0>(J, C, grid, waves, st);
+    case 6: return launch_ud<float, 64, 0>(J, C, grid, waves, st);
+    case 7: return launch_ud<float, 128, 0>(J, C, grid, waves, st);
+    case 13: return launch_ud<double, 32, 0>(J, C, grid, waves, st);
+    case 14: return launch_ud<double, 64, 0>(J, C, grid, waves, st);
+    case 15: return launch_ud<double, 128, 0>(J, C, grid, waves, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_batch_unit_decode(const Job* d_jobs, const uint32_t* d_map, uint32_t njobs,
+                                    uint32_t total, uint32_t cus, const Ctl& C, hipStream_t st) {
+  const uint64_t units = std::max<uint64_t>(1, 2ull * total);
+  const uint32_t grid = (uint32_t)std::min<uint64_t>(
+      (uint64_t)cus * 16 / UnitDec::WAVES, (units + UnitDec::WAVES - 1) / UnitDec::WAVES);
+  hipLaunchKernelGGL(k_batch_unit_decode, dim3(grid), dim3(UnitDec::WAVES * 64),
+                     (size_t)UnitDec::WAVES * UnitDec::XW * 4, st, d_jobs, d_map, njobs, total, C);
+  return hipGetLastError();
+}
+
 template <int L>
 static hipError_t launch_aw(const Job& J, const Ctl& C, uint32_t grid, hipStream_t st) {
   const size_t lds = (size_t)WaveDec<float>::WAVES * WaveDec<float>::REGION * 4;
@@ -3939,33 +4158,29 @@ hipError_t launch_accum_wave(const Job& J, const Ctl& C, uint32_t cus, hipStream
   return hipErrorInvalidValue;
 }
 
-template <bool WIDE, uint32_t OP>
-static hipError_t launch_bdw(const Job* d_jobs, const uint32_t* d_map, uint32_t njobs,
-                             uint32_t total, uint32_t jw, uint32_t cus, const Ctl& C,
-                             hipStream_t st) {
-  constexpr uint32_t WAVES = WIDE ? WaveDec<double>::WAVES : WaveDec<float>::WAVES;
-  const size_t lds = (size_t)WAVES * (WIDE ? WaveDec<double>::REGION : WaveDec<float>::REGION) * 4;
-  const uint64_t need = ((uint64_t)(jw ? jw : total) + WAVES - 1) / WAVES;
-  const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(cus, need));
-  hipLaunchKernelGGL((k_batch_decode_w<WIDE, OP>), dim3(grid), dim3(WAVES * 64), lds, st, d_jobs,
-                     d_map, njobs, total, jw, C);
+hipError_t launch_decode_shares(const Job* d_jobs, const uint32_t* d_map, uint32_t jw,
+                                uint32_t cus, const Ctl& C, hipStream_t st) {
+  constexpr uint32_t WAVES = WaveDec<float>::WAVES;
+  const uint32_t grid =
+      (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(cus, (jw + WAVES - 1) / WAVES));
+  hipLaunchKernelGGL(k_batch_decode_w, dim3(grid), dim3(WAVES * 64), wave_decode_lds(), st, d_jobs,
+                     d_map, jw, C);
   return hipGetLastError();
 }
 
-hipError_t launch_decode_wave_batch(uint32_t op, const Job* d_jobs, const uint32_t* d_map,
-                                    uint32_t njobs, uint32_t total, bool wide, uint32_t jw,
-                                    uint32_t cus, const Ctl& C, hipStream_t st) {
-  if (op == 1)
-    return wide ? launch_bdw<true, 1>(d_jobs, d_map, njobs, total, 0, cus, C, st)
-                : launch_bdw<false, 1>(d_jobs, d_map, njobs, total, jw, cus, C, st);
-  if (op == 3 && !wide) return launch_bdw<false, 3>(d_jobs, d_map, njobs, total, 0, cus, C, st);
-  return hipErrorInvalidValue;
+hipError_t launch_accum_wave_batch(const Job* d_jobs, const uint32_t* d_map, uint32_t njobs,
+                                   uint32_t total, uint32_t cus, const Ctl& C, hipStream_t st) {
+  constexpr uint32_t WAVES = WaveDec<float>::WAVES;
+  const uint64_t need = ((uint64_t)total + WAVES - 1) / WAVES;
+  const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(cus, need));
+  hipLaunchKernelGGL(k_batch_accum_w, dim3(grid), dim3(WAVES * 64), wave_decode_lds(), st, d_jobs,
+                     d_map, njobs, total, C);
+  return hipGetLastError();
 }
 
-size_t wave_decode_lds(uint32_t dtype) {
-  return dtype == 0 ? (size_t)WaveDec<float>::WAVES * WaveDec<float>::REGION * 4
-                    : (size_t)WaveDec<double>::WAVES * WaveDec<double>::REGION * 4;
-}
+size_t wave_decode_lds() { return (size_t)WaveDec<float>::WAVES * WaveDec<float>::REGION * 4; }
+
+size_t unit_decode_lds() { return (size_t)UnitDec::WAVES * UnitDec::XW * 4; }
 
 template <int L>
 static hipError_t launch_a(const Job& J, const Ctl& C, uint32_t tpb, uint32_t grid,

@@ -153,3 +153,72 @@ def test_fp64_quotients_are_correctly_rounded(ctx, eb):
         want = np.where(fail, 0.0, rr).astype(np.int64)
     assert np.array_equal(got_f.cpu().numpy() != 0, fail)
     assert np.array_equal(got_q.cpu().numpy().astype(np.int64), want)
+
+
+@pytest.mark.parametrize("dt", [np.float32, np.float64])
+@pytest.mark.parametrize("L", [32, 64, 128])
+@pytest.mark.parametrize("kind", ["smooth", "dense", "raw", "mixed"])
+def test_decompress_at_unit_edges(ctx, oracle, dt, L, kind):
+    """fp32 streams of 128 to 4096 superblocks and all fp64 streams are decoded
+    by units; fp64 RAW payloads exceed the unit's LDS region."""
+    import torch
+    lo = 127 * 4096 if dt == np.float32 else 0
+    for n in [lo + k for k in (1, 2047, 2048, 2049, 4095, 4096, 4097, 3 * UNIT + 33)]:
+        say("decode units", dt.__name__, L, kind, n)
+        s = oracle.compress(field(kind, n, dt, n), 1e-4, block_len=L)
+        out = torch.full((n + 8,), -7.0, dtype=torch.float32 if dt == np.float32 else torch.float64,
+                         device="cuda")
+        ctx.decompress(dev(s), n, block_len=L, out=out[:n])
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()
+        assert got[:n].tobytes() == oracle.decompress(s).tobytes(), n
+        assert (got[n:] == -7.0).all(), n
+    assert ctx.device_status() == 0
+
+
+@pytest.mark.parametrize("dt", [np.float32, np.float64])
+def test_malformed_units_set_the_status(gz, ctx, oracle, dt):
+    """A damaged header byte, table entry or stream header is found whichever
+    unit of the superblock holds it, in single streams and in batches."""
+    import torch
+    n = 130 * 4096 + 5
+    s = oracle.compress(field("smooth", n, dt, 3), 1e-4)
+    ns = (n + 4095) // 4096
+    hb = 64 + 4 * ns
+    tdt = torch.float32 if dt == np.float32 else torch.float64
+    for what, at in (("first unit's header byte", hb + 128 * 7 + 3),
+                     ("second unit's header byte", hb + 128 * 7 + 100), ("table", 64 + 4 * 9),
+                     ("magic", 0), ("size", 8)):
+        say("malformed", dt.__name__, what)
+        b = s.copy()
+        b[at] ^= 0x15
+        ctx.decompress(dev(b), n, dtype=tdt)
+        assert ctx.device_status() == gz.GZ_ECORRUPT, what
+        x64 = oracle.compress(field("smooth", 5000, np.float64, 4), 1e-4)
+        good = torch.zeros(5000, dtype=torch.float64, device="cuda")
+        ctx.batch(gz.GZ_OP_DECOMPRESS, ctx.requests([
+            {"in": dev(b), "in_bytes": b.size, "out": torch.zeros(n, dtype=tdt, device="cuda"),
+             "n": n, "dtype": gz.GZ_F32 if dt == np.float32 else gz.GZ_F64},
+            {"in": dev(x64), "in_bytes": x64.size, "out": good, "n": 5000, "dtype": gz.GZ_F64}]))
+        assert ctx.device_status() == gz.GZ_ECORRUPT, what
+        assert good.cpu().numpy().tobytes() == oracle.decompress(x64).tobytes(), what
+    ctx.decompress(dev(s), n, dtype=tdt)
+    assert ctx.device_status() == 0
+
+
+@pytest.mark.parametrize("nx,rows", [(8, 8), (8, 264), (72, 40), (1024, 72)])
+def test_tile_decode_at_unit_edges(gz, ctx, oracle, nx, rows):
+    import ctypes
+    import torch
+    for kind in ("smooth", "mixed"):
+        x = field(kind, nx * rows, np.float32, nx + rows)
+        s = oracle.compress(x, 1e-4, block_len=64, mode=1, nx=nx, select=1)
+        y = torch.zeros(x.size, device="cuda")
+        S = dev(s)
+        p = gz.gz_params(64, 0, 0, 1, 1, nx)
+        say("tiles", nx, rows, kind)
+        assert gz.gz_decompress(ctx.h, gz._ptr(S), s.size, x.size, gz.GZ_F32, ctypes.byref(p),
+                                gz._ptr(y), gz._stream()) == gz.GZ_OK
+        torch.cuda.synchronize()
+        assert ctx.device_status() == 0
+        assert y.cpu().numpy().tobytes() == oracle.decompress(s).tobytes()
