@@ -80,9 +80,9 @@ typedef struct gz_graph gz_graph;
  * ignored): 1D decompression of either type (also batched and scatter), fp32
  * 1D compression, the fused step and decode-and-accumulate; GZ_EUNSUPPORTED
  * elsewhere.  With no shape given or tuned, 1D compression of either type
- * (single, batched and fp64 scatter chunks), decompression (single, batched,
- * scatter and tiles) and the fused step take them; decode-and-accumulate, fp32
- * scatter compression and tile compression take strips.  mode 0 = 1D blocks, 1 = 8x8 tiles (block_len 64,
+ * (single, batched and fp64 scatter chunks), decompression (single, batched and
+ * scatter), both directions of tiles and the fused step take them;
+ * decode-and-accumulate and fp32 scatter compression take strips.  mode 0 = 1D blocks, 1 = 8x8 tiles (block_len 64,
  * nx = row length, multiple of 8, n a multiple of 8*nx); select (mode 1):
  * 0 = int8 MLP selector, 1 = exhaustive trial, 2 = always L1D. */
 typedef struct {

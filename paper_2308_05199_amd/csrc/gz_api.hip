@@ -805,6 +805,11 @@ gz_status compress_impl(gz_ctx* c, const void* d_in, uint64_t n, gz_dtype dtype,
     J.mode = 1;
     J.nx = p->nx;
     J.select = p->select;
+    uint32_t W;
+    gzk::Job U = J;  // units, unless a shape was asked for
+    if (!p->threads && !p->grid && unit_fits(c, 0) && unit_single(c, 0, U, W))
+      return hip_status(
+          gzk::launch_unit(0, U, c->ctl(), W, (uint32_t)c->cus, (hipStream_t)stream));
     const uint32_t grid = pick_tile_grid(c, gzk::OCC_TILE_C, tpb, J.nstrips, p);
     return hip_status(gzk::launch_tiles(0, J, c->ctl(), tpb, grid, (hipStream_t)stream));
   }

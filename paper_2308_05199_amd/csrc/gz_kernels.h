@@ -44,8 +44,8 @@ hipError_t launch_fused_wave(const Job* d_jobs, uint32_t njobs, uint32_t total, 
 constexpr uint64_t WAVE_ROUND = 8;  // superblocks per round
 size_t wave_fused_lds();            // its workgroup's LDS bytes
 inline uint64_t wave_rounds(uint64_t NS) { return (NS + WAVE_ROUND - 1) / WAVE_ROUND; }
-// Unit encoding (op 0 compression of either type, op 2 the fp32 fused step),
-// mode 0: every working wave codes units of 2048 elements, the `workers` of a
+// Unit encoding (op 0 compression of either type or of 8x8 tiles, op 2 the fp32
+// fused step): every working wave codes units of 2048 elements, the `workers` of a
 // workgroup (which has one wave more, the scheduler) a round of that many
 // units (one look-back word).  J.nstrips = total rounds (unit_rounds).
 hipError_t launch_unit(uint32_t op, const Job& J, const Ctl& C, uint32_t workers, uint32_t cus,

@@ -1101,9 +1101,9 @@ __device__ __forceinline__ uint64_t seg_off(const Job& J, int i) {
 template <int MODE>
 __device__ __forceinline__ uint64_t seg_first(const Job& J, uint64_t seg) {
   if (MODE == 0) return seg * SEG;
-  const uint64_t b = seg >> 1, tpr = J.nx / 8;
-  const uint64_t R = b / tpr, Cc = b - R * tpr;
-  return (8 * R + 4 * (seg & 1)) * J.nx + 8 * Cc;
+  const uint32_t b = (uint32_t)(seg >> 1), tpr = J.nx / 8;  // fewer than 2^26 tiles: n < 2^32
+  const uint32_t R = b / tpr, Cc = b - R * tpr;
+  return (8 * (uint64_t)R + 4 * (seg & 1)) * J.nx + 8 * Cc;
 }
 
 // Scan, publish, stage, look back and write one strip (any mode).  KEEPV:
@@ -2354,15 +2354,16 @@ __device__ __forceinline__ bool lds_wait_ge(const Ctl& C, const uint32_t* p, uin
 // The lane's share of its block's payload at st (the block's first word):
 // base, sign word and planes of an L1D block, or the values of a RAW block
 // (from registers, re-derived by the fused step, or re-read from J.in).
-template <typename T, int L, bool FUSED, bool FULL>
+template <typename T, int L, bool FUSED, bool FULL, int MODE = 0>
 __device__ __forceinline__ void wave_pack(const Job& J, uint64_t seg, uint32_t w, uint32_t vcnt,
                                           const LaneCode& lc, const FusedSrc& fs, uint32_t* st) {
   constexpr uint32_t LPB = L / 32, EW = sizeof(T) / 4;
-  if (lc.kind == K_L1D) {
-    if (w == 0) st[0] = (uint32_t)lc.base;
+  if (lc.kind == K_L1D || (MODE == 1 && (lc.kind == K_L2D || lc.kind == K_NONE))) {
+    const uint32_t o = MODE == 1 && lc.kind == K_NONE ? 0u : 1u;  // NONE stores no base
+    if (o && w == 0) st[0] = (uint32_t)lc.base;
     if (lc.F) {
-      st[1 + w] = lc.sg;
-      put_planes(lc.a, lc.F, st + 1 + LPB + w, LPB);
+      st[o + w] = lc.sg;
+      put_planes(lc.a, lc.F, st + o + LPB + w, LPB);
     }
   }
   if (FUSED && lc.kind == K_RAW && lc.rawregs) {
@@ -2373,13 +2374,41 @@ __device__ __forceinline__ void wave_pack(const Job& J, uint64_t seg, uint32_t w
     if (FUSED) {
       fused_raw_stage<LPB>(J, fs, seg, w, vcnt, st);
     } else {
-      const T* src = (const T*)J.in + seg * SEG;
+      const T* src = (const T*)J.in + seg_first<MODE>(J, seg);
       for (int i = 0; i < (int)vcnt; ++i) {
         uint32_t wd[2];
-        raw_words(src[i], wd);
+        raw_words(src[seg_off<MODE>(J, i)], wd);
         st[(w * 32 + i) * EW] = wd[0];
         if (EW == 2) st[(w * 32 + i) * EW + 1] = wd[1];
       }
+    }
+  }
+}
+
+// Mode 1 (fp32, 8x8 tiles, L = 64): lane w of tile seg/2 owns its rows
+// 4w..4w+3, loaded/stored as 4 rows of 8 floats.
+__device__ __forceinline__ void load_tile(const Job& J, const float* __restrict__ p, bool ex,
+                                          float (&v)[32]) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      f4u t = ex ? *(const f4u*)(p + r * (uint64_t)J.nx + 4 * h) : f4u{0, 0, 0, 0};
+      v[8 * r + 4 * h] = t.x; v[8 * r + 4 * h + 1] = t.y;
+      v[8 * r + 4 * h + 2] = t.z; v[8 * r + 4 * h + 3] = t.w;
+    }
+  }
+}
+__device__ __forceinline__ void store_tile(const Job& J, float* __restrict__ p,
+                                           const float (&v)[32]) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      f4u t;
+      t.x = v[8 * r + 4 * h]; t.y = v[8 * r + 4 * h + 1];
+      t.z = v[8 * r + 4 * h + 2]; t.w = v[8 * r + 4 * h + 3];
+      *(f4u*)(p + r * (uint64_t)J.nx + 4 * h) = t;
     }
   }
 }
@@ -2973,16 +3002,21 @@ __device__ __forceinline__ bool unit_in_eval(const Job& J, uint64_t sb, uint32_t
 // Loads and analyses unit u of job J (fused: incoming stream J.in plus
 // addend J.local): the lane's code lc and, for RAW blocks of the fused step,
 // its source fs.  X is free for the payload afterwards.
-template <typename T, int L, bool FUSED, bool FULL>
+template <typename T, int L, bool FUSED, bool FULL, int MODE>
 __device__ __forceinline__ void unit_analyse(const Job& J, uint64_t u, uint32_t w, uint32_t vcnt,
                                              uint32_t* X, LaneCode& lc, FusedSrc& fs,
-                                             bool& good) {
+                                             bool& good, const uint32_t* wts) {
   constexpr uint32_t LPB = L / 32, EW = sizeof(T) / 4, STR = UnitEnc<FUSED>::STR;
   const uint32_t lane = __lane_id();
   const uint64_t e0 = u * (uint32_t)UNIT_ELEMS, seg = u * 64 + lane;
   const uint32_t hval = FULL ? (uint32_t)UNIT_ELEMS : (uint32_t)min((uint64_t)(uint32_t)UNIT_ELEMS, J.n - e0);
   good = true;
-  if constexpr (FUSED) {
+  if constexpr (MODE == 1) {
+    const bool ex = FULL || (seg >> 1) < J.B;
+    float v[32];
+    load_tile(J, (const float*)J.in + (ex ? seg_first<1>(J, seg) : 0), ex, v);
+    analyze_tile(J, w, v, ex, wts, lc);
+  } else if constexpr (FUSED) {
     const uint8_t* in = (const uint8_t*)J.in;
     const uint64_t sb = u >> 1;
     uint32_t raw[3];
@@ -3244,11 +3278,12 @@ __device__ __forceinline__ void unit_flush(const Job& J, const Ctl& C, USched& u
 // One unit: round k of the workgroup is round r of job J (index job); worker
 // wid codes unit u = W r + wid (past the job's end: an empty slot).  flush(q)
 // writes the oldest unit held.
-template <typename T, int L, bool FUSED, bool FULL, class Flush>
+template <typename T, int L, bool FUSED, bool FULL, int MODE, class Flush>
 __device__ __forceinline__ void unit_code(const Job& J, uint32_t job, uint64_t gs, uint64_t u,
                                           bool live, uint32_t k, uint32_t wid, uint32_t W,
                                           uint32_t total, USched& us, const Ctl& C,
-                                          uint32_t* X, UnitQueue& q, const Flush& flush) {
+                                          uint32_t* X, UnitQueue& q, const Flush& flush,
+                                          const uint32_t* wts) {
   using U = UnitEnc<FUSED>;
   constexpr uint32_t LPB = L / 32;
   const uint32_t lane = __lane_id(), w = lane & (LPB - 1);
@@ -3265,7 +3300,7 @@ __device__ __forceinline__ void unit_code(const Job& J, uint32_t job, uint64_t g
   if (live) {
     if (!FULL)
       vcnt = (uint32_t)min((int64_t)32, max((int64_t)0, (int64_t)(J.n - e0) - 32 * (int64_t)lane));
-    unit_analyse<T, L, FUSED, FULL>(J, u, w, vcnt, X, lc, fs, good);
+    unit_analyse<T, L, FUSED, FULL, MODE>(J, u, w, vcnt, X, lc, fs, good, wts);
     const uint32_t contrib = w == 0 ? lc.size_dw : 0u;
     const uint32_t incl = wave_incl_scan(contrib);
     boff = w == 0 ? incl - contrib : incl - lc.size_dw;
@@ -3324,7 +3359,7 @@ __device__ __forceinline__ void unit_code(const Job& J, uint32_t job, uint64_t g
     ((uint8_t*)HB)[lane / LPB] = (uint8_t)(lc.exists ? ((lc.kind << 5) | lc.F) : 0u);
   wave_lds_sync();  // every row of X is read before the payload goes there
   if (held) {
-    wave_pack<T, L, FUSED, FULL>(J, seg, w, vcnt, lc, fs, Q + at + boff);
+    wave_pack<T, L, FUSED, FULL, MODE>(J, seg, w, vcnt, lc, fs, Q + at + boff);
     if (first) open(tk);
     wave_lds_sync();  // payload and header bytes are complete
     if (good) {
@@ -3339,7 +3374,7 @@ __device__ __forceinline__ void unit_code(const Job& J, uint32_t job, uint64_t g
   // it is packed in two halves of 32 lanes (no block crosses them).
   const uint32_t lo = sizeof(T) == 8 ? read_lane(boff, 32) : 0u;
   const bool two = sizeof(T) == 8 && size > U::PACKW;
-  if (!two) wave_pack<T, L, FUSED, FULL>(J, seg, w, vcnt, lc, fs, X + boff);
+  if (!two) wave_pack<T, L, FUSED, FULL, MODE>(J, seg, w, vcnt, lc, fs, X + boff);
   wave_lds_sync();
   uint64_t off, pj;
   const bool known = unit_offset(C, us, k, wid, off, pj);
@@ -3355,7 +3390,7 @@ __device__ __forceinline__ void unit_code(const Job& J, uint32_t job, uint64_t g
 #pragma unroll 1
     for (uint32_t p = 0; p < 2; ++p) {
       const uint32_t o = p ? lo : 0u, m = p ? size - lo : lo;
-      if ((lane >> 5) == p) wave_pack<T, L, FUSED, FULL>(J, seg, w, vcnt, lc, fs, X + boff - o);
+      if ((lane >> 5) == p) wave_pack<T, L, FUSED, FULL, MODE>(J, seg, w, vcnt, lc, fs, X + boff - o);
       wave_lds_sync();
       for (uint32_t i = lane; i < m; i += 64) dst[o + i] = X[i];
       wave_lds_sync();
@@ -3364,18 +3399,19 @@ __device__ __forceinline__ void unit_code(const Job& J, uint32_t job, uint64_t g
   wave_lds_sync();  // the region is read before the next unit reuses it
 }
 
-template <typename T, int L, bool FUSED, class Flush>
+template <typename T, int L, bool FUSED, int MODE = 0, class Flush>
 __device__ __forceinline__ void unit_one(const Job& J, uint32_t job, uint64_t r, uint32_t k,
                                          uint32_t wid, uint32_t W, uint32_t total, USched& us,
                                          const Ctl& C, uint32_t* X, UnitQueue& q,
-                                         const Flush& flush) {
+                                         const Flush& flush,
+                                         const uint32_t* wts = nullptr) {
   const uint64_t u = r * W + wid;
   // an empty stream is one unit of no values
   const bool live = u == 0 || u * UNIT_ELEMS < J.n;
   if ((u + 1) * UNIT_ELEMS <= J.n)
-    unit_code<T, L, FUSED, true>(J, job, J.strip0 + r, u, live, k, wid, W, total, us, C, X, q, flush);
+    unit_code<T, L, FUSED, true, MODE>(J, job, J.strip0 + r, u, live, k, wid, W, total, us, C, X, q, flush, wts);
   else
-    unit_code<T, L, FUSED, false>(J, job, J.strip0 + r, u, live, k, wid, W, total, us, C, X, q, flush);
+    unit_code<T, L, FUSED, false, MODE>(J, job, J.strip0 + r, u, live, k, wid, W, total, us, C, X, q, flush, wts);
 }
 
 // Registers for four waves per SIMD (the fused step: three), as the LDS allows.
@@ -3408,6 +3444,42 @@ __global__ GZ_UNIT_ATTR(FUSED) void k_unit(Job J, Ctl C) {
       const uint32_t t = __builtin_amdgcn_readfirstlane(us.rs[k % RING].ticket);
       if (t >= total) break;
       unit_one<T, L, FUSED>(J, 0, t, k, wid, W, total, us, C, X, q, flush);
+    }
+    while (q.n) flush(q);
+  }
+  unit_end(C, us, total);
+}
+
+// One field of 8x8 tiles: a unit's lanes load their rows straight from the
+// field.  Bound by VALU issue (the selector's features and network, or three
+// predictors).  33 M values with the learned selector, compressed and
+// decompressed: 150 -> 125 us against 256-thread strips (128-131 us with 11
+// workers).
+__global__ GZ_UNIT_ATTR(false) void k_unit_tiles(Job J, Ctl C) {
+  __shared__ USched us;
+  __shared__ uint32_t wts[192];
+  const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t W = (blockDim.x >> 6) - 1, total = J.nstrips;
+  for (uint32_t k = threadIdx.x; k < 189; k += blockDim.x) wts[k] = ((const uint32_t*)C.blob)[k];
+  unit_begin(C, us, total);  // ends with a barrier
+  if (wid == W) {
+    __builtin_amdgcn_s_setprio(3);
+    for (uint32_t k = 0;; ++k) {
+      if (!lds_wait_ge(C, &us.rs[k % RING].ready, k + 1)) break;
+      const uint32_t t = __builtin_amdgcn_readfirstlane(us.rs[k % RING].ticket);
+      if (t >= total) break;
+      if (!unit_sched(C, us, k, W, UChain{t, 0, t, 0, false})) break;
+    }
+  } else {
+    uint32_t* X = g_stage + wid * UnitEnc<false>::REGION;
+    UnitQueue q;
+    q.n = 0;
+    auto flush = [&](UnitQueue& x) { unit_flush(J, C, us, wid, X + UnitEnc<false>::XW, x); };
+    for (uint32_t k = 0;; ++k) {
+      if (!lds_wait_ge(C, &us.rs[k % RING].ready, k + 1)) break;
+      const uint32_t t = __builtin_amdgcn_readfirstlane(us.rs[k % RING].ticket);
+      if (t >= total) break;
+      unit_one<float, 64, false, 1>(J, 0, t, k, wid, W, total, us, C, X, q, flush, wts);
     }
     while (q.n) flush(q);
   }
@@ -3465,34 +3537,6 @@ __global__ GZ_UNIT_ATTR(OP == 2) void k_batch_unit(const Job* __restrict__ jobs,
     while (q.n) flush(q);
   }
   unit_end(C, us, total);
-}
-
-// Mode 1 (fp32, 8x8 tiles, L = 64): lane w of tile seg/2 owns its rows
-// 4w..4w+3, loaded/stored as 4 rows of 8 floats.
-__device__ __forceinline__ void load_tile(const Job& J, const float* __restrict__ p, bool ex,
-                                          float (&v)[32]) {
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      f4u t = ex ? *(const f4u*)(p + r * (uint64_t)J.nx + 4 * h) : f4u{0, 0, 0, 0};
-      v[8 * r + 4 * h] = t.x; v[8 * r + 4 * h + 1] = t.y;
-      v[8 * r + 4 * h + 2] = t.z; v[8 * r + 4 * h + 3] = t.w;
-    }
-  }
-}
-__device__ __forceinline__ void store_tile(const Job& J, float* __restrict__ p,
-                                           const float (&v)[32]) {
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      f4u t;
-      t.x = v[8 * r + 4 * h]; t.y = v[8 * r + 4 * h + 1];
-      t.z = v[8 * r + 4 * h + 2]; t.w = v[8 * r + 4 * h + 3];
-      *(f4u*)(p + r * (uint64_t)J.nx + 4 * h) = t;
-    }
-  }
 }
 
 // ------------------------------------------------------------ unit decode
@@ -4075,6 +4119,11 @@ hipError_t launch_unit(uint32_t op, const Job& J, const Ctl& C, uint32_t workers
                        hipStream_t st) {
   const bool fused = op == 2;
   const uint32_t grid = unit_grid(fused, cus, workers, J.nstrips);
+  if (J.mode == 1) {
+    hipLaunchKernelGGL(k_unit_tiles, dim3(grid), dim3((workers + 1) * 64),
+                       (size_t)workers * UnitEnc<false>::REGION * 4, st, J, C);
+    return hipGetLastError();
+  }
   switch ((J.dtype << 3) | J.log2L) {
     case 5: return fused ? launch_u<float, 32, true>(J, C, workers, grid, st)
                          : launch_u<float, 32, false>(J, C, workers, grid, st);

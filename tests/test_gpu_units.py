@@ -222,3 +222,22 @@ def test_tile_decode_at_unit_edges(gz, ctx, oracle, nx, rows):
         torch.cuda.synchronize()
         assert ctx.device_status() == 0
         assert y.cpu().numpy().tobytes() == oracle.decompress(s).tobytes()
+
+
+@pytest.mark.parametrize("select", [1, 2])
+@pytest.mark.parametrize("nx,rows", [(8, 8), (64, 32), (72, 40), (8, 264), (1024, 72), (2048, 360)])
+def test_tile_compress_at_unit_edges(gz, ctx, oracle, select, nx, rows):
+    """Units of 32 tiles: one tile, a whole unit, ragged rows of tiles, and more
+    than one round; payloads held and not."""
+    import torch
+    from paper_2308_05199_amd import selector
+    for kind in ("smooth", "dense", "raw", "mixed"):
+        say("tile units", nx, rows, select, kind)
+        x = field(kind, nx * rows, np.float32, nx * rows + select)
+        out = torch.zeros(gz.bound(x.size, gz.GZ_F32, 64), dtype=torch.uint8, device="cuda")
+        nb = torch.zeros(1, dtype=torch.int64, device="cuda")
+        selector.tile_compress(ctx, dev(x), nx, 1e-4, select, out, nb)
+        torch.cuda.synchronize()
+        want = oracle.compress(x, 1e-4, block_len=64, mode=1, nx=nx, select=select)
+        assert out[:int(nb.item())].cpu().numpy().tobytes() == want.tobytes()
+    assert ctx.device_status() == 0
