@@ -655,7 +655,7 @@ def main():
         "headline_1GiB": head,
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBPS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBPS,
-                     "kernel": "k_batch_encode_w<32, true> (per-wave fused decode-add-encode, "
+                     "kernel": "k_batch_fused_w<32> (per-wave fused decode-add-encode, "
                                "8 chunks per launch)",
                      "alg_bytes_per_launch": fused_alg,
                      "traffic": traffic},
