@@ -141,7 +141,7 @@ gz_status gz_ctx_status(gz_ctx* ctx, gz_stream_t stream, gz_status* device_statu
 gz_status gz_ctx_reset(gz_ctx* ctx, gz_stream_t stream);
 
 /* Bound of every wait between workgroups or waves of one launch (the
- * look-back of Sec. 3.3.4's offset scan, the per-wave encoder's rounds), in
+ * look-back of Sec. 3.3.4's offset scan, the unit kernels' rounds), in
  * microseconds of the device's constant-rate clock; default one second.  A
  * wait that expires sets GZ_ETIMEOUT in the device status (the stream being
  * written is then invalid) and its kernel finishes instead of waiting on.
@@ -333,9 +333,9 @@ gz_status gz_mlp_adam(gz_ctx* ctx, float* d_w, const float* d_grad, float* d_m,
  * gz_compress, except that the MLP selector (mode 1, select 0) is not
  * available (GZ_EINVAL).  The workspace is a device-resident array of
  * 263,424 bytes that the library holds on each device until the process
- * ends; it serves streams of at most 32768 strips (2^30 fp32 elements at the
- * default 1024 threads, 2^28 fp64 elements at 256) or, with threads 64,
- * 32768 rounds of 8 superblocks (also 2^30 fp32 elements); larger inputs
+ * ends; it serves streams of at most 32768 strips (2^30 fp32 elements at
+ * 1024 threads, 2^28 fp64 elements at 256; the same limits hold for the
+ * default path and for threads 64); larger inputs
  * return GZ_ENOSPC with nothing enqueued.  The call allocates nothing: its first
  * call on a device only looks up the array's address.  It enqueues the
  * compression and a one-wave kernel that writes the device status of the

@@ -8,6 +8,10 @@
 // look-back pass over agent-scope status words (a single read of the input,
 // a single write of the output), tagged with a launch epoch so they never
 // need clearing.  No MFMA: the path is bound by HBM, not by arithmetic.
+// Most of the encoding runs by units (2048 elements, a wave each, section
+// "unit encode") and most of the decoding by waves that need no scan; strips serve
+// the explicit thread counts, the tuner, decode-and-accumulate and fp32
+// scatter compression.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -231,73 +235,6 @@ __device__ __forceinline__ float bad_bound<float>(const Job& J) { return J.eblo;
 template <>
 __device__ __forceinline__ double bad_bound<double>(const Job& J) { return J.eb; }
 
-// ------------------------------------------------------------ load/store
-template <typename T>
-__device__ __forceinline__ void load_seg(const T* __restrict__ p, uint32_t vcnt, T (&v)[32]);
-template <>
-__device__ __forceinline__ void load_seg<float>(const float* __restrict__ p, uint32_t vcnt,
-                                                float (&v)[32]) {
-  if (vcnt == 32) {
-#pragma unroll
-    for (int k = 0; k < 32; k += 4) {
-      f4u t = *(const f4u*)(p + k);
-      v[k] = t.x; v[k + 1] = t.y; v[k + 2] = t.z; v[k + 3] = t.w;
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < 32; ++k) v[k] = (k < (int)vcnt) ? p[k] : 0.0f;
-  }
-}
-template <>
-__device__ __forceinline__ void load_seg<double>(const double* __restrict__ p, uint32_t vcnt,
-                                                 double (&v)[32]) {
-  if (vcnt == 32) {
-#pragma unroll
-    for (int k = 0; k < 32; k += 2) {
-      d2u t = *(const d2u*)(p + k);
-      v[k] = t.x; v[k + 1] = t.y;
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < 32; ++k) v[k] = (k < (int)vcnt) ? p[k] : 0.0;
-  }
-}
-
-template <typename T>
-__device__ __forceinline__ void store_seg(T* __restrict__ p, uint32_t vcnt, const T (&v)[32]);
-template <>
-__device__ __forceinline__ void store_seg<float>(float* __restrict__ p, uint32_t vcnt,
-                                                 const float (&v)[32]) {
-  if (vcnt == 32) {
-#pragma unroll
-    for (int k = 0; k < 32; k += 4) {
-      f4u t;
-      t.x = v[k]; t.y = v[k + 1]; t.z = v[k + 2]; t.w = v[k + 3];
-      *(f4u*)(p + k) = t;
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < 32; ++k)
-      if (k < (int)vcnt) p[k] = v[k];
-  }
-}
-template <>
-__device__ __forceinline__ void store_seg<double>(double* __restrict__ p, uint32_t vcnt,
-                                                  const double (&v)[32]) {
-  if (vcnt == 32) {
-#pragma unroll
-    for (int k = 0; k < 32; k += 2) {
-      d2u t;
-      t.x = v[k]; t.y = v[k + 1];
-      *(d2u*)(p + k) = t;
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < 32; ++k)
-      if (k < (int)vcnt) p[k] = v[k];
-  }
-}
-
 // bits of element i as u32 words (1 for float, 2 for double)
 __device__ __forceinline__ void raw_words(float v, uint32_t* dst) {
   dst[0] = __float_as_uint(v);
@@ -388,8 +325,8 @@ __device__ __forceinline__ void publish_agg(const Ctl& C, uint64_t gs, uint64_t 
 // exclusive prefix (dwords) of strip gs within its chain and publishes its
 // inclusive prefix.  One probe reads SUB x 64 predecessors (SUB independent
 // loads per lane); sub-windows resolved before a not-yet-published word are
-// added in before the probe is retried from there.  Strips probe 256 words;
-// the per-wave encoder, with eight times as many chain elements, probes 64
+// added in before the probe is retried from there.  Strips and units probe 256 words;
+// the per-wave fused kernel, with more and smaller chain elements, probes 64
 // (its status-word reads would otherwise rival its payload traffic).
 constexpr int LB_SUB = 4;
 
