@@ -18,6 +18,7 @@
 
 #include "gz_common.h"
 #include "gz_kernels.h"
+#include "gz_ring.h"
 
 namespace gzk {
 
@@ -3041,25 +3042,24 @@ __device__ __forceinline__ void unit_analyse(const Job& J, uint64_t u, uint32_t 
 // delay every later round's prefix (taken at the first publication: 852 us per
 // GiB).  The worker that publishes last also publishes the round's sum; the
 // scheduler then runs the look-back and puts the round's prefix into the entry.
-// Round k + 1 is opened once every worker has published round k - 1; a worker
-// that has holds nothing older than round k - 3, whose entry is reused four
-// rounds later still.
+// Round k + 1 is opened once every worker has published round k - 1 and the
+// scheduler is done with round k + 1 - RING (ring_need).
 // Deadlock freedom: a worker waits for the offset of a round only after
 // publishing it, and prefixes depend on earlier tickets only; tickets are
 // handed only to running workgroups, nothing assumes that the grid's
-// workgroups are resident together, and every wait is bounded.
+// workgroups are resident together, and every wait is bounded.  Opening round
+// k + 1 with its ticket in hand waits for the scheduler's look-back of an
+// earlier round, on earlier tickets only.
 // Every workgroup takes exactly one ticket past the end, so the last of them
 // (total + workgroups - 1) ends the launch's use of the counter: its taker
 // resets counter and epoch for the next launch.
-constexpr uint32_t RING = 8;
-
 struct URound {
   unsigned long long prefix;  // exclusive prefix of the round (dwords)
   unsigned long long pj;      // the chain's prefix at the job's first round
   uint32_t ticket;
   uint32_t ready;   // 1 + round number once ticket (and the reset) is done
   uint32_t cnt;     // sizes written
-  uint32_t pready;  // 1 + round number once prefix is set
+  uint32_t pready;  // 1 + round number once prefix is set: the scheduler's mark
   uint32_t bad;     // 1: the prefix is not to be used (a wait expired)
   uint32_t agg;     // 1 + round number once its aggregate's store has completed
   uint32_t size[16];
@@ -3262,9 +3262,10 @@ __device__ __forceinline__ void unit_code(const Job& J, uint32_t job, uint64_t g
       lds_store_rel(&e.agg, k + 1);
     }
   }
-  // the next round's entry is free once every worker has published round k - 1
-  auto open = [&](uint32_t t) {
-    const bool free = k == 0 || lds_wait_ge(C, &us.rs[(k - 1) % RING].cnt, W);
+  auto open = [&](uint32_t t) {  // once the next round's entry is free
+    const RingNeed n = ring_need(k + 1);
+    const bool free = (!n.published || lds_wait_ge(C, &us.rs[n.pub].cnt, W)) &&
+                      (!n.scheduled || lds_wait_ge(C, &us.rs[n.sched].pready, n.mark));
     if (lane == 0) {
       if (free) unit_open(C, us, k + 1, t, total);
       else unit_taken(C, us, t, total);

@@ -241,3 +241,40 @@ def test_tile_compress_at_unit_edges(gz, ctx, oracle, select, nx, rows):
         want = oracle.compress(x, 1e-4, block_len=64, mode=1, nx=nx, select=select)
         assert out[:int(nb.item())].cpu().numpy().tobytes() == want.tobytes()
     assert ctx.device_status() == 0
+
+
+@pytest.mark.parametrize("kind", ["smooth", "dense"])
+def test_good_jobs_among_malformed_ones(gz, ctx, oracle, kind):
+    """Long runs of malformed one-unit jobs, whose workers wait for no offset,
+    between good jobs of one and of several rounds: a run is longer than the
+    rounds a workgroup keeps, and the good jobs' streams are whole."""
+    import torch
+    ns = [1500] * 4000
+    for k in range(0, 4000, 397):
+        ns[k] = 1500 + 11 * UNIT * (k // 397 % 3)
+    good = [k % 397 == 0 or k % 131 == 7 or k == 3999 for k in range(4000)]
+    xs = {n: (field(kind, n, np.float32, n), field(kind, n, np.float32, n + 1)) for n in set(ns)}
+    s = {n: oracle.compress(x, 1e-4) for n, (x, _) in xs.items()}
+    want = {n: oracle.fused_step(s[n], xs[n][1], 1e-4).tobytes() for n in xs}
+    bad = s[1500].copy()
+    bad[0] ^= 0x15  # the magic word
+    S, Y, B = {n: dev(a) for n, a in s.items()}, {n: dev(y) for n, (_, y) in xs.items()}, dev(bad)
+    sizes = torch.zeros(len(ns), dtype=torch.int64, device="cuda")
+    items = []
+    for k, n in enumerate(ns):
+        cap = gz.bound(n)
+        items.append({"in": S[n] if good[k] else B, "in_bytes": S[n].numel() if good[k] else bad.size,
+                      "local": Y[n], "out": torch.zeros(cap, dtype=torch.uint8, device="cuda"),
+                      "out_bytes": sizes[k:k + 1], "n": n, "out_cap": cap, "eb": 1e-4,
+                      "dtype": gz.GZ_F32})
+    say("good among malformed", kind, sum(good), "of", len(ns))
+    for _ in range(2):
+        sizes.zero_()
+        ctx.batch(gz.GZ_OP_FUSED, ctx.requests(items))
+        assert ctx.device_status() == gz.GZ_ECORRUPT
+        got = sizes.cpu().numpy()
+        for k, n in enumerate(ns):
+            if good[k]:
+                assert items[k]["out"][:int(got[k])].cpu().numpy().tobytes() == want[n], k
+            else:
+                assert got[k] == 0, k
