@@ -2957,15 +2957,18 @@ __device__ __forceinline__ void unit_analyse(const Job& J, uint64_t u, uint32_t 
   } else if constexpr (FUSED) {
     const uint8_t* in = (const uint8_t*)J.in;
     const uint64_t sb = u >> 1;
+    // an empty stream (n = 0) is its header: it has no table entry or header
+    // byte to read, and what lies behind it in the buffer is not looked at
+    const bool some = FULL || J.NS != 0;
     uint32_t raw[3];
     const uint32_t hdr = wave_header_load(J, in);
-    wave_blocks_load<L, true>(J, in, sb, raw);  // table words with the header's
+    if (some) wave_blocks_load<L, true>(J, in, sb, raw);  // table words with the header's
     u4u lr[8];  // the unit's addend, in flight until the add
     unit_rows_load<32, FULL>((const uint32_t*)(J.local + e0), hval, lr);
     uint64_t paydw = 0;
     good = wave_header_eval<float>(J, hdr, paydw, fs.t);
-    UnitIn ui;
-    if (good)
+    UnitIn ui = {0u, 0u, K_ZERO, 0u, 0u, false};
+    if (good && some)
       good = unit_in_eval<float, L>(J, sb, (uint32_t)(u & 1), paydw,
                              (uint32_t)min((uint64_t)SUPER, J.n - sb * SUPER), raw, ui);
     fs.pay = (const uint32_t*)(in + J.pay_off);

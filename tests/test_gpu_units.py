@@ -278,3 +278,52 @@ def test_good_jobs_among_malformed_ones(gz, ctx, oracle, kind):
                 assert items[k]["out"][:int(got[k])].cpu().numpy().tobytes() == want[n], k
             else:
                 assert got[k] == 0, k
+
+
+@pytest.mark.parametrize("L", [32, 64, 128])
+def test_empty_fused_step_ignores_what_follows(gz, ctx, oracle, L):
+    """An empty stream (n = 0) at the start of a larger buffer with other bytes
+    behind it, stated whole as readable: single calls on every kernel, a batch
+    and a plan with other jobs beside it."""
+    import torch
+    s = oracle.compress(np.zeros(0, np.float32), 1e-4, block_len=L)
+    want = oracle.fused_step(s, np.zeros(0, np.float32), 2e-4, block_len=L).tobytes()
+    buf = np.full(400, 0xA7, np.uint8)
+    buf[:s.size] = s
+    x, y = field("smooth", 5000, np.float32, 1), field("smooth", 5000, np.float32, 2)
+    t = oracle.compress(x, 1e-4, block_len=L)
+    want_t = oracle.fused_step(t, y, 2e-4, block_len=L).tobytes()
+    B, T, Y, none = dev(buf), dev(t), dev(y), torch.zeros(0, device="cuda")
+    for in_bytes in (64, 67, 68, 72, 400):
+        for threads in (0, 64, 128, 256, 1024):
+            say("empty fused", L, in_bytes, threads)
+            out, nb = ctx.fused_reduce_step(B, none, 2e-4, block_len=L, in_bytes=in_bytes,
+                                            threads=threads)
+            assert ctx.device_status() == 0, (in_bytes, threads)
+            assert out[:int(nb.item())].cpu().numpy().tobytes() == want, (in_bytes, threads)
+
+    def items():
+        r = []
+        for n, a, ib, loc in ((0, B, 400, none), (5000, T, t.size, Y), (0, B, 400, none)):
+            cap = gz.bound(n, gz.GZ_F32, L)
+            r.append({"in": a, "in_bytes": ib, "local": loc, "n": n, "out_cap": cap, "eb": 2e-4,
+                      "out": torch.zeros(cap, dtype=torch.uint8, device="cuda"),
+                      "out_bytes": torch.zeros(1, dtype=torch.int64, device="cuda"),
+                      "dtype": gz.GZ_F32, "block_len": L})
+        return r
+
+    for how in ("batch", "plan"):
+        for sel, threads in ((slice(0, 3), 0), (slice(0, 1), 0), (slice(0, 3), 256)):
+            it = items()[sel]
+            say("empty fused", how, L, len(it), threads)
+            if how == "batch":
+                ctx.batch(gz.GZ_OP_FUSED, ctx.requests(it), threads=threads)
+            else:
+                plan = ctx.plan(gz.GZ_OP_FUSED, ctx.requests(it), threads=threads)
+                plan.launch()
+            assert ctx.device_status() == 0
+            for k, q in enumerate(it):
+                got = q["out"][:int(q["out_bytes"].item())].cpu().numpy().tobytes()
+                assert got == (want_t if q["n"] else want), (how, k)
+            if how == "plan":
+                plan.close()
