@@ -110,6 +110,7 @@ struct gz_plan {
   uint32_t tpb = 0, grid = 0;
   bool wide = false;
   uint32_t unit_w = 0;  // unit encoding: workers per workgroup (total = rounds); 0: not used
+  uint32_t longest = 0; // unit encoding: rounds of the longest job
   uint32_t wave_log2L = 0;  // per-wave fused batch: its block length (total = rounds); 0: not used
   bool wave_dec = false;  // per-wave decoding kernels (total = superblocks)
   bool has_map = false;   // wave_dec: d_map lists (job, superblock) pairs
@@ -460,6 +461,13 @@ hipError_t launch_decode(uint32_t op, const Job* d_jobs, const uint32_t* d_map, 
     return gzk::launch_accum_wave_batch(d_jobs, d_map, njobs, total, cus, c->ctl(), st);
   if (jw) return gzk::launch_decode_shares(d_jobs, d_map, jw, cus, c->ctl(), st);
   return gzk::launch_batch_unit_decode(d_jobs, d_map, njobs, total, cus, c->ctl(), st);
+}
+
+// Strips or rounds of the longest job.
+uint32_t longest_job(const std::vector<Job>& jobs) {
+  uint32_t m = 0;
+  for (const Job& J : jobs) m = std::max(m, J.nstrips);
+  return m;
 }
 
 // Builds the jobs of a request batch; fills the strip map.
@@ -993,7 +1001,8 @@ gz_status gz_scatter_compress(gz_ctx* c, const void* d_root, gz_dtype dtype,
   if (W)
     return hip_status(gzk::launch_batch_unit(0, c->d_jobs, c->d_map, 0,
                                              (uint32_t)(map.size() / 2), dtype == GZ_F64,
-                                             c->ctl(), W, (uint32_t)c->cus, st));
+                                             c->ctl(), W, (uint32_t)(map.size() / 2),
+                                             (uint32_t)c->cus, st));
   const uint32_t grid = pick_grid(c, 0, dtype, L, tpb, strip, p);
   return hip_status(gzk::launch_batch(0, c->d_jobs, c->d_map, 0, (uint32_t)strip, c->ctl(), tpb,
                                       grid, dtype == GZ_F64, st));
@@ -1118,7 +1127,8 @@ gz_status batch_impl(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t nre
   if (W)
     return hip_status(gzk::launch_batch_unit((uint32_t)op, c->d_jobs, c->d_map,
                                              uniform_jobs(jobs), (uint32_t)(map.size() / 2),
-                                             wide, c->ctl(), W, (uint32_t)c->cus, st));
+                                             wide, c->ctl(), W, longest_job(jobs),
+                                             (uint32_t)c->cus, st));
   const uint64_t total = map.size() / 2;
   const uint32_t g = batch_grid(c, op, wide, tpb, total, p);
   return hip_status(gzk::launch_batch((uint32_t)op, c->d_jobs, c->d_map, uniform_jobs(jobs),
@@ -1196,6 +1206,7 @@ gz_status gz_plan_create(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t
   pl->wide = wide;
   pl->grid = batch_grid(c, op, wide, tpb, pl->total, p);
   pl->unit_w = unit_w;
+  pl->longest = longest_job(jobs);
   if (fw) {
     pl->wave_log2L = jobs[0].log2L;
     pl->njobs = (uint32_t)jobs.size();
@@ -1228,7 +1239,7 @@ gz_status gz_plan_launch(gz_plan* pl, gz_stream_t stream) {
                                              (hipStream_t)stream));
   if (pl->unit_w)
     return hip_status(gzk::launch_batch_unit(pl->op, pl->d_jobs, pl->d_map, pl->njobs, pl->total,
-                                             pl->wide, pl->ctx->ctl(), pl->unit_w,
+                                             pl->wide, pl->ctx->ctl(), pl->unit_w, pl->longest,
                                              (uint32_t)pl->ctx->cus, (hipStream_t)stream));
   if (pl->wave_dec)
     return hip_status(launch_decode(pl->op, pl->d_jobs, pl->has_map ? pl->d_map : nullptr,

@@ -51,10 +51,11 @@ inline uint64_t wave_rounds(uint64_t NS) { return (NS + WAVE_ROUND - 1) / WAVE_R
 hipError_t launch_unit(uint32_t op, const Job& J, const Ctl& C, uint32_t workers, uint32_t cus,
                        hipStream_t st);
 // total rounds of njobs jobs of equal round counts (njobs > 0: round t is
-// round t / njobs of job t % njobs) or of the (job, round) pairs of d_map.
+// round t / njobs of job t % njobs) or of the (job, round) pairs of d_map;
+// longest: rounds of the longest chain.
 hipError_t launch_batch_unit(uint32_t op, const Job* d_jobs, const uint32_t* d_map,
                              uint32_t njobs, uint32_t total, bool wide, const Ctl& C,
-                             uint32_t workers, uint32_t cus, hipStream_t st);
+                             uint32_t workers, uint32_t longest, uint32_t cus, hipStream_t st);
 constexpr uint32_t UNIT_WORKERS = 15;        // most workers of a workgroup: compression
 constexpr uint32_t UNIT_WORKERS_FUSED = 11;  // the fused step
 constexpr uint64_t UNIT_ELEMS = 2048;

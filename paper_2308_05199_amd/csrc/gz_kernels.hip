@@ -2868,9 +2868,10 @@ struct UnitEnc {
   // sums); compression stages half rows of 16 at a time
   static constexpr uint32_t STR = FUSED ? 36 : 20;
   static constexpr uint32_t XW = SEGS * STR;            // staging (dwords)
-  static constexpr uint32_t QW = FUSED ? 1344 : 1392;   // payloads held
-  static constexpr uint32_t HELD = FUSED ? QW : QW / 2; // largest payload held
   static constexpr uint32_t HBW = SEGS / 4;             // header bytes
+  // payloads held, each behind its header bytes
+  static constexpr uint32_t QW = FUSED ? 1344 : 1392;
+  static constexpr uint32_t HELD = (FUSED ? QW : QW / 2) - HBW;  // largest payload held
   static constexpr uint32_t PACKW = FUSED ? XW : XW + QW;  // payloads not held
   static constexpr uint32_t REGION = XW + QW + HBW;     // per worker
   static constexpr uint32_t MAXW = FUSED ? UNIT_WORKERS_FUSED : UNIT_WORKERS;
@@ -3039,12 +3040,20 @@ __device__ __forceinline__ void unit_analyse(const Job& J, uint64_t u, uint32_t 
 
 // ---- rounds.  A workgroup's state: a ring of RING rounds in LDS and the
 // launch's epoch.  Round k of the workgroup (k = 0, 1, ...) sits in entry
-// k % RING.  The worker that publishes first in round k takes the ticket of
-// round k + 1, after it has written what it held (in flight while it packs),
-// and opens that round's entry: a ticket held during a wait for a prefix would
-// delay every later round's prefix (taken at the first publication: 852 us per
-// GiB).  The worker that publishes last also publishes the round's sum; the
-// scheduler then runs the look-back and puts the round's prefix into the entry.
+// k % RING.  From the moment that the ticket of round k + 1 is taken, every later
+// round's prefix waits for round k + 1's sizes; so it is taken when no worker of
+// the workgroup has a wait for a prefix before its next size: by the worker that
+// publishes last in round k (in flight while it packs), if all sizes are small
+// enough to be held, else by the scheduler once it has the round's prefix.  Taken
+// at the first publication, tickets were held through such waits where large and
+// small payloads alternate, and each of them delayed the whole chain (2^28 fp32
+// values, half of the units large: 6058 us, now 447; a thousandth large: 1095,
+// now 394; 2^27 of ratio 2.8: 1815, now 233; all small or all large: the same).
+// Launches that give no workgroup a second round, and batches of short chains
+// (unit_early), take the ticket at the first publication all the same, unless
+// that payload is large.  Whoever takes it opens the round's entry.  The worker
+// that publishes last also publishes the round's sum; the scheduler then runs the
+// look-back and puts the round's prefix into the entry.
 // Round k + 1 is opened once every worker has published round k - 1 and the
 // scheduler is done with round k + 1 - RING (ring_need).
 // Deadlock freedom: a worker waits for the offset of a round only after
@@ -3056,19 +3065,26 @@ __device__ __forceinline__ void unit_analyse(const Job& J, uint64_t u, uint32_t 
 // Every workgroup takes exactly one ticket past the end, so the last of them
 // (total + workgroups - 1) ends the launch's use of the counter: its taker
 // resets counter and epoch for the next launch.
+constexpr uint32_t UNIT_PUB = 256;
+// When a round's first worker takes the next ticket: never, until a workgroup
+// has had a payload too large to be held, always.
+enum : uint32_t { EARLY_NO = 0, EARLY_SMALL = 1, EARLY_YES = 2 };
+
 struct URound {
   unsigned long long prefix;  // exclusive prefix of the round (dwords)
   unsigned long long pj;      // the chain's prefix at the job's first round
   uint32_t ticket;
   uint32_t ready;   // 1 + round number once ticket (and the reset) is done
-  uint32_t cnt;     // sizes written
+  uint32_t cnt;     // UNIT_PUB for each size written, and 1 for each of them too large to be held
   uint32_t pready;  // 1 + round number once prefix is set: the scheduler's mark
   uint32_t bad;     // 1: the prefix is not to be used (a wait expired)
+  uint32_t claim;   // 1 once a worker has claimed the next round's ticket
   uint32_t agg;     // 1 + round number once its aggregate's store has completed
   uint32_t size[16];
 };
 struct USched {
   uint32_t epoch;
+  uint32_t early; // batches: EARLY_*
   uint32_t over;  // 1 once this workgroup has taken a ticket past the end
   URound rs[RING];
 };
@@ -3090,6 +3106,7 @@ __device__ __forceinline__ void unit_open(const Ctl& C, USched& us, uint32_t k, 
   URound& e = us.rs[k % RING];
   e.cnt = 0;
   e.bad = 0;
+  e.claim = 0;
   e.ticket = t;
   lds_store_rel(&e.ready, k + 1);
 }
@@ -3111,6 +3128,13 @@ __device__ __forceinline__ void unit_end(const Ctl& C, USched& us, uint32_t tota
     while (!us.over) unit_taken(C, us, atomicAdd(&C.ctrl->ticket, 1u), total);  // after a timeout
 }
 
+// True for one of those who ask for the next ticket in round entry e.
+__device__ __forceinline__ bool unit_claim(URound& e) {
+  uint32_t won = 0;
+  if (__lane_id() == 0) won = atomicCAS(&e.claim, 0u, 1u) == 0u ? 1u : 0u;
+  return read_lane(won, 0) != 0;
+}
+
 // A round's place in its chain.
 struct UChain {
   uint64_t gs, chain0;  // look-back words of the round and the chain's start
@@ -3122,10 +3146,11 @@ struct UChain {
 // The scheduler's step for round k: sizes, look-back, prefix.  False once a
 // wait expired.
 __device__ __forceinline__ bool unit_sched(const Ctl& C, USched& us, uint32_t k, uint32_t W,
-                                           const UChain& ch) {
+                                           uint32_t total, const UChain& ch) {
   URound& e = us.rs[k % RING];
   const uint32_t lane = __lane_id(), ep = us.epoch;
-  if (!lds_wait_ge(C, &e.cnt, W)) return false;
+  if (!lds_wait_ge(C, &e.cnt, W * UNIT_PUB)) return false;
+  const uint32_t cnt = __builtin_amdgcn_readfirstlane(e.cnt);
   const uint64_t agg = wave_sum64(lane < W ? e.size[lane] : 0u);
   bool to = false;
   const uint64_t prefix = lookback<LB_SUB, false>(C, ch.gs, ch.chain0, ep, agg, to);
@@ -3145,17 +3170,22 @@ __device__ __forceinline__ bool unit_sched(const Ctl& C, USched& us, uint32_t k,
     e.pj = pj;
     lds_store_rel(&e.pready, k + 1);
   }
+  // a round with a payload too large to be held: the next ticket, unless its
+  // first worker has it
+  const bool taker = (cnt % UNIT_PUB) != 0 && unit_claim(e);
+  uint32_t tk = 0;
+  if (taker && lane == 0) tk = atomicAdd(&C.ctrl->ticket, 1u);
   // the inclusive prefix, once the aggregate cannot land after it (the head
   // of a chain publishes its inclusive prefix as its aggregate)
   if (ch.gs != ch.chain0 && !to && lds_wait_ge(C, &e.agg, k + 1) && lane == 0)
     st_agent(C.status + ch.gs, sw_pack(2, ep, prefix + agg));
+  if (taker && lane == 0) unit_open(C, us, k + 1, tk, total);
   return true;
 }
 
-// A coded unit whose payload is held (size dwords at Q + at) until its offset
-// is known.
+// A coded unit that is held until its offset is known: its header bytes at Q +
+// at, then size dwords of payload.
 struct UnitHeld {
-  uint32_t hb;                  // header-byte word `lane`
   uint32_t at, size, k, job;    // k: round of the workgroup
   uint64_t u;                   // unit of the job
 };
@@ -3209,10 +3239,12 @@ __device__ __forceinline__ void unit_flush(const Job& J, const Ctl& C, USched& u
   --q.n;
   uint64_t off, pj;
   if (!unit_offset(C, us, h.k, wid, off, pj)) return;
-  uint32_t* dst = J.log2L == 5   ? unit_meta<32>(J, h.u, off, pj, h.size, h.hb)
-                  : J.log2L == 6 ? unit_meta<64>(J, h.u, off, pj, h.size, h.hb)
-                                 : unit_meta<128>(J, h.u, off, pj, h.size, h.hb);
-  for (uint32_t i = __lane_id(); i < h.size; i += 64) dst[i] = Q[h.at + i];
+  const uint32_t hb = Q[h.at + (__lane_id() & 15)];
+  const uint32_t* pay = Q + h.at + 16;
+  uint32_t* dst = J.log2L == 5   ? unit_meta<32>(J, h.u, off, pj, h.size, hb)
+                  : J.log2L == 6 ? unit_meta<64>(J, h.u, off, pj, h.size, hb)
+                                 : unit_meta<128>(J, h.u, off, pj, h.size, hb);
+  for (uint32_t i = __lane_id(); i < h.size; i += 64) dst[i] = pay[i];
 }
 
 // One unit: round k of the workgroup is round r of job J (index job); worker
@@ -3221,7 +3253,7 @@ __device__ __forceinline__ void unit_flush(const Job& J, const Ctl& C, USched& u
 template <typename T, int L, bool FUSED, bool FULL, int MODE, class Flush>
 __device__ __forceinline__ void unit_code(const Job& J, uint32_t job, uint64_t gs, uint64_t u,
                                           bool live, uint32_t k, uint32_t wid, uint32_t W,
-                                          uint32_t total, USched& us, const Ctl& C,
+                                          uint32_t total, bool batch, USched& us, const Ctl& C,
                                           uint32_t* X, UnitQueue& q, const Flush& flush,
                                           const uint32_t* wts) {
   using U = UnitEnc<FUSED>;
@@ -3251,13 +3283,29 @@ __device__ __forceinline__ void unit_code(const Job& J, uint32_t job, uint64_t g
   uint32_t c = 0;
   if (lane == 0) {
     e.size[wid] = size;
-    c = 1 + __hip_atomic_fetch_add(&e.cnt, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const uint32_t add = UNIT_PUB + (size > U::HELD ? 1u : 0u);
+    c = add + __hip_atomic_fetch_add(&e.cnt, add, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
   // the round's last size: publish their sum at once (the scheduler may still
   // be in the look-back of the round before, which must not hold it up)
   c = read_lane(c, 0);
-  const bool held = size <= U::HELD, first = c == 1;
-  if (c == W) {
+  const bool held = size <= U::HELD;
+  // (workers of a round may see us.early before and after a change: if both the
+  // first and the last ask, the claim settles it; if neither does, the change
+  // came from a payload of this round, and the scheduler asks)
+  const bool early = total <= gridDim.x ||
+                     (batch && __builtin_amdgcn_readfirstlane(us.early) != EARLY_NO);
+  if (batch && !held && lane == 0 && us.early == EARLY_SMALL) us.early = EARLY_NO;
+  auto open = [&](uint32_t t) {  // once the next round's entry is free
+    const RingNeed n = ring_need(k + 1);
+    const bool free = (!n.published || lds_wait_ge(C, &us.rs[n.pub].cnt, W * UNIT_PUB)) &&
+                      (!n.scheduled || lds_wait_ge(C, &us.rs[n.sched].pready, n.mark));
+    if (lane == 0) {
+      if (free) unit_open(C, us, k + 1, t, total);
+      else unit_taken(C, us, t, total);
+    }
+  };
+  if (c / UNIT_PUB == W) {
     const uint64_t agg = wave_sum64(lane < W ? e.size[lane] : 0u);
     if (lane == 0) {
       publish_agg(C, gs, J.chain0, us.epoch, agg);
@@ -3265,46 +3313,42 @@ __device__ __forceinline__ void unit_code(const Job& J, uint32_t job, uint64_t g
       lds_store_rel(&e.agg, k + 1);
     }
   }
-  auto open = [&](uint32_t t) {  // once the next round's entry is free
-    const RingNeed n = ring_need(k + 1);
-    const bool free = (!n.published || lds_wait_ge(C, &us.rs[n.pub].cnt, W)) &&
-                      (!n.scheduled || lds_wait_ge(C, &us.rs[n.sched].pready, n.mark));
-    if (lane == 0) {
-      if (free) unit_open(C, us, k + 1, t, total);
-      else unit_taken(C, us, t, total);
-    }
-  };
-  // room for this unit's payload: beside the newest one held, or where the
-  // oldest ones were.  Units of two rounds ago and older are written whatever
-  // the room (a worker may be past the end of many short jobs in a row, and
-  // their rounds' entries are reused)
+  // the next ticket is this worker's to take: the first one's (early) or the
+  // last one's, while no size so far is too large to be held
+  const bool taker = c == (early ? UNIT_PUB : W * UNIT_PUB) && unit_claim(e);
+  // room for this unit's payload: held ones lie at the two ends of Q, so that
+  // two fit whenever their sizes' sum does (laid one behind the other, a third
+  // often fitted neither before nor behind the second, which then had to be
+  // waited for: 2^27 fp32 values of ratio 3.6 458 us, now 212).  Units of two
+  // rounds ago and older are written whatever the room (a worker may be past the
+  // end of many short jobs in a row, and their rounds' entries are reused)
   uint32_t at = 0;
   if (!held) {
     while (q.n) flush(q);
   } else {
     while (q.n && (q.n == 2 || q.h0.k + 1 < k)) flush(q);
     if (q.n) {
-      const uint32_t end = q.h0.at + q.h0.size;
-      if (end + size <= U::QW) at = end;
-      else if (size > q.h0.at) flush(q);
+      if (q.h0.size + size + 2 * U::HBW <= U::QW) at = q.h0.at ? 0u : U::QW - U::HBW - size;
+      else flush(q);
     }
   }
   uint32_t tk = 0;
-  if (first && held) {
+  if (taker) {
     if (lane == 0) tk = atomicAdd(&C.ctrl->ticket, 1u);  // in flight while packing
     if (!live) open(tk);
   }
   if (!live) return;
   if (!good && lane == 0) atomicOr(&C.ctrl->err, ERRF_CORRUPT);
-  if (w == 0)
-    ((uint8_t*)HB)[lane / LPB] = (uint8_t)(lc.exists ? ((lc.kind << 5) | lc.F) : 0u);
   wave_lds_sync();  // every row of X is read before the payload goes there
+  if (w == 0)
+    ((uint8_t*)(held ? Q + at : HB))[lane / LPB] =
+        (uint8_t)(lc.exists ? ((lc.kind << 5) | lc.F) : 0u);
   if (held) {
-    wave_pack<T, L, FUSED, FULL, MODE>(J, seg, w, vcnt, lc, fs, Q + at + boff);
-    if (first) open(tk);
+    wave_pack<T, L, FUSED, FULL, MODE>(J, seg, w, vcnt, lc, fs, Q + at + U::HBW + boff);
+    if (taker) open(tk);
     wave_lds_sync();  // payload and header bytes are complete
     if (good) {
-      const UnitHeld h = {HB[lane & (U::HBW - 1)], at, size, k, job, u};
+      const UnitHeld h = {at, size, k, job, u};
       if (q.n) q.h1 = h;  // (not an indexed array: that would live in memory)
       else q.h0 = h;
       ++q.n;
@@ -3319,10 +3363,6 @@ __device__ __forceinline__ void unit_code(const Job& J, uint32_t job, uint64_t g
   wave_lds_sync();
   uint64_t off, pj;
   const bool known = unit_offset(C, us, k, wid, off, pj);
-  if (first) {  // a ticket taken before the wait would be held as long as it
-    if (lane == 0) tk = atomicAdd(&C.ctrl->ticket, 1u);
-    open(tk);
-  }
   if (!known || !good) return;
   uint32_t* dst = unit_meta<L>(J, u, off, pj, size, HB[lane & (U::HBW - 1)]);
   if (!two) {
@@ -3342,7 +3382,7 @@ __device__ __forceinline__ void unit_code(const Job& J, uint32_t job, uint64_t g
 
 template <typename T, int L, bool FUSED, int MODE = 0, class Flush>
 __device__ __forceinline__ void unit_one(const Job& J, uint32_t job, uint64_t r, uint32_t k,
-                                         uint32_t wid, uint32_t W, uint32_t total, USched& us,
+                                         uint32_t wid, uint32_t W, uint32_t total, bool early, USched& us,
                                          const Ctl& C, uint32_t* X, UnitQueue& q,
                                          const Flush& flush,
                                          const uint32_t* wts = nullptr) {
@@ -3350,9 +3390,9 @@ __device__ __forceinline__ void unit_one(const Job& J, uint32_t job, uint64_t r,
   // an empty stream is one unit of no values
   const bool live = u == 0 || u * UNIT_ELEMS < J.n;
   if ((u + 1) * UNIT_ELEMS <= J.n)
-    unit_code<T, L, FUSED, true, MODE>(J, job, J.strip0 + r, u, live, k, wid, W, total, us, C, X, q, flush, wts);
+    unit_code<T, L, FUSED, true, MODE>(J, job, J.strip0 + r, u, live, k, wid, W, total, early, us, C, X, q, flush, wts);
   else
-    unit_code<T, L, FUSED, false, MODE>(J, job, J.strip0 + r, u, live, k, wid, W, total, us, C, X, q, flush, wts);
+    unit_code<T, L, FUSED, false, MODE>(J, job, J.strip0 + r, u, live, k, wid, W, total, early, us, C, X, q, flush, wts);
 }
 
 // Registers for four waves per SIMD (the fused step: three), as the LDS allows.
@@ -3373,7 +3413,7 @@ __global__ GZ_UNIT_ATTR(FUSED) void k_unit(Job J, Ctl C) {
       if (!lds_wait_ge(C, &us.rs[k % RING].ready, k + 1)) break;
       const uint32_t t = __builtin_amdgcn_readfirstlane(us.rs[k % RING].ticket);
       if (t >= total) break;
-      if (!unit_sched(C, us, k, W, UChain{t, 0, t, 0, false})) break;
+      if (!unit_sched(C, us, k, W, total, UChain{t, 0, t, 0, false})) break;
     }
   } else {
     uint32_t* X = g_stage + wid * UnitEnc<FUSED>::REGION;
@@ -3384,7 +3424,7 @@ __global__ GZ_UNIT_ATTR(FUSED) void k_unit(Job J, Ctl C) {
       if (!lds_wait_ge(C, &us.rs[k % RING].ready, k + 1)) break;
       const uint32_t t = __builtin_amdgcn_readfirstlane(us.rs[k % RING].ticket);
       if (t >= total) break;
-      unit_one<T, L, FUSED>(J, 0, t, k, wid, W, total, us, C, X, q, flush);
+      unit_one<T, L, FUSED>(J, 0, t, k, wid, W, total, false, us, C, X, q, flush);
     }
     while (q.n) flush(q);
   }
@@ -3409,7 +3449,7 @@ __global__ GZ_UNIT_ATTR(false) void k_unit_tiles(Job J, Ctl C) {
       if (!lds_wait_ge(C, &us.rs[k % RING].ready, k + 1)) break;
       const uint32_t t = __builtin_amdgcn_readfirstlane(us.rs[k % RING].ticket);
       if (t >= total) break;
-      if (!unit_sched(C, us, k, W, UChain{t, 0, t, 0, false})) break;
+      if (!unit_sched(C, us, k, W, total, UChain{t, 0, t, 0, false})) break;
     }
   } else {
     uint32_t* X = g_stage + wid * UnitEnc<false>::REGION;
@@ -3420,7 +3460,7 @@ __global__ GZ_UNIT_ATTR(false) void k_unit_tiles(Job J, Ctl C) {
       if (!lds_wait_ge(C, &us.rs[k % RING].ready, k + 1)) break;
       const uint32_t t = __builtin_amdgcn_readfirstlane(us.rs[k % RING].ticket);
       if (t >= total) break;
-      unit_one<float, 64, false, 1>(J, 0, t, k, wid, W, total, us, C, X, q, flush, wts);
+      unit_one<float, 64, false, 1>(J, 0, t, k, wid, W, total, false, us, C, X, q, flush, wts);
     }
     while (q.n) flush(q);
   }
@@ -3432,11 +3472,13 @@ __global__ GZ_UNIT_ATTR(false) void k_unit_tiles(Job J, Ctl C) {
 template <uint32_t OP, bool WIDE>
 __global__ GZ_UNIT_ATTR(OP == 2) void k_batch_unit(const Job* __restrict__ jobs,
                                                    const uint32_t* __restrict__ map,
-                                                   uint32_t njobs, uint32_t total, Ctl C) {
+                                                   uint32_t njobs, uint32_t total,
+                                                   uint32_t early, Ctl C) {
   constexpr bool FUSED = OP == 2;
   __shared__ USched us;
   const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t W = (blockDim.x >> 6) - 1;
+  if (threadIdx.x == 0) us.early = early;
   unit_begin(C, us, total);
   if (wid == W) {
     __builtin_amdgcn_s_setprio(3);
@@ -3447,7 +3489,7 @@ __global__ GZ_UNIT_ATTR(OP == 2) void k_batch_unit(const Job* __restrict__ jobs,
       const uint32_t j = njobs ? t % njobs : map[2 * (uint64_t)t];
       const uint64_t r = njobs ? t / njobs : map[2 * (uint64_t)t + 1];
       const Job& J = jobs[j];
-      if (!unit_sched(C, us, k, W,
+      if (!unit_sched(C, us, k, W, total,
                       UChain{J.strip0 + r, J.chain0, r, j, J.chain0 != J.strip0}))
         break;
     }
@@ -3466,12 +3508,12 @@ __global__ GZ_UNIT_ATTR(OP == 2) void k_batch_unit(const Job* __restrict__ jobs,
       const uint64_t r = njobs ? t / njobs : map[2 * (uint64_t)t + 1];
       const Job J = jobs[j];
       switch ((J.dtype << 3) | J.log2L) {
-        case 5: unit_one<float, 32, FUSED>(J, j, r, k, wid, W, total, us, C, X, q, flush); break;
-        case 6: unit_one<float, 64, FUSED>(J, j, r, k, wid, W, total, us, C, X, q, flush); break;
-        case 7: unit_one<float, 128, FUSED>(J, j, r, k, wid, W, total, us, C, X, q, flush); break;
-        case 13: if constexpr (WIDE) unit_one<double, 32, FUSED>(J, j, r, k, wid, W, total, us, C, X, q, flush); break;
-        case 14: if constexpr (WIDE) unit_one<double, 64, FUSED>(J, j, r, k, wid, W, total, us, C, X, q, flush); break;
-        case 15: if constexpr (WIDE) unit_one<double, 128, FUSED>(J, j, r, k, wid, W, total, us, C, X, q, flush); break;
+        case 5: unit_one<float, 32, FUSED>(J, j, r, k, wid, W, total, true, us, C, X, q, flush); break;
+        case 6: unit_one<float, 64, FUSED>(J, j, r, k, wid, W, total, true, us, C, X, q, flush); break;
+        case 7: unit_one<float, 128, FUSED>(J, j, r, k, wid, W, total, true, us, C, X, q, flush); break;
+        case 13: if constexpr (WIDE) unit_one<double, 32, FUSED>(J, j, r, k, wid, W, total, true, us, C, X, q, flush); break;
+        case 14: if constexpr (WIDE) unit_one<double, 64, FUSED>(J, j, r, k, wid, W, total, true, us, C, X, q, flush); break;
+        case 15: if constexpr (WIDE) unit_one<double, 128, FUSED>(J, j, r, k, wid, W, total, true, us, C, X, q, flush); break;
         default: break;
       }
     }
@@ -4041,11 +4083,11 @@ static hipError_t launch_u(const Job& J, const Ctl& C, uint32_t workers, uint32_
 
 template <uint32_t OP, bool WIDE>
 static hipError_t launch_bu(const Job* d_jobs, const uint32_t* d_map, uint32_t njobs,
-                            uint32_t total, const Ctl& C, uint32_t workers, uint32_t grid,
-                            hipStream_t st) {
+                            uint32_t total, const Ctl& C, uint32_t workers, uint32_t early,
+                            uint32_t grid, hipStream_t st) {
   hipLaunchKernelGGL((k_batch_unit<OP, WIDE>), dim3(grid), dim3((workers + 1) * 64),
                      (size_t)workers * UnitEnc<OP == 2>::REGION * 4, st, d_jobs, d_map, njobs,
-                     total, C);
+                     total, early, C);
   return hipGetLastError();
 }
 
@@ -4054,6 +4096,20 @@ static hipError_t launch_bu(const Job* d_jobs, const uint32_t* d_map, uint32_t n
 static uint32_t unit_grid(bool fused, uint32_t cus, uint32_t workers, uint32_t total) {
   const uint32_t per_cu = ((fused ? UNIT_WORKERS_FUSED : UNIT_WORKERS) + 1) / (workers + 1);
   return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)cus * per_cu, total));
+}
+
+// Whether a batch takes tickets at a round's first publication (longest: rounds
+// of its longest chain): it lets a workgroup whose round is part empty go on to
+// the next job's (512 requests of 1 K to 1 M values 137 us, early 130; 64 jobs of
+// 2^20, 35 rounds each, 110 and 100), but a wait between two sizes of a workgroup
+// then holds up a chain.  At ratio 3, large and small payloads in turn, that
+// costs chains of 35 rounds 122 us against 115, but 137 rounds (8 jobs of 2^22)
+// 82 against 69: those only until a large payload is met (all small: 61 against
+// 64).  Past five rounds per workgroup it gained nothing (381 against 209 us: 32
+// jobs of 2^22).
+static uint32_t unit_early(uint32_t longest, uint32_t total, uint32_t grid) {
+  if (longest <= 48) return EARLY_YES;
+  return longest <= 192 && total <= 5ull * grid ? EARLY_SMALL : EARLY_NO;
 }
 
 hipError_t launch_unit(uint32_t op, const Job& J, const Ctl& C, uint32_t workers, uint32_t cus,
@@ -4084,13 +4140,15 @@ hipError_t launch_unit(uint32_t op, const Job& J, const Ctl& C, uint32_t workers
 
 hipError_t launch_batch_unit(uint32_t op, const Job* d_jobs, const uint32_t* d_map,
                              uint32_t njobs, uint32_t total, bool wide, const Ctl& C,
-                             uint32_t workers, uint32_t cus, hipStream_t st) {
+                             uint32_t workers, uint32_t longest, uint32_t cus,
+                             hipStream_t st) {
   const uint32_t grid = unit_grid(op == 2, cus, workers, total);
+  const uint32_t early = unit_early(longest, total, grid);
   if (op == 0)
-    return wide ? launch_bu<0, true>(d_jobs, d_map, njobs, total, C, workers, grid, st)
-                : launch_bu<0, false>(d_jobs, d_map, njobs, total, C, workers, grid, st);
+    return wide ? launch_bu<0, true>(d_jobs, d_map, njobs, total, C, workers, early, grid, st)
+                : launch_bu<0, false>(d_jobs, d_map, njobs, total, C, workers, early, grid, st);
   if (op == 2 && !wide)
-    return launch_bu<2, false>(d_jobs, d_map, njobs, total, C, workers, grid, st);
+    return launch_bu<2, false>(d_jobs, d_map, njobs, total, C, workers, early, grid, st);
   return hipErrorInvalidValue;
 }
 

@@ -327,3 +327,46 @@ def test_empty_fused_step_ignores_what_follows(gz, ctx, oracle, L):
                 assert got == (want_t if q["n"] else want), (how, k)
             if how == "plan":
                 plan.close()
+
+
+def patchy(n, dt, share, seed):
+    """Runs of one unit, the given share of them dense (payloads too large to be
+    held), the others smooth."""
+    g = np.random.default_rng(seed)
+    x = synth.sinusoids(n, seed=seed).astype(dt)
+    for u in np.flatnonzero(g.random(n // UNIT) < share):
+        x[u * UNIT:(u + 1) * UNIT] += g.uniform(-50.0, 50.0, UNIT).astype(dt)
+    return x
+
+
+@pytest.mark.parametrize("dt", [np.float32, np.float64])
+@pytest.mark.parametrize("share", [0.02, 0.5])
+def test_large_payloads_between_small_ones(oracle, gz, dt, share):
+    """Several rounds per workgroup, with payloads that are held and payloads
+    that are not: single streams, and batches on both sides of the rule for
+    early tickets."""
+    import torch
+    c = gz.Context(0, max_elems=3 << 24, max_requests=16)
+    for n, L in ((1 << 24) + 777, 32), ((3 << 22) + UNIT, 64), ((1 << 23) + 4097, 128):
+        say("patchy", dt.__name__, share, n, L)
+        x = patchy(n, dt, share, n)
+        out, nb = c.compress(dev(x), 1e-4, block_len=L)
+        torch.cuda.synchronize()
+        want = oracle.compress(x, 1e-4, block_len=L, mt=True)
+        assert out[:int(nb.item())].cpu().numpy().tobytes() == want.tobytes(), (n, L)
+    for jobs, n in ((8, (1 << 20) + 5), (12, (1 << 22) + 3)):
+        code = gz.GZ_F32 if dt == np.float32 else gz.GZ_F64
+        xs = [patchy(n, dt, share, k) for k in range(3)]
+        want = [oracle.compress(x, 1e-4, mt=True).tobytes() for x in xs]
+        D, cap = [dev(x) for x in xs], gz.bound(n, code)
+        sizes = torch.zeros(jobs, dtype=torch.int64, device="cuda")
+        items = [{"in": D[k % 3], "out": torch.zeros(cap, dtype=torch.uint8, device="cuda"),
+                  "out_bytes": sizes[k:k + 1], "n": n, "out_cap": cap, "eb": 1e-4, "dtype": code}
+                 for k in range(jobs)]
+        say("patchy batch", dt.__name__, share, jobs, n)
+        for _ in range(2):
+            c.batch(gz.GZ_OP_COMPRESS, c.requests(items))
+        assert c.device_status() == 0
+        for k, it in enumerate(items):
+            assert it["out"][:int(sizes[k].item())].cpu().numpy().tobytes() == want[k % 3], (jobs, k)
+    c.close()
