@@ -343,6 +343,17 @@ uint32_t unit_batch(const gz_ctx* c, uint32_t op, std::vector<Job>& jobs, bool c
     return t;
   };
   uint32_t W = unit_workers(op, units);
+  // A round holds units of one job, so jobs of few units fill small rounds better.
+  // They pay while every job is one round and no workgroup gets a second one (512
+  // jobs of 6000 elements in rounds of 3 against 15, fused 11: fp32 25 and 30 us,
+  // fp64 24 and 33, the fused step 27 and 41); past that, tickets bound the
+  // launch, and more workgroups slow them (4096 jobs of 6000 elements: fp32 171
+  // and 110, fp64 305 and 136; 8 jobs of 2^19 in rounds of 3 29 and 20).
+  if (W == most && !chained)
+    for (uint32_t w = 3; w < most && W == most; w = 2 * w + 1)
+      if (rounds(w) == jobs.size() &&
+          jobs.size() <= (uint64_t)c->cus * gzk::unit_per_cu(op == 2, w))
+        W = w;
   if (rounds(W) > c->max_strips) W = most;
   if (rounds(W) > c->max_strips) return 0;
   uint64_t at = 0;

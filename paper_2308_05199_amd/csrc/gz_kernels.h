@@ -60,6 +60,10 @@ constexpr uint32_t UNIT_WORKERS = 15;        // most workers of a workgroup: com
 constexpr uint32_t UNIT_WORKERS_FUSED = 11;  // the fused step
 constexpr uint64_t UNIT_ELEMS = 2048;
 size_t unit_lds(bool fused, uint32_t workers);  // its workgroup's LDS bytes
+// Workgroups a CU holds (16 waves, the fused step's 12).
+inline uint32_t unit_per_cu(bool fused, uint32_t workers) {
+  return ((fused ? UNIT_WORKERS_FUSED : UNIT_WORKERS) + 1) / (workers + 1);
+}
 inline uint64_t unit_rounds(uint64_t n, uint32_t workers) {  // an empty stream is one unit
   const uint64_t units = n ? (n + UNIT_ELEMS - 1) / UNIT_ELEMS : 1;
   return (units + workers - 1) / workers;

@@ -2844,7 +2844,7 @@ __global__ GZ_WAVE_ATTR void k_batch_fused_w(const Job* __restrict__ jobs, uint3
 // short stream spreads over many CUs.
 //
 // Offsets come from a two-level scan: the W working waves of a workgroup
-// code W consecutive units, a round (wave w: unit W r + w); inside a round
+// code W consecutive units, a round (unit_slot); inside a round
 // sizes are combined through LDS, and the round is one element of the
 // decoupled look-back, which the workgroup's last wave, the scheduler, runs.
 // A worker does not wait for its offset: small payloads are held in LDS, up
@@ -3050,8 +3050,8 @@ __device__ __forceinline__ void unit_analyse(const Job& J, uint64_t u, uint32_t 
 // values, half of the units large: 6058 us, now 447; a thousandth large: 1095,
 // now 394; 2^27 of ratio 2.8: 1815, now 233; all small or all large: the same).
 // Launches that give no workgroup a second round, and batches of short chains
-// (unit_early), take the ticket at the first publication all the same, unless
-// that payload is large.  Whoever takes it opens the round's entry.  The worker
+// until a workgroup meets a large payload (unit_early), take the ticket at the
+// first publication all the same, unless that payload is large.  Whoever takes it opens the round's entry.  The worker
 // that publishes last also publishes the round's sum; the scheduler then runs the
 // look-back and puts the round's prefix into the entry.
 // Round k + 1 is opened once every worker has published round k - 1 and the
@@ -3066,9 +3066,6 @@ __device__ __forceinline__ void unit_analyse(const Job& J, uint64_t u, uint32_t 
 // (total + workgroups - 1) ends the launch's use of the counter: its taker
 // resets counter and epoch for the next launch.
 constexpr uint32_t UNIT_PUB = 256;
-// When a round's first worker takes the next ticket: never, until a workgroup
-// has had a payload too large to be held, always.
-enum : uint32_t { EARLY_NO = 0, EARLY_SMALL = 1, EARLY_YES = 2 };
 
 struct URound {
   unsigned long long prefix;  // exclusive prefix of the round (dwords)
@@ -3084,7 +3081,7 @@ struct URound {
 };
 struct USched {
   uint32_t epoch;
-  uint32_t early; // batches: EARLY_*
+  uint32_t early; // batches: 1 while a round's first worker takes the next ticket
   uint32_t over;  // 1 once this workgroup has taken a ticket past the end
   URound rs[RING];
 };
@@ -3195,16 +3192,24 @@ struct UnitQueue {
   uint32_t n;
 };
 
+// The worker's unit of round k: in turn from either end, so that the units of
+// consecutive rounds of short jobs (one live unit or a few) go to different
+// workers, which code two rounds at once (4096 jobs of 200 values: fp32 108 -> 88
+// us, fp64 141 -> 102; of 6000 values 110 -> 93 and 137 -> 106).
+__device__ __forceinline__ uint32_t unit_slot(uint32_t wid, uint32_t k, uint32_t W) {
+  return k & 1 ? W - 1 - wid : wid;
+}
+
 // Unit u's offset in its job's payload (dwords); pj: the chain's prefix at
 // the job's first round.  False if a wait expired.
-__device__ __forceinline__ bool unit_offset(const Ctl& C, USched& us, uint32_t k, uint32_t wid,
+__device__ __forceinline__ bool unit_offset(const Ctl& C, USched& us, uint32_t k, uint32_t slot,
                                             uint64_t& off, uint64_t& pj) {
   URound& e = us.rs[k % RING];
   const uint32_t lane = __lane_id();
   if (!lds_wait_ge(C, &e.pready, k + 1) || e.bad) return false;
   pj = e.pj;
   // plus the round's earlier units (all sizes are there once the prefix is)
-  off = e.prefix - pj + wave_sum64(lane < wid ? e.size[lane] : 0u);
+  off = e.prefix - pj + wave_sum64(lane < slot ? e.size[lane] : 0u);
   return true;
 }
 
@@ -3233,12 +3238,12 @@ __device__ __forceinline__ uint32_t* unit_meta(const Job& J, uint64_t u, uint64_
 
 // Writes the oldest held unit (of job J).
 __device__ __forceinline__ void unit_flush(const Job& J, const Ctl& C, USched& us, uint32_t wid,
-                                           const uint32_t* Q, UnitQueue& q) {
+                                           uint32_t W, const uint32_t* Q, UnitQueue& q) {
   const UnitHeld h = q.h0;
   q.h0 = q.h1;
   --q.n;
   uint64_t off, pj;
-  if (!unit_offset(C, us, h.k, wid, off, pj)) return;
+  if (!unit_offset(C, us, h.k, unit_slot(wid, h.k, W), off, pj)) return;
   const uint32_t hb = Q[h.at + (__lane_id() & 15)];
   const uint32_t* pay = Q + h.at + 16;
   uint32_t* dst = J.log2L == 5   ? unit_meta<32>(J, h.u, off, pj, h.size, hb)
@@ -3248,11 +3253,11 @@ __device__ __forceinline__ void unit_flush(const Job& J, const Ctl& C, USched& u
 }
 
 // One unit: round k of the workgroup is round r of job J (index job); worker
-// wid codes unit u = W r + wid (past the job's end: an empty slot).  flush(q)
+// wid codes its slot's unit W r + slot (past the job's end: an empty slot).  flush(q)
 // writes the oldest unit held.
 template <typename T, int L, bool FUSED, bool FULL, int MODE, class Flush>
 __device__ __forceinline__ void unit_code(const Job& J, uint32_t job, uint64_t gs, uint64_t u,
-                                          bool live, uint32_t k, uint32_t wid, uint32_t W,
+                                          bool live, uint32_t k, uint32_t slot, uint32_t W,
                                           uint32_t total, bool batch, USched& us, const Ctl& C,
                                           uint32_t* X, UnitQueue& q, const Flush& flush,
                                           const uint32_t* wts) {
@@ -3282,7 +3287,7 @@ __device__ __forceinline__ void unit_code(const Job& J, uint32_t job, uint64_t g
   URound& e = us.rs[k % RING];
   uint32_t c = 0;
   if (lane == 0) {
-    e.size[wid] = size;
+    e.size[slot] = size;
     const uint32_t add = UNIT_PUB + (size > U::HELD ? 1u : 0u);
     c = add + __hip_atomic_fetch_add(&e.cnt, add, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
@@ -3294,8 +3299,8 @@ __device__ __forceinline__ void unit_code(const Job& J, uint32_t job, uint64_t g
   // first and the last ask, the claim settles it; if neither does, the change
   // came from a payload of this round, and the scheduler asks)
   const bool early = total <= gridDim.x ||
-                     (batch && __builtin_amdgcn_readfirstlane(us.early) != EARLY_NO);
-  if (batch && !held && lane == 0 && us.early == EARLY_SMALL) us.early = EARLY_NO;
+                     (batch && __builtin_amdgcn_readfirstlane(us.early) != 0);
+  if (batch && !held && lane == 0) us.early = 0;
   auto open = [&](uint32_t t) {  // once the next round's entry is free
     const RingNeed n = ring_need(k + 1);
     const bool free = (!n.published || lds_wait_ge(C, &us.rs[n.pub].cnt, W * UNIT_PUB)) &&
@@ -3362,7 +3367,7 @@ __device__ __forceinline__ void unit_code(const Job& J, uint32_t job, uint64_t g
   if (!two) wave_pack<T, L, FUSED, FULL, MODE>(J, seg, w, vcnt, lc, fs, X + boff);
   wave_lds_sync();
   uint64_t off, pj;
-  const bool known = unit_offset(C, us, k, wid, off, pj);
+  const bool known = unit_offset(C, us, k, slot, off, pj);
   if (!known || !good) return;
   uint32_t* dst = unit_meta<L>(J, u, off, pj, size, HB[lane & (U::HBW - 1)]);
   if (!two) {
@@ -3386,13 +3391,14 @@ __device__ __forceinline__ void unit_one(const Job& J, uint32_t job, uint64_t r,
                                          const Ctl& C, uint32_t* X, UnitQueue& q,
                                          const Flush& flush,
                                          const uint32_t* wts = nullptr) {
-  const uint64_t u = r * W + wid;
+  const uint32_t slot = unit_slot(wid, k, W);
+  const uint64_t u = r * W + slot;
   // an empty stream is one unit of no values
   const bool live = u == 0 || u * UNIT_ELEMS < J.n;
   if ((u + 1) * UNIT_ELEMS <= J.n)
-    unit_code<T, L, FUSED, true, MODE>(J, job, J.strip0 + r, u, live, k, wid, W, total, early, us, C, X, q, flush, wts);
+    unit_code<T, L, FUSED, true, MODE>(J, job, J.strip0 + r, u, live, k, slot, W, total, early, us, C, X, q, flush, wts);
   else
-    unit_code<T, L, FUSED, false, MODE>(J, job, J.strip0 + r, u, live, k, wid, W, total, early, us, C, X, q, flush, wts);
+    unit_code<T, L, FUSED, false, MODE>(J, job, J.strip0 + r, u, live, k, slot, W, total, early, us, C, X, q, flush, wts);
 }
 
 // Registers for four waves per SIMD (the fused step: three), as the LDS allows.
@@ -3419,7 +3425,7 @@ __global__ GZ_UNIT_ATTR(FUSED) void k_unit(Job J, Ctl C) {
     uint32_t* X = g_stage + wid * UnitEnc<FUSED>::REGION;
     UnitQueue q;
     q.n = 0;
-    auto flush = [&](UnitQueue& x) { unit_flush(J, C, us, wid, X + UnitEnc<FUSED>::XW, x); };
+    auto flush = [&](UnitQueue& x) { unit_flush(J, C, us, wid, W, X + UnitEnc<FUSED>::XW, x); };
     for (uint32_t k = 0;; ++k) {
       if (!lds_wait_ge(C, &us.rs[k % RING].ready, k + 1)) break;
       const uint32_t t = __builtin_amdgcn_readfirstlane(us.rs[k % RING].ticket);
@@ -3455,7 +3461,7 @@ __global__ GZ_UNIT_ATTR(false) void k_unit_tiles(Job J, Ctl C) {
     uint32_t* X = g_stage + wid * UnitEnc<false>::REGION;
     UnitQueue q;
     q.n = 0;
-    auto flush = [&](UnitQueue& x) { unit_flush(J, C, us, wid, X + UnitEnc<false>::XW, x); };
+    auto flush = [&](UnitQueue& x) { unit_flush(J, C, us, wid, W, X + UnitEnc<false>::XW, x); };
     for (uint32_t k = 0;; ++k) {
       if (!lds_wait_ge(C, &us.rs[k % RING].ready, k + 1)) break;
       const uint32_t t = __builtin_amdgcn_readfirstlane(us.rs[k % RING].ticket);
@@ -3498,7 +3504,7 @@ __global__ GZ_UNIT_ATTR(OP == 2) void k_batch_unit(const Job* __restrict__ jobs,
     UnitQueue q;
     q.n = 0;
     auto flush = [&](UnitQueue& x) {
-      unit_flush(jobs[x.h0.job], C, us, wid, X + UnitEnc<FUSED>::XW, x);
+      unit_flush(jobs[x.h0.job], C, us, wid, W, X + UnitEnc<FUSED>::XW, x);
     };
     for (uint32_t k = 0;; ++k) {
       if (!lds_wait_ge(C, &us.rs[k % RING].ready, k + 1)) break;
@@ -4091,26 +4097,21 @@ static hipError_t launch_bu(const Job* d_jobs, const uint32_t* d_map, uint32_t n
   return hipGetLastError();
 }
 
-// Workgroups in flight: as many as the CUs hold (16 waves, the fused step's
-// 12), at most one per round.
+// Workgroups in flight: as many as the CUs hold, at most one per round.
 static uint32_t unit_grid(bool fused, uint32_t cus, uint32_t workers, uint32_t total) {
-  const uint32_t per_cu = ((fused ? UNIT_WORKERS_FUSED : UNIT_WORKERS) + 1) / (workers + 1);
-  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)cus * per_cu, total));
+  return (uint32_t)std::max<uint64_t>(
+      1, std::min<uint64_t>((uint64_t)cus * unit_per_cu(fused, workers), total));
 }
 
-// Whether a batch takes tickets at a round's first publication (longest: rounds
-// of its longest chain): it lets a workgroup whose round is part empty go on to
-// the next job's (512 requests of 1 K to 1 M values 137 us, early 130; 64 jobs of
-// 2^20, 35 rounds each, 110 and 100), but a wait between two sizes of a workgroup
-// then holds up a chain.  At ratio 3, large and small payloads in turn, that
-// costs chains of 35 rounds 122 us against 115, but 137 rounds (8 jobs of 2^22)
-// 82 against 69: those only until a large payload is met (all small: 61 against
-// 64).  Past five rounds per workgroup it gained nothing (381 against 209 us: 32
-// jobs of 2^22).
-static uint32_t unit_early(uint32_t longest, uint32_t total, uint32_t grid) {
-  if (longest <= 48) return EARLY_YES;
-  return longest <= 192 && total <= 5ull * grid ? EARLY_SMALL : EARLY_NO;
-}
+// Whether a batch's workgroups take tickets at a round's first publication until
+// they meet a payload too large to be held (longest: rounds of its longest
+// chain).  It lets a workgroup whose round is part empty go on to the next job's
+// (512 requests of 1 K to 1 M values 115 us, early 107; 64 jobs of 2^20 110 and
+// 98), but the first large payload of each workgroup then delays a chain: with
+// one unit in a hundred large, chains of 137 rounds lost nothing to it (32 jobs of
+// 2^22 206 us, 210 by strips), 547 rounds 314 against 196 (8 of 2^24).  Not given
+// up at a large payload, it cost chains of 35 rounds of ratio 3 122 against 109.
+static uint32_t unit_early(uint32_t longest) { return longest <= 192 ? 1u : 0u; }
 
 hipError_t launch_unit(uint32_t op, const Job& J, const Ctl& C, uint32_t workers, uint32_t cus,
                        hipStream_t st) {
@@ -4143,7 +4144,7 @@ hipError_t launch_batch_unit(uint32_t op, const Job* d_jobs, const uint32_t* d_m
                              uint32_t workers, uint32_t longest, uint32_t cus,
                              hipStream_t st) {
   const uint32_t grid = unit_grid(op == 2, cus, workers, total);
-  const uint32_t early = unit_early(longest, total, grid);
+  const uint32_t early = unit_early(longest);
   if (op == 0)
     return wide ? launch_bu<0, true>(d_jobs, d_map, njobs, total, C, workers, early, grid, st)
                 : launch_bu<0, false>(d_jobs, d_map, njobs, total, C, workers, early, grid, st);

@@ -370,3 +370,37 @@ def test_large_payloads_between_small_ones(oracle, gz, dt, share):
         for k, it in enumerate(items):
             assert it["out"][:int(sizes[k].item())].cpu().numpy().tobytes() == want[k % 3], (jobs, k)
     c.close()
+
+
+@pytest.mark.parametrize("op", ["compress", "fused"])
+@pytest.mark.parametrize("jobs,n", [(900, 1 * UNIT), (700, 3 * UNIT), (500, 3 * UNIT + 1),
+                                    (400, 7 * UNIT), (300, 7 * UNIT + 1), (1100, 3 * UNIT)])
+def test_batches_of_equal_short_jobs(gz, ctx, oracle, op, jobs, n):
+    """Rounds of 3, 7 or all workers, one round per job or two, one round per
+    workgroup or several; every third compression job is fp64, one size less."""
+    import torch
+    xs = [field("mixed", n - (k % 3 == 2), np.float64 if op == "compress" and k % 3 == 2
+                else np.float32, k) for k in range(6)]
+    ys = [field("smooth", x.size, np.float32, k + 9) for k, x in enumerate(xs)]
+    if op == "fused":
+        xs = [oracle.compress(x, 1e-4) for x in xs]
+        want = [oracle.fused_step(x, y, 1e-4).tobytes() for x, y in zip(xs, ys)]
+    else:
+        want = [oracle.compress(x, 1e-4).tobytes() for x in xs]
+    X, Y = [dev(x) for x in xs], [dev(y) for y in ys]
+    sizes = torch.zeros(jobs, dtype=torch.int64, device="cuda")
+    items = []
+    for k in range(jobs):
+        i, m = k % 6, ys[k % 6].size
+        code = gz.GZ_F64 if xs[i].dtype == np.float64 else gz.GZ_F32
+        cap = gz.bound(m, code)
+        items.append({"in": X[i], "out": torch.zeros(cap, dtype=torch.uint8, device="cuda"),
+                      "out_bytes": sizes[k:k + 1], "n": m, "out_cap": cap, "eb": 1e-4,
+                      "dtype": code, **({"local": Y[i], "in_bytes": xs[i].size}
+                                        if op == "fused" else {})})
+    say("short jobs", op, jobs, n)
+    for _ in range(2):
+        ctx.batch(gz.GZ_OP_COMPRESS if op == "compress" else gz.GZ_OP_FUSED, ctx.requests(items))
+    assert ctx.device_status() == 0
+    for k, it in enumerate(items):
+        assert it["out"][:int(sizes[k].item())].cpu().numpy().tobytes() == want[k % 6], k
