@@ -316,18 +316,24 @@ bool unit_single(const gz_ctx* c, uint32_t op, Job& J, uint32_t& W) {
   return rounds <= c->max_strips;
 }
 
-// A fused batch that the per-wave kernel codes faster than the unit kernel:
-// jobs of equal block length and superblock count (`uniform`), more units than
-// one pass of the unit kernel's workers (256 CUs x 11 = 2816: 8 jobs of 2^20
-// elements 27 against 35 us a launch, 8 of 2^21 50 against 53; 8 of 2^19, one
-// pass, 22 against 19).  Returns its rounds, 0 if units are to code it.
+// Whether the per-wave kernel codes a fused step of this many units faster than
+// the unit kernel: more than one pass of the unit kernel's workers (256 CUs x 11
+// = 2816: a stream of 2^22.5 elements 36 against 40 us, 2^23 38 against 45, 8 jobs
+// of 2^20 27 against 35 a launch, 8 of 2^21 50 against 53; in one pass, a stream of
+// 2^22 33 against 29, 8 jobs of 2^19 22 against 19).
+bool fused_by_waves(const gz_ctx* c, uint64_t units) {
+  return units > (uint64_t)c->cus * gzk::UNIT_WORKERS_FUSED && gzk::wave_fused_lds() <= c->lds_max;
+}
+
+// The same for a batch, which the per-wave kernel takes if its jobs have equal
+// block length and superblock count (`uniform`): its rounds, 0 if units are to
+// code it.
 uint64_t wave_fused_rounds(const gz_ctx* c, gz_op op, const std::vector<Job>& jobs,
                            bool uniform) {
-  if (op != GZ_OP_FUSED || !uniform || gzk::wave_fused_lds() > c->lds_max) return 0;
-  const uint64_t units = jobs.size() * gzk::unit_rounds(jobs[0].n, 1);
-  return units > (uint64_t)c->cus * gzk::UNIT_WORKERS_FUSED
-             ? jobs.size() * gzk::wave_rounds(jobs[0].NS)
-             : 0;
+  if (op != GZ_OP_FUSED || !uniform ||
+      !fused_by_waves(c, jobs.size() * gzk::unit_rounds(jobs[0].n, 1)))
+    return 0;
+  return jobs.size() * gzk::wave_rounds(jobs[0].NS);
 }
 
 // Lays out a batch's jobs for unit encoding (strip0/nstrips in rounds; one
@@ -919,6 +925,9 @@ gz_status gz_fused_reduce_step(gz_ctx* c, const void* d_cmp_in, uint64_t in_byte
     }
     set_geom(J, n, L, gzk::MAX_TPB);
     if (J.nstrips > c->max_strips) return GZ_ENOSPC;
+    if (fused_by_waves(c, gzk::unit_rounds(n, 1)))
+      return hip_status(gzk::launch_fused_wave_single(J, c->ctl(), (uint32_t)c->cus,
+                                                      (hipStream_t)stream));
     uint32_t W;
     if (unit_single(c, 2, J, W))
       return hip_status(

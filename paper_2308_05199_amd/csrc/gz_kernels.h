@@ -41,6 +41,8 @@ hipError_t launch_accum_wave_batch(const Job* d_jobs, const uint32_t* d_map, uin
 // ticket t = round t / njobs of job t % njobs.
 hipError_t launch_fused_wave(const Job* d_jobs, uint32_t njobs, uint32_t total, uint32_t log2L,
                              const Ctl& C, uint32_t cus, hipStream_t st);
+// The same of one stream: wave_rounds(J.NS) look-back words.
+hipError_t launch_fused_wave_single(const Job& J, const Ctl& C, uint32_t cus, hipStream_t st);
 constexpr uint64_t WAVE_ROUND = 8;  // superblocks per round
 size_t wave_fused_lds();            // its workgroup's LDS bytes
 inline uint64_t wave_rounds(uint64_t NS) { return (NS + WAVE_ROUND - 1) / WAVE_ROUND; }

@@ -2351,9 +2351,9 @@ __device__ __forceinline__ void store_tile(const Job& J, float* __restrict__ p,
   }
 }
 
-// ------------------------------------------------- per-wave fused batches
-// The fused step of large uniform fp32 batches (more units than one pass of
-// the unit kernel below codes) by single waves, a whole superblock each: eight
+// ---------------------------------------------------- per-wave fused step
+// The fused step of long fp32 streams and large uniform batches (more units than
+// one pass of the unit kernel below codes) by single waves, a whole superblock each: eight
 // waves a CU with two units' work per claim.  On an 8-rank ring of 256^3 (2048
 // waves, two superblocks each) 376 us against 407 us by units, whose 2816
 // workers pass over the 8192 units three times; from one pass down the unit
@@ -2788,6 +2788,45 @@ __device__ __forceinline__ bool wave_round_begin(const Job& J, uint64_t u, const
 // Rounds of a job of NS superblocks.
 __device__ __forceinline__ uint64_t rounds_of(uint64_t NS) {
   return (NS + WaveEnc::WAVES - 1) / WaveEnc::WAVES;
+}
+
+// One stream: round ticket T covers superblocks WAVES * T + slot, look-back
+// word T.  Longer streams than one pass of the unit kernel's workers: 2^23, 2^24
+// and 2^26 elements 38, 58 and 170 us, by units 45, 61 and 183.
+template <int L>
+__global__ GZ_WAVE_ATTR void k_fused_w(Job J, Ctl C) {
+  __shared__ WaveSched ws;
+  wave_sched_init(ws);
+  uint32_t* R = g_stage + (threadIdx.x >> 6) * WaveEnc::REGION;
+  const uint32_t ep = ld_agent32(&C.ctrl->epoch);
+  const uint64_t NR = rounds_of(J.NS);
+  Claim cl = wave_claim(C, ws);
+  UnitPre pre;
+  pre.valid = false;
+  for (;;) {
+    RoundState& rs = ws.rs[cl.round % WRING];
+    if (cl.ticket >= NR) {  // past the end (or timed out)
+      if (cl.slot == 0 && __lane_id() == 0) wave_hand_on(C, ws, cl.round, cl.ticket, false);
+      wave_release(rs);
+      break;
+    }
+    const uint64_t u = (uint64_t)cl.ticket * WaveEnc::WAVES + cl.slot;
+    uint32_t tot[2];
+    uint64_t off = 0;
+    const bool wr = wave_round_begin<L>(J, u, cl, ws, cl.ticket, 0, C, ep, R, pre, tot, off);
+    // the next slot, and its first words ahead of this unit's stores
+    Claim nx = wave_claim_try(C, ws);
+    pre.valid = false;
+    if (nx.done && nx.ticket < NR) {
+      const uint64_t v = (uint64_t)nx.ticket * WaveEnc::WAVES + nx.slot;
+      if (v < J.NS) wave_unit_preload<L>(J, v, pre);
+    }
+    if (wr) wave_write_unit<L>(J, u, off, tot, R);
+    wave_release(rs);
+    wave_claim_finish(C, ws, nx);
+    cl = nx;
+  }
+  epilogue(C);
 }
 
 // njobs streams of NS superblocks each (total = njobs x rounds per job),
@@ -4062,6 +4101,23 @@ static hipError_t launch_fw(const Job* d_jobs, uint32_t njobs, uint32_t total, c
   hipLaunchKernelGGL((k_batch_fused_w<L>), dim3(grid), dim3(WaveEnc::WAVES * 64),
                      (size_t)WaveEnc::WAVES * WaveEnc::REGION * 4, st, d_jobs, njobs, total, C);
   return hipGetLastError();
+}
+
+template <int L>
+static hipError_t launch_fw1(const Job& J, const Ctl& C, uint32_t cus, hipStream_t st) {
+  const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(cus, wave_rounds(J.NS)));
+  hipLaunchKernelGGL((k_fused_w<L>), dim3(grid), dim3(WaveEnc::WAVES * 64),
+                     (size_t)WaveEnc::WAVES * WaveEnc::REGION * 4, st, J, C);
+  return hipGetLastError();
+}
+
+hipError_t launch_fused_wave_single(const Job& J, const Ctl& C, uint32_t cus, hipStream_t st) {
+  switch (J.log2L) {
+    case 5: return launch_fw1<32>(J, C, cus, st);
+    case 6: return launch_fw1<64>(J, C, cus, st);
+    case 7: return launch_fw1<128>(J, C, cus, st);
+  }
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_fused_wave(const Job* d_jobs, uint32_t njobs, uint32_t total, uint32_t log2L,

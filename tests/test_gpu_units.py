@@ -404,3 +404,44 @@ def test_batches_of_equal_short_jobs(gz, ctx, oracle, op, jobs, n):
     assert ctx.device_status() == 0
     for k, it in enumerate(items):
         assert it["out"][:int(sizes[k].item())].cpu().numpy().tobytes() == want[k % 6], k
+
+
+@pytest.mark.parametrize("L", [32, 64, 128])
+def test_long_fused_streams(ctx, oracle, gz, L):
+    """Streams on both sides of one pass of the unit workers (256 CUs x 11 units),
+    at edges of superblocks and rounds of eight; a damaged one sets the status."""
+    import torch
+    edge = 256 * 11 * UNIT
+    for n, kind in ((edge, "mixed"), (edge + 1, "smooth"), (edge + 4097, "mixed"),
+                    (edge + 8 * 4096 - 1, "raw")):
+        say("long fused", L, n, kind)
+        x, y = field(kind, n, np.float32, 3), field("smooth", n, np.float32, 4)
+        s = oracle.compress(x, 1e-4, block_len=L, mt=True)
+        want = oracle.fused_step(s, y, 1e-4, block_len=L, mt=True).tobytes()
+        S, Y = dev(s), dev(y)
+        for threads in (0, 64):
+            out, nb = ctx.fused_reduce_step(S, Y, 1e-4, block_len=L, threads=threads)
+            assert ctx.device_status() == 0
+            assert out[:int(nb.item())].cpu().numpy().tobytes() == want, (n, threads)
+    b = s.copy()
+    b[64 + 4 * 700] ^= 0x15  # a table word
+    ctx.fused_reduce_step(dev(b), Y, 1e-4, block_len=L)
+    assert ctx.device_status() == gz.GZ_ECORRUPT
+    out, nb = ctx.fused_reduce_step(S, Y, 1e-4, block_len=L)
+    assert ctx.device_status() == 0
+    assert out[:int(nb.item())].cpu().numpy().tobytes() == want
+
+
+@pytest.mark.parametrize("L", [32, 64, 128])
+def test_fused_raw_input_at_unit_edges(ctx, oracle, L):
+    """Incoming streams of RAW blocks only, sums that are coded and sums that stay RAW."""
+    for n in (1, 33, 2047, 2049, 4097, 3 * UNIT + 31, ROUND_FUSED + 5):
+        x = field("smooth", n, np.float32, n)
+        x[::8] = np.float32(3e38)
+        for y in (-x, field("raw", n, np.float32, n + 1), field("smooth", n, np.float32, n + 2)):
+            say("raw fused", L, n)
+            s = oracle.compress(x, 1e-4, block_len=L)
+            out, nb = ctx.fused_reduce_step(dev(s), dev(y), 1e-4, block_len=L)
+            want = oracle.fused_step(s, y, 1e-4, block_len=L)
+            assert ctx.device_status() == 0
+            assert out[:int(nb.item())].cpu().numpy().tobytes() == want.tobytes(), n
