@@ -285,6 +285,10 @@ bool wave_wanted(const gz_ctx* c, uint32_t op, uint32_t dt, uint32_t L, const gz
   return t.tpb ? t.tpb == WAVE_TPB : wave_default(op);
 }
 
+bool tuned_shape(const gz_ctx* c, uint32_t op, uint32_t dt, uint32_t L) {
+  return c->tuned[tune_op(op)][dt][log2_of(L) - 5].tpb != 0;
+}
+
 // Workers per workgroup of a unit-encoding launch over `units` units: the
 // fewest that leave at most 192 rounds.  Short streams gain from more CUs (2^14
 // to 2^20 elements in rounds of 3 rather than 15: compression 10.6-11.0 against
@@ -303,6 +307,16 @@ uint32_t unit_workers(uint32_t op, uint64_t units) {
 // at 2^24; below, one launch's latency either way; above, the superblocks'
 // pipeline is the faster, 68 against 75 us at 2^26).
 bool unit_decodes(const Job& J) { return J.dtype == GZ_F64 || (J.NS >= 128 && J.NS <= 4096); }
+
+// Whether one stream is compressed by units if nothing else is asked for or
+// tuned: fp64, and fp32 in one pass of the unit kernel's workers (256 CUs x 15).
+// Longer fp32 streams take strips, whose four waves per SIMD hide as much and do
+// less control work: 2^23, 2^24, 2^26 and 2^27 elements 30, 42, 111 and 207 us, by
+// units 34, 47, 118 and 214; 2^28 402 and 401 at ratio 4, 404 and 439 at ratio 2.
+// In one pass units win: 2^22.75 elements 26 against 28 us, 2^14 9 against 14.
+bool unit_compresses(const gz_ctx* c, uint32_t dt, uint64_t n) {
+  return dt == GZ_F64 || gzk::unit_rounds(n, 1) <= (uint64_t)c->cus * gzk::UNIT_WORKERS;
+}
 
 // Lays out single job J (n, dtype, L set by set_geom) for unit encoding:
 // workers per workgroup, J.nstrips rounds.  False if the workspace has too
@@ -609,7 +623,20 @@ bool batch_unit(const gz_ctx* c, gz_op op, const std::vector<Job>& jobs, bool wi
   if ((op != GZ_OP_COMPRESS && op != GZ_OP_FUSED) || !unit_fits(c, op)) return false;
   if (any) return true;
   if (p && p->threads) return p->threads == WAVE_TPB && !wide && batch_wave_ok(c, op, jobs);
-  return batch_wave_wanted(c, op, p, wide);
+  if (!batch_wave_wanted(c, op, p, wide)) return false;
+  if (op != GZ_OP_COMPRESS || wide || c->batch_tuned[op][0].tpb) return true;
+  // fp32 compression by strips where they divide the jobs better: a round of 15
+  // units is a little smaller than a strip, so jobs of 2^15 elements need two
+  // rounds for one strip (512 of them 36 us by strips, 41-46 by units; 100 of 2^16
+  // 22 and 25; 64 of 2^17 24 and 26), and 8 jobs of 2^20 more than one round per
+  // CU (26 and 28).  From a tenth more rounds down units win (64 of 2^20 99 us
+  // against 105), and by far for jobs well below a strip (4096 of 2^13 86 and 172).
+  uint64_t strips = 0, rounds = 0;
+  for (const Job& J : jobs) {
+    strips += J.nstrips;
+    rounds += gzk::unit_rounds(J.n, gzk::UNIT_WORKERS);
+  }
+  return rounds <= (uint64_t)c->cus || (rounds * 5 < strips * 6 && strips > (uint64_t)c->cus);
 }
 
 uint32_t batch_grid(const gz_ctx* c, gz_op op, bool wide, uint32_t tpb, uint64_t total,
@@ -798,7 +825,8 @@ gz_status compress_impl(gz_ctx* c, const void* d_in, uint64_t n, gz_dtype dtype,
   gz_params q;  // waves asked for: the default strips' geometry, should units not fit
   if (!tile_mode(p) && unit_fits(c, 0) &&
       (unit || (wave_wanted(c, 0, dtype, L, p) &&
-                !(p && p->threads == WAVE_TPB && !wave_fits(c, 0, dtype))))) {
+                (p && p->threads ? wave_fits(c, 0, dtype)
+                                 : tuned_shape(c, 0, dtype, L) || unit_compresses(c, dtype, n))))) {
     if (p && p->threads) {
       q = *p;
       q.threads = q.grid = 0;

@@ -350,10 +350,12 @@ def test_large_payloads_between_small_ones(oracle, gz, dt, share):
     for n, L in ((1 << 24) + 777, 32), ((3 << 22) + UNIT, 64), ((1 << 23) + 4097, 128):
         say("patchy", dt.__name__, share, n, L)
         x = patchy(n, dt, share, n)
-        out, nb = c.compress(dev(x), 1e-4, block_len=L)
-        torch.cuda.synchronize()
-        want = oracle.compress(x, 1e-4, block_len=L, mt=True)
-        assert out[:int(nb.item())].cpu().numpy().tobytes() == want.tobytes(), (n, L)
+        want = oracle.compress(x, 1e-4, block_len=L, mt=True).tobytes()
+        # fp32 streams of this size take strips by default, units when asked for
+        for threads in (0, 64) if dt == np.float32 else (0,):
+            out, nb = c.compress(dev(x), 1e-4, block_len=L, threads=threads)
+            torch.cuda.synchronize()
+            assert out[:int(nb.item())].cpu().numpy().tobytes() == want, (n, L, threads)
     for jobs, n in ((8, (1 << 20) + 5), (12, (1 << 22) + 3)):
         code = gz.GZ_F32 if dt == np.float32 else gz.GZ_F64
         xs = [patchy(n, dt, share, k) for k in range(3)]
@@ -445,3 +447,28 @@ def test_fused_raw_input_at_unit_edges(ctx, oracle, L):
             want = oracle.fused_step(s, y, 1e-4, block_len=L)
             assert ctx.device_status() == 0
             assert out[:int(nb.item())].cpu().numpy().tobytes() == want.tobytes(), n
+
+
+@pytest.mark.parametrize("jobs,n", [(256, 1 << 15), (300, 1 << 15), (64, 1 << 17), (8, 1 << 20),
+                                    (300, (1 << 15) - UNIT), (40, (1 << 16) + 3)])
+def test_batches_on_both_sides_of_the_strip_rule(gz, ctx, oracle, jobs, n):
+    """fp32 batches that strips divide better than rounds of units, and their
+    neighbours that units take, by batch and by plan."""
+    import torch
+    xs = [field(k, n, np.float32, 5) for k in ("smooth", "mixed", "dense")]
+    want = [oracle.compress(x, 1e-4).tobytes() for x in xs]
+    D, cap = [dev(x) for x in xs], gz.bound(n)
+    sizes = torch.zeros(jobs, dtype=torch.int64, device="cuda")
+    items = [{"in": D[k % 3], "out": torch.zeros(cap, dtype=torch.uint8, device="cuda"),
+              "out_bytes": sizes[k:k + 1], "n": n, "out_cap": cap, "eb": 1e-4,
+              "dtype": gz.GZ_F32} for k in range(jobs)]
+    reqs = ctx.requests(items)
+    say("strip rule", jobs, n)
+    plan = ctx.plan(gz.GZ_OP_COMPRESS, reqs)
+    for run in (lambda: ctx.batch(gz.GZ_OP_COMPRESS, reqs), plan.launch):
+        sizes.zero_()
+        run()
+        assert ctx.device_status() == 0
+        for k, it in enumerate(items):
+            assert it["out"][:int(sizes[k].item())].cpu().numpy().tobytes() == want[k % 3], k
+    plan.close()
