@@ -711,7 +711,9 @@ gz_status gz_ctx_create(gz_ctx** out, int device, uint64_t max_elems, uint32_t m
   ok = ok && hipMalloc((void**)&c->train_ws, gzs::mlp_workspace_bytes()) == hipSuccess;
   // live plans may hold up to 16 batches' worth of descriptors and maps
   c->plan_jobs_arena.cap = 16ull * max_requests + 64;
-  c->plan_map_arena.cap = 16ull * 2 * c->max_strips + 1024;
+  // (a map of unit rounds, three units or more each, has up to 16/3 entries for
+  // one of a 32768-element strip)
+  c->plan_map_arena.cap = 6ull * 16 * 2 * c->max_strips + 1024;
   ok = ok && hipMalloc((void**)&c->plan_jobs, c->plan_jobs_arena.cap * sizeof(Job)) == hipSuccess;
   ok = ok && hipMalloc((void**)&c->plan_map, c->plan_map_arena.cap * 4) == hipSuccess;
   c->stage_bytes = (size_t)max_requests * sizeof(Job) + c->max_strips * 8;
@@ -1227,6 +1229,9 @@ gz_status gz_plan_create(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t
   uint32_t unit_w = 0;
   if (unit && !fw) unit_w = unit_batch(c, op, jobs, false);
   if (unit_w) fill_map(jobs, true, map);
+  const uint64_t total = map.size() / 2;
+  // jobs of equal strip or round counts: the kernels derive the map
+  if (!wave_dec && (fw || uniform_jobs(jobs))) map.clear();
   // a range released by gz_plan_destroy may still be read by a launch in
   // flight: the device finishes its work before the arena is written
   if (hipDeviceSynchronize() != hipSuccess) return GZ_EHIP;
@@ -1248,7 +1253,7 @@ gz_status gz_plan_create(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t
   pl->map_off = mo;
   pl->d_jobs = c->plan_jobs + jo;
   pl->d_map = c->plan_map + mo;
-  pl->total = (uint32_t)(map.size() / 2);
+  pl->total = (uint32_t)total;
   pl->njobs = uniform_jobs(jobs);
   pl->tpb = tpb;
   pl->wide = wide;

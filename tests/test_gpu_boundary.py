@@ -128,3 +128,24 @@ def test_two_contexts_on_two_streams_write_identical_bytes(gz, oracle):
         assert c.device_status(st) == 0
         c.close()
     ref_ctx.close()
+
+
+def test_small_uneven_plans_fill_the_arena(gz):
+    """The plan arena's job descriptors, not its maps, bound the number of plans
+    of small uneven batches, whose rounds of units are short."""
+    import torch
+    say("small uneven plans")
+    ctx = gz.Context(0, max_elems=1 << 22, max_requests=64)  # arena: 16 * 64 + 64 jobs
+    xs = [torch.zeros(1 << e, device="cuda") for e in (19, 18)]
+    outs = [torch.empty(gz.bound(x.numel()), dtype=torch.uint8, device="cuda") for x in xs]
+    nbs = [torch.zeros(1, dtype=torch.int64, device="cuda") for _ in xs]
+    reqs = ctx.requests(compress_items(gz, xs, outs, nbs))
+    plans = [ctx.plan(gz.GZ_OP_COMPRESS, reqs) for _ in range(8 * 64 + 32)]
+    with pytest.raises(gz.GzError) as e:
+        ctx.plan(gz.GZ_OP_COMPRESS, reqs)
+    assert e.value.status == gz.GZ_ENOSPC
+    plans[-1].launch()
+    assert ctx.device_status() == 0
+    for p in plans:
+        p.close()
+    ctx.close()
