@@ -450,10 +450,10 @@ uint32_t uniform_jobs(const std::vector<Job>& jobs) {
 // (job, first superblock, stride) triples, each job given waves in
 // proportion to its superblocks (at least one) out of the waves the
 // per-wave decoder is launched with; empty where that does not apply
-// (accumulation, fp64, tiles, more jobs than waves), and the (job,
-// superblock) map is used instead.
+// (accumulation, fp64, tiles, more jobs than waves, more than cap words), and
+// the (job, superblock) map is used instead.
 std::vector<uint32_t> wave_job_shares(const gz_ctx* c, gz_op op, const std::vector<Job>& jobs,
-                                      bool wide, uint64_t total) {
+                                      bool wide, uint64_t total, uint64_t cap) {
   std::vector<uint32_t> m;
   if (op != GZ_OP_DECOMPRESS || wide || jobs.empty() || total == 0) return m;
   for (const Job& J : jobs)
@@ -473,6 +473,7 @@ std::vector<uint32_t> wave_job_shares(const gz_ctx* c, gz_op op, const std::vect
     --*it;
     --sum;
   }
+  if (3 * sum > cap) return m;
   m.reserve(3 * sum);
   for (size_t j = 0; j < jobs.size(); ++j)
     for (uint64_t i = 0; i < cnt[j]; ++i) {
@@ -1108,7 +1109,7 @@ gz_status gz_scatter_decompress(gz_ctx* c, const void* d_packed, uint64_t packed
     const uint64_t total = wave_decode_map(jobs, smap);
     if (batch_decode_wave_ok(c, GZ_OP_DECOMPRESS, jobs, dtype == GZ_F64, total)) {
       const std::vector<uint32_t> jm =
-          wave_job_shares(c, GZ_OP_DECOMPRESS, jobs, dtype == GZ_F64, total);
+          wave_job_shares(c, GZ_OP_DECOMPRESS, jobs, dtype == GZ_F64, total, 2 * c->max_strips);
       if (asked || !jm.empty() || dtype == GZ_F64) {
         gz_status r = stage_upload(c, jobs, jm.empty() ? smap : jm, st);
         if (r != GZ_OK) return r;
@@ -1152,7 +1153,8 @@ gz_status batch_impl(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t nre
     std::vector<uint32_t> smap;
     const uint64_t total = wave_decode_map(jobs, smap);
     if (batch_decode_wave_ok(c, op, jobs, wide, total)) {
-      const std::vector<uint32_t> jm = wave_job_shares(c, op, jobs, wide, total);
+      const std::vector<uint32_t> jm =
+          wave_job_shares(c, op, jobs, wide, total, 2 * c->max_strips);
       r = stage_upload(c, jobs, jm.empty() ? smap : jm, st);
       if (r != GZ_OK) return r;
       return hip_status(launch_decode((uint32_t)op, c->d_jobs,
@@ -1215,7 +1217,8 @@ gz_status gz_plan_create(gz_ctx* c, gz_op op, const gz_request* h_reqs, uint32_t
     dec_total = wave_decode_map(jobs, smap);
     wave_dec = batch_decode_wave_ok(c, op, jobs, wide, dec_total);
     if (wave_dec) {
-      std::vector<uint32_t> jm = wave_job_shares(c, op, jobs, wide, dec_total);
+      std::vector<uint32_t> jm =
+          wave_job_shares(c, op, jobs, wide, dec_total, c->plan_map_arena.cap);
       jw = (uint32_t)(jm.size() / 3);
       map.swap(jm.empty() ? smap : jm);
     } else if (p && p->threads == WAVE_TPB) {

@@ -149,3 +149,31 @@ def test_small_uneven_plans_fill_the_arena(gz):
     for p in plans:
         p.close()
     ctx.close()
+
+
+def test_decoding_in_a_context_without_spare_room(gz, oracle):
+    """Default fp32 decoding, batched and scattered, of as many elements as the
+    context was made for: a map that does not fit is not chosen."""
+    import torch
+    from paper_2308_05199_amd import synth
+    say("decoding in a tight context")
+    n = 1 << 17
+    x = synth.sinusoids(n, seed=5)
+    ctx = gz.Context(0, max_elems=n, max_requests=1)
+    s = torch.from_numpy(oracle.compress(x, 1e-4)).cuda()
+    y = torch.zeros(n, device="cuda")
+    ctx.batch(gz.GZ_OP_DECOMPRESS, ctx.requests([
+        {"in": s, "in_bytes": s.numel(), "out": y, "n": n, "dtype": gz.GZ_F32}]))
+    assert ctx.device_status() == 0
+    want = oracle.decompress(oracle.compress(x, 1e-4))
+    assert y.cpu().numpy().tobytes() == want.tobytes()
+    ctx.close()
+    ctx = gz.Context(0, max_elems=n, max_requests=4)
+    counts, displs = [n // 4 - 3, n // 4 + 3, n // 4, n // 4], [0, n // 4 - 3, n // 2, 3 * n // 4]
+    packed, _, offs = ctx.scatter_compress(torch.from_numpy(x).cuda(), counts, displs, 1e-4)
+    out = ctx.scatter_decompress(packed, offs, counts, displs)
+    assert ctx.device_status() == 0
+    want = np.concatenate([oracle.decompress(oracle.compress(x[d:d + c], 1e-4))
+                           for c, d in zip(counts, displs)])
+    assert out.cpu().numpy().tobytes() == want.tobytes()
+    ctx.close()
