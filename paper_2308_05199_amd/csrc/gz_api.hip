@@ -156,7 +156,7 @@ bool set_bound(Job& J, uint32_t dtype, double eb) {
     if (!isfinite(two) || two == 0.0) return false;
     J.t64 = two;
     J.t32 = 0;
-    // 0: the kernels divide (steps whose quotients' remainders could underflow)
+    // 0: the kernels scale or divide (steps whose quotients' remainders could underflow)
     J.rinv = two >= ldexp(1.0, -900) && two <= ldexp(1.0, 900) ? 1.0 / two : 0.0;
     J.eblo = 0;
   }

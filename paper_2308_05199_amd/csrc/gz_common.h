@@ -58,7 +58,7 @@ struct Job {
   uint64_t fixed_off;               // packed output: fixed bytes of earlier streams
   uint64_t NS, B, hdr_off, pay_off; // stream geometry
   double eb;
-  double rinv;                      // 1 / (double)t32; fp64: 1 / t64, or 0 (divide)
+  double rinv;                      // 1 / (double)t32; fp64: 1 / t64, or 0 (scale or divide)
   double t64;                       // fp64 step
   float t32;                        // fp32 step
   float eblo;                       // largest float <= eb

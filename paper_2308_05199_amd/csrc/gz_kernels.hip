@@ -178,7 +178,9 @@ __device__ __forceinline__ int32_t quant(float x, double rinv, float t, QBad<flo
 // The host sets rinv only for steps t in [2^-900, 2^900]: then remainders of
 // quotients of 2^-2 and more are normal, smaller quotients round to q = 0
 // whatever their last bits, and overflowing ones end as NaN or infinity, which
-// fail.  Other steps take the division.
+// fail.  For other steps x and t are scaled by 2^600 or 2^-600 first (exactly, or
+// to an infinity whose quotient fails, or below a quotient of 2^-1000), or
+// divided.
 __device__ __forceinline__ double quot(double x, double t, double y) {
   const double q0 = x * y;
   const double q1 = __builtin_fma(__builtin_fma(-q0, t, x), y, q0);
@@ -216,7 +218,18 @@ __device__ __forceinline__ void quant_run(const double* v, const Job& J, uint32_
       const double x = FULL || i < (int)vcnt ? v[i] : 0.0;
       q[i] = (uint32_t)quant(x, quot(x, J.t64, J.rinv), J.t64, J.eb, b);
     }
+  } else if constexpr (N == 32) {
+    // strips: steps out of the reciprocal's range, brought into it by a power of
+    // two (2^24 values with 256 threads: 140 us by a rolled loop of divisions,
+    // 73.5 so)
+    const double s = J.t64 < 1.0 ? 0x1p600 : 0x1p-600, ts = J.t64 * s, y = 1.0 / ts;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const double x = FULL || i < (int)vcnt ? v[i] : 0.0;
+      q[i] = (uint32_t)quant(x, quot(x * s, ts, y), J.t64, J.eb, b);
+    }
   } else {
+    // units, short of registers (unrolled, mixed batches lost 5%, 132 -> 136 us)
 #pragma unroll 1
     for (int i = 0; i < N; ++i) {
       // (a rolled loop over registers would put them in memory)

@@ -472,3 +472,24 @@ def test_batches_on_both_sides_of_the_strip_rule(gz, ctx, oracle, jobs, n):
         for k, it in enumerate(items):
             assert it["out"][:int(sizes[k].item())].cpu().numpy().tobytes() == want[k % 3], k
     plan.close()
+
+
+@pytest.mark.parametrize("eb", [5e-324, 1e-310, 2.0 ** -1023, 1e-290, 2.0 ** -902, 2.0 ** 900,
+                                1e300, 8e307])
+def test_fp64_steps_out_of_the_reciprocals_range(ctx, oracle, eb):
+    """Strips scale such steps by a power of two, units divide: the oracle's bytes
+    from both, for quotients near halves, over the whole range and failing ones."""
+    import torch
+    g = np.random.default_rng(21)
+    n = 40000
+    with np.errstate(over="ignore", invalid="ignore", under="ignore"):
+        x = np.concatenate([g.integers(-300, 300, n) + 0.5, g.integers(-40, 40, n) + 0.5,
+                            np.exp(g.uniform(-3, 21, n)), g.uniform(-4, 4, n)]) * (2.0 * eb)
+        x = np.concatenate([x, np.nextafter(x, np.inf), np.nextafter(x, -np.inf),
+                            [0.0, -0.0, np.inf, np.nan, 1.7e308, -1.7e308, 5e-324, 1.0, 2.0 ** 424]])
+    want = oracle.compress(x, eb).tobytes()
+    for threads in (0, 128, 256):
+        say("steps out of range", eb, threads)
+        out, nb = ctx.compress(dev(x), eb, threads=threads)
+        assert ctx.device_status() == 0
+        assert out[:int(nb.item())].cpu().numpy().tobytes() == want, threads
