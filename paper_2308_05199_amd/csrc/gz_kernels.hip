@@ -1696,9 +1696,19 @@ __device__ __forceinline__ uint32_t wave_header_load(const Job& J, const uint8_t
   return (lane < 16 && J.in_bytes >= HDR) ? ((const uint32_t*)in)[lane] : 0u;
 }
 
+// A lane's value in every lane: as a scalar, or (VEC) in a vector register.  The
+// job-share decoder has vector registers to spare and spills scalar ones (23 and
+// 6): 64 chunks of 2^21, ring data, 137 and 136 us a launch, 6 ranks of 4 M
+// elements 31.4 and 29.7, 64 chunks of 2^20 at ratio 2 84.5 and 81.3; the fused
+// kernels lose 2 to 6% by it.
+template <bool VEC>
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, int lane) {
+  return VEC ? __shfl(v, lane) : read_lane(v, lane);
+}
+
 // The stream header (the lanes' words wv) against the job, by one wave: ok,
 // payload dwords and step.
-template <typename T>
+template <typename T, bool VEC = false>
 __device__ __forceinline__ bool wave_header_eval(const Job& J, uint32_t wv, uint64_t& paydw,
                                                  T& t) {
   const uint32_t lane = __lane_id();
@@ -1716,8 +1726,8 @@ __device__ __forceinline__ bool wave_header_eval(const Job& J, uint32_t wv, uint
     default: ok = lane < 16 ? wv == 0u : true; break;
   }
   const bool allok = __ballot(ok) == ~0ull;
-  const uint32_t e0 = read_lane(wv, 4), e1 = read_lane(wv, 5), p0 = read_lane(wv, 6),
-                 p1 = read_lane(wv, 7);
+  const uint32_t e0 = lane_value<VEC>(wv, 4), e1 = lane_value<VEC>(wv, 5),
+                 p0 = lane_value<VEC>(wv, 6), p1 = lane_value<VEC>(wv, 7);
   const double eb = __longlong_as_double((long long)(((uint64_t)e1 << 32) | e0));
   const uint64_t payload = ((uint64_t)p1 << 32) | p0;
   bool good = readable && allok && (eb > 0.0) && isfinite(eb);
@@ -1731,10 +1741,10 @@ __device__ __forceinline__ bool wave_header_eval(const Job& J, uint32_t wv, uint
   return good;
 }
 
-template <typename T>
+template <typename T, bool VEC = false>
 __device__ __forceinline__ bool wave_header(const Job& J, const uint8_t* in, uint64_t& paydw,
                                             T& t) {
-  return wave_header_eval<T>(J, wave_header_load(J, in), paydw, t);
+  return wave_header_eval<T, VEC>(J, wave_header_load(J, in), paydw, t);
 }
 
 // Block layout of superblock sb of an incoming stream, read by one wave:
@@ -1778,7 +1788,7 @@ __device__ __forceinline__ void wave_blocks_load(const Job& J, const uint8_t* in
 // False if the table entries, header bytes or block sizes are inconsistent
 // (the same checks as the strip decoder's); raw from wave_blocks_load, of a
 // stream whose header passed.
-template <typename T, int L, int MODE = 0>
+template <typename T, int L, int MODE = 0, bool VEC = false>
 __device__ bool wave_blocks_eval(const Job& J, uint64_t sb, uint64_t paydw, uint32_t nval,
                                  const uint32_t (&raw)[3], WaveBlocks& wb) {
   constexpr uint32_t EW = sizeof(T) / 4, LPB = L / 32, BPS = SUPER / L;
@@ -1820,7 +1830,7 @@ __device__ bool wave_blocks_eval(const Job& J, uint64_t sb, uint64_t paydw, uint
     const uint32_t incl = wave_incl_scan(contrib);
     const uint32_t excl = tot + incl - contrib;
     wb.boff[h] = w == 0 ? excl : excl - size_dw;  // later lanes of a block contribute 0
-    tot += read_lane(incl, 63);
+    tot += lane_value<VEC>(incl, 63);
     if (h == 0) wb.half0 = tot;
     wb.kind[h] = kd;
     wb.F[h] = f;
@@ -2086,7 +2096,7 @@ __device__ __forceinline__ void wave_unpack_store(const Job& J, uint64_t sb, uin
 // step earlier), evaluates the layout of the next one (its words loaded a
 // step earlier), issues that payload and the words after it, then decodes
 // and stores sb.
-template <int L>
+template <int L, bool VEC>
 __device__ __forceinline__ void wave_whole_step(const Job& J, const uint8_t* in, uint64_t paydw,
                                                 float t, uint32_t* R, uint64_t W, uint64_t NF,
                                                 uint64_t sb, const WaveBlocks& wb, PayRegs& pr,
@@ -2094,7 +2104,7 @@ __device__ __forceinline__ void wave_whole_step(const Job& J, const uint8_t* in,
   const uint32_t* pay = (const uint32_t*)(in + J.pay_off);
   const uint32_t* S = wave_pay_commit(pr, R);
   const uint64_t nx = min(sb + W, NF - 1);  // past the end: a whole superblock again, unused
-  okn = wave_blocks_eval<float, L>(J, nx, paydw, SUPER, raw, wbn);
+  okn = wave_blocks_eval<float, L, 0, VEC>(J, nx, paydw, SUPER, raw, wbn);
   wave_pay_issue(okn ? pay + wbn.E : hdr_chunk(in), okn ? (uint32_t)(wbn.En - wbn.E) : 0u, in, pr);
   wave_blocks_load<L, false>(J, in, min(nx + W, NF - 1), raw);
   const u4u none[1] = {};
@@ -2108,7 +2118,7 @@ __device__ __forceinline__ void wave_whole_step(const Job& J, const uint8_t* in,
 // for the payload, not for the previous superblock's stores).  On return sb
 // is the wave's first superblock not decoded; bad is set (and decoding
 // stops) at a malformed one.
-template <int L>
+template <int L, bool VEC = false>
 __device__ __forceinline__ void wave_decode_whole(const Job& J, const uint8_t* in, uint64_t paydw,
                                                   float t, uint32_t* R, uint64_t W, uint64_t& sb,
                                                   bool& bad) {
@@ -2118,7 +2128,7 @@ __device__ __forceinline__ void wave_decode_whole(const Job& J, const uint8_t* i
   uint32_t raw[3];
   wave_blocks_load<L, false>(J, in, sb, raw);
   WaveBlocks wb, wbn;
-  bool ok = wave_blocks_eval<float, L>(J, sb, paydw, SUPER, raw, wb), okn;
+  bool ok = wave_blocks_eval<float, L, 0, VEC>(J, sb, paydw, SUPER, raw, wb), okn;
   PayRegs pr;
   wave_pay_issue(ok ? pay + wb.E : hdr_chunk(in), ok ? (uint32_t)(wb.En - wb.E) : 0u, in, pr);
   wave_blocks_load<L, false>(J, in, min(sb + W, NF - 1), raw);
@@ -2126,14 +2136,14 @@ __device__ __forceinline__ void wave_decode_whole(const Job& J, const uint8_t* i
     bad = true;
     return;
   }
-  wave_whole_step<L>(J, in, paydw, t, R, W, NF, sb, wb, pr, raw, wbn, okn);
+  wave_whole_step<L, VEC>(J, in, paydw, t, R, W, NF, sb, wb, pr, raw, wbn, okn);
   for (sb += W; sb < NF; sb += W) {
     if (!okn) {
       bad = true;
       return;
     }
     wb = wbn;
-    wave_whole_step<L>(J, in, paydw, t, R, W, NF, sb, wb, pr, raw, wbn, okn);
+    wave_whole_step<L, VEC>(J, in, paydw, t, R, W, NF, sb, wb, pr, raw, wbn, okn);
   }
 }
 
@@ -2205,12 +2215,12 @@ __device__ __forceinline__ void wave_job_decode(const Job& J, const uint8_t* in,
                                                 uint64_t stride, uint32_t* R, bool& bad) {
   uint64_t paydw = 0;
   float t = 0;
-  if (!wave_header<float>(J, in, paydw, t)) {
+  if (!wave_header<float, true>(J, in, paydw, t)) {
     bad = true;
     return;
   }
   uint64_t sb = first;
-  wave_decode_whole<L>(J, in, paydw, t, R, stride, sb, bad);
+  wave_decode_whole<L, true>(J, in, paydw, t, R, stride, sb, bad);
   if (bad) return;
   uint32_t raw[3] = {0u, 0u, 0u};
   if (sb < J.NS) wave_blocks_load<L, false>(J, in, sb, raw);
