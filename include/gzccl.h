@@ -79,10 +79,11 @@ typedef struct gz_graph gz_graph;
  * codes superblocks of 4096 elements or units of 2048 on its own (grid
  * ignored): 1D decompression of either type (also batched and scatter), fp32
  * 1D compression, the fused step and decode-and-accumulate; GZ_EUNSUPPORTED
- * elsewhere.  With no shape given or tuned, 1D compression of either type
- * (single, batched and fp64 scatter chunks), decompression (single, batched and
- * scatter), both directions of tiles and the fused step take them;
- * decode-and-accumulate and fp32 scatter compression take strips.  mode 0 = 1D blocks, 1 = 8x8 tiles (block_len 64,
+ * elsewhere.  With no shape given or tuned, decompression (single, batched and
+ * scatter), both directions of tiles, the fused step, fp64 1D compression and
+ * fp32 1D compression of short streams and most batches take them; longer fp32
+ * streams, fp32 batches that strips divide better, fp32 scatter compression and
+ * decode-and-accumulate take strips.  mode 0 = 1D blocks, 1 = 8x8 tiles (block_len 64,
  * nx = row length, multiple of 8, n a multiple of 8*nx); select (mode 1):
  * 0 = int8 MLP selector, 1 = exhaustive trial, 2 = always L1D. */
 typedef struct {
@@ -247,7 +248,7 @@ gz_status gz_scatter_decompress(gz_ctx* ctx, const void* d_packed,
  * each hold at least one element, and for a compress or fused batch whose
  * jobs are all fp32 with the same block length and superblock count
  * (GZ_EUNSUPPORTED for other batches).  By default compress, decompress and fused
- * batches run on them where they can. */
+ * batches run on them where they can and are the faster for it. */
 gz_status gz_batch(gz_ctx* ctx, gz_op op, const gz_request* h_reqs,
                    uint32_t nreq, const gz_params* p, gz_stream_t stream);
 
@@ -255,7 +256,7 @@ gz_status gz_batch(gz_ctx* ctx, gz_op op, const gz_request* h_reqs,
  * the device, then copies) into the context's plan arena, so that
  * gz_plan_launch is a single kernel launch with no host work, suitable for
  * stream capture.  No device memory is allocated: the arena, sized at
- * gz_ctx_create, holds 16 * max_requests + 64 descriptors and the strip
+ * gz_ctx_create, holds 16 * max_requests + 64 descriptors and the
  * maps of 16 batches of max_elems elements; a plan that does not fit
  * returns GZ_ENOSPC.  Plans of one context must run in order on one stream.
  * Destroy graphs and plans before their context (a plan outliving its

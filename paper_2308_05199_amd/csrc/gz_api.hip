@@ -256,23 +256,25 @@ bool params_ok(const gz_params* p, uint32_t& L) {
 
 bool tile_mode(const gz_params* p) { return p && p->mode == 1; }
 
-// Whether a caller may ask for the per-wave kernels (threads 64): 1D decoding
-// of either type (op 1), fp32 1D encoding, the fused step and
-// decode-and-accumulate (ops 0, 2, 3), which need their LDS.
+// Whether the unit kernels' LDS fits the device: compression of either type and
+// of tiles (op 0), the fused step (op 2).
 bool unit_fits(const gz_ctx* c, uint32_t op) {
   return gzk::unit_lds(op == 2, op == 2 ? gzk::UNIT_WORKERS_FUSED : gzk::UNIT_WORKERS) <=
          c->lds_max;
 }
 
+// Whether a caller may ask for the per-wave kernels (threads 64): 1D decoding
+// of either type (op 1), fp32 1D encoding, the fused step and
+// decode-and-accumulate (ops 0, 2, 3), which need their LDS.
 bool wave_fits(const gz_ctx* c, uint32_t op, uint32_t dt) {
   if (op == 1) return std::max(gzk::wave_decode_lds(), gzk::unit_decode_lds()) <= c->lds_max;
   if (op == 3) return dt == GZ_F32 && gzk::wave_decode_lds() <= c->lds_max;
   return (op == 0 || op == 2) && dt == GZ_F32 && unit_fits(c, op);
 }
 
-// Measured defaults: the unit and per-wave kernels for encoding, the fused
-// step and decoding (single streams and batches); strips for decode-and-
-// accumulate (1 GiB: 436 vs 478 us: there four waves per SIMD hide the
+// Measured defaults: the unit and per-wave kernels for the fused step, decoding
+// and, where unit_compresses and batch_unit say so, compression; strips for
+// decode-and-accumulate (1 GiB: 436 vs 478 us: there four waves per SIMD hide the
 // accumulator loads, where the per-wave kernel has two).
 bool wave_default(uint32_t op) { return op <= 2; }
 

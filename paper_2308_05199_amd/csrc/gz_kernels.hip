@@ -8,10 +8,11 @@
 // look-back pass over agent-scope status words (a single read of the input,
 // a single write of the output), tagged with a launch epoch so they never
 // need clearing.  No MFMA: the path is bound by HBM, not by arithmetic.
-// Most of the encoding runs by units (2048 elements, a wave each, section
-// "unit encode") and most of the decoding by waves that need no scan; strips serve
-// the explicit thread counts, the tuner, decode-and-accumulate and fp32
-// scatter compression.
+// Short streams, fp64, tiles, most batches and short fused steps are encoded by
+// units (2048 elements, a wave each, section "unit encode"), long fused steps by
+// waves that code superblocks, and most of the decoding runs by waves that need
+// no scan.  Strips serve long fp32 compressions, the explicit thread counts, the
+// tuner, decode-and-accumulate and fp32 scatter compression.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -1064,7 +1065,6 @@ struct FusedSrc {
   const uint32_t* pay;  // incoming payload (global)
   DecInfo di;
   float t;
-  bool exists;
 };
 
 // Residual i of a lane read straight from its block's planes.
@@ -1674,11 +1674,10 @@ __device__ __forceinline__ void decompress_tp_one(const Job& J, uint64_t s, cons
 // padded segment layout for coalesced stores.  Lane l decodes segments l and
 // 64 + l of the superblock.  For fp32 streams of more than 2^24 elements,
 // shorter than 2^19, and batches of them (the unit decoder takes the rest).
-template <typename T>
 struct WaveDec {
-  static constexpr uint32_t WAVES = sizeof(T) == 4 ? 8 : 4;               // per workgroup
-  static_assert(sizeof(T) != 4 || WAVES == DEC_WAVES_F32, "host's job shares assume this");
-  static constexpr uint32_t REGION = 2 * 64 * seg_stride<T>() + 8;         // dwords per wave
+  static constexpr uint32_t WAVES = 8;  // per workgroup
+  static_assert(WAVES == DEC_WAVES_F32, "host's job shares assume this");
+  static constexpr uint32_t REGION = 2 * 64 * seg_stride<float>() + 8;  // dwords per wave
 };
 
 // LDS written by some lanes of the wave is read by others: the wave's LDS
@@ -1966,8 +1965,8 @@ __device__ __forceinline__ const uint32_t* wave_pay_commit(const PayRegs& pr, ui
   return dst + pr.delta;
 }
 
-template <typename T, int L, uint32_t OP, uint32_t NOLD>
-__device__ __forceinline__ void wave_unpack_store(const Job& J, uint64_t sb, uint32_t nval, T t,
+template <int L, uint32_t OP, uint32_t NOLD>
+__device__ __forceinline__ void wave_unpack_store(const Job& J, uint64_t sb, uint32_t nval, float t,
                                                   uint32_t* R, const uint32_t* S,
                                                   const WaveBlocks& wb, const u4u (&old)[NOLD]);
 
@@ -1976,16 +1975,14 @@ __device__ __forceinline__ void wave_unpack_store(const Job& J, uint64_t sb, uin
 // malformed.  raw: sb's table and header-byte words (wave_blocks_load), on
 // return those of the wave's next superblock nsb (if it exists), whose
 // loads go out with this superblock's payload copy.
-template <typename T, int L, uint32_t OP = 1>
+template <int L, uint32_t OP = 1>
 __device__ bool wave_decode_super(const Job& J, const uint8_t* in, uint64_t sb, uint64_t paydw,
-                                  T t, uint32_t* R, uint32_t (&raw)[3], uint64_t nsb) {
-  static_assert(OP == 1 || (OP == 3 && sizeof(T) == 4), "accumulation is fp32");
-  constexpr uint32_t EW = sizeof(T) / 4;
-  constexpr uint32_t CPL = SUPER * EW / 4 / 64;  // 16-byte chunks per lane of a superblock
+                                  float t, uint32_t* R, uint32_t (&raw)[3], uint64_t nsb) {
+  constexpr uint32_t CPL = SUPER / 4 / 64;  // 16-byte chunks per lane of a superblock
   const uint32_t lane = __lane_id();
   const uint64_t e0 = sb * SUPER;
   const uint32_t nval = (uint32_t)min((uint64_t)SUPER, J.n - e0);
-  uint32_t* d32 = (uint32_t*)((T*)J.out + e0);
+  uint32_t* d32 = (uint32_t*)((float*)J.out + e0);
   // OP 3: the accumulator of a whole superblock is in flight during the decode
   u4u old[OP == 3 ? CPL : 1];
   if (OP == 3 && nval == SUPER) {
@@ -1993,48 +1990,47 @@ __device__ bool wave_decode_super(const Job& J, const uint8_t* in, uint64_t sb, 
     for (uint32_t u = 0; u < CPL; ++u) old[u] = ((const u4u*)d32)[u * 64 + lane];
   }
   WaveBlocks wb;
-  const bool ok = wave_blocks_eval<T, L>(J, sb, paydw, nval, raw, wb);
+  const bool ok = wave_blocks_eval<float, L>(J, sb, paydw, nval, raw, wb);
   const uint32_t* S = R;
   if (ok)
-    S = wave_stage_payload<SUPER * EW, true>((const uint32_t*)(in + J.pay_off) + wb.E,
-                                             (uint32_t)(wb.En - wb.E), R);
+    S = wave_stage_payload<SUPER, true>((const uint32_t*)(in + J.pay_off) + wb.E,
+                                        (uint32_t)(wb.En - wb.E), R);
   // the next superblock's words are in flight during this one's unpacking
   if (nsb < J.NS) wave_blocks_load<L, false>(J, in, nsb, raw);
   if (!ok) return false;
-  wave_unpack_store<T, L, OP>(J, sb, nval, t, R, S, wb, old);
+  wave_unpack_store<L, OP>(J, sb, nval, t, R, S, wb, old);
   return true;
 }
 
 // Decodes superblock sb (layout wb, payload staged at S in the wave's
 // region R) into J.out (OP 1), or adds it to the fp32 values there (OP 3,
 // old: the accumulator's superblock if whole).
-template <typename T, int L, uint32_t OP, uint32_t NOLD>
-__device__ __forceinline__ void wave_unpack_store(const Job& J, uint64_t sb, uint32_t nval, T t,
+template <int L, uint32_t OP, uint32_t NOLD>
+__device__ __forceinline__ void wave_unpack_store(const Job& J, uint64_t sb, uint32_t nval, float t,
                                                   uint32_t* R, const uint32_t* S,
                                                   const WaveBlocks& wb, const u4u (&old)[NOLD]) {
-  constexpr uint32_t EW = sizeof(T) / 4, LPB = L / 32;
-  constexpr uint32_t SEGW = 32 * EW, STR = seg_stride<T>();
-  constexpr uint32_t CPL = SUPER * EW / 4 / 64;  // 16-byte chunks per lane of a superblock
+  constexpr uint32_t LPB = L / 32, STR = seg_stride<float>();
+  constexpr uint32_t CPL = SUPER / 4 / 64;  // 16-byte chunks per lane of a superblock
   const uint32_t lane = __lane_id();
   const uint64_t e0 = sb * SUPER;
-  uint32_t* d32 = (uint32_t*)((T*)J.out + e0);
+  uint32_t* d32 = (uint32_t*)((float*)J.out + e0);
   wave_lds_sync();
   const uint32_t* boff = wb.boff;
   const uint32_t* kind = wb.kind;
   const uint32_t* F = wb.F;
   const bool* ex = wb.ex;
-  T v0[32], v1[32];
+  float v0[32], v1[32];
   {
     const uint32_t seg = lane, w = seg % LPB;
     const uint32_t vc = (uint32_t)min(32, max(0, (int)nval - (int)(seg * 32)));
-    if (nval == SUPER) unpack_seg<T, LPB, true>(S + boff[0], kind[0], F[0], w, vc, ex[0], t, v0);
-    else unpack_seg<T, LPB, false>(S + boff[0], kind[0], F[0], w, vc, ex[0], t, v0);
+    if (nval == SUPER) unpack_seg<float, LPB, true>(S + boff[0], kind[0], F[0], w, vc, ex[0], t, v0);
+    else unpack_seg<float, LPB, false>(S + boff[0], kind[0], F[0], w, vc, ex[0], t, v0);
   }
   {
     const uint32_t seg = 64 + lane, w = seg % LPB;
     const uint32_t vc = (uint32_t)min(32, max(0, (int)nval - (int)(seg * 32)));
-    if (nval == SUPER) unpack_seg<T, LPB, true>(S + boff[1], kind[1], F[1], w, vc, ex[1], t, v1);
-    else unpack_seg<T, LPB, false>(S + boff[1], kind[1], F[1], w, vc, ex[1], t, v1);
+    if (nval == SUPER) unpack_seg<float, LPB, true>(S + boff[1], kind[1], F[1], w, vc, ex[1], t, v1);
+    else unpack_seg<float, LPB, false>(S + boff[1], kind[1], F[1], w, vc, ex[1], t, v1);
   }
   wave_lds_sync();  // every lane has read its payload words
   // values into the padded segment layout, then coalesced 16-byte stores
@@ -2043,24 +2039,18 @@ __device__ __forceinline__ void wave_unpack_store(const Job& J, uint64_t sb, uin
     uint32_t* p1 = R + (64 + lane) * STR;
 #pragma unroll
     for (int i = 0; i < 32; ++i) {
-      uint32_t wd[2];
-      raw_words(v0[i], wd);
-      p0[i * EW] = wd[0];
-      if (EW == 2) p0[i * EW + 1] = wd[1];
-      raw_words(v1[i], wd);
-      p1[i * EW] = wd[0];
-      if (EW == 2) p1[i * EW + 1] = wd[1];
+      p0[i] = __float_as_uint(v0[i]);
+      p1[i] = __float_as_uint(v1[i]);
     }
   }
   wave_lds_sync();
-  const uint32_t vdw = nval * EW;
   // decoded + old, in fp32 (OP 3)
   auto addf = [](uint32_t a, uint32_t b) { return __float_as_uint(__uint_as_float(a) + __uint_as_float(b)); };
   if (nval == SUPER) {
 #pragma unroll
-    for (uint32_t u = 0; u < CPL; ++u) {  // 16 (fp32) or 32 (fp64) chunks per lane
+    for (uint32_t u = 0; u < CPL; ++u) {
       const uint32_t k = u * 64 + lane, dw = 4 * k;
-      u4u r = *(const u4u*)(R + (dw / SEGW) * STR + dw % SEGW);
+      u4u r = *(const u4u*)(R + (dw / SEG) * STR + dw % SEG);
       if (OP == 3) {
         r.x = addf(r.x, old[u].x);
         r.y = addf(r.y, old[u].y);
@@ -2070,10 +2060,10 @@ __device__ __forceinline__ void wave_unpack_store(const Job& J, uint64_t sb, uin
       ((u4u*)d32)[k] = r;
     }
   } else {
-    for (uint32_t k = lane; 4 * k < vdw; k += 64) {
+    for (uint32_t k = lane; 4 * k < nval; k += 64) {
       const uint32_t dw = 4 * k;
-      u4u r = *(const u4u*)(R + (dw / SEGW) * STR + dw % SEGW);
-      if (dw + 4 <= vdw) {
+      u4u r = *(const u4u*)(R + (dw / SEG) * STR + dw % SEG);
+      if (dw + 4 <= nval) {
         if (OP == 3) {
           const u4u a = ((const u4u*)d32)[k];
           r.x = addf(r.x, a.x);
@@ -2083,9 +2073,9 @@ __device__ __forceinline__ void wave_unpack_store(const Job& J, uint64_t sb, uin
         }
         ((u4u*)d32)[k] = r;
       } else {
-        if (dw + 0 < vdw) d32[dw + 0] = OP == 3 ? addf(r.x, d32[dw + 0]) : r.x;
-        if (dw + 1 < vdw) d32[dw + 1] = OP == 3 ? addf(r.y, d32[dw + 1]) : r.y;
-        if (dw + 2 < vdw) d32[dw + 2] = OP == 3 ? addf(r.z, d32[dw + 2]) : r.z;
+        if (dw + 0 < nval) d32[dw + 0] = OP == 3 ? addf(r.x, d32[dw + 0]) : r.x;
+        if (dw + 1 < nval) d32[dw + 1] = OP == 3 ? addf(r.y, d32[dw + 1]) : r.y;
+        if (dw + 2 < nval) d32[dw + 2] = OP == 3 ? addf(r.z, d32[dw + 2]) : r.z;
       }
     }
   }
@@ -2108,7 +2098,7 @@ __device__ __forceinline__ void wave_whole_step(const Job& J, const uint8_t* in,
   wave_pay_issue(okn ? pay + wbn.E : hdr_chunk(in), okn ? (uint32_t)(wbn.En - wbn.E) : 0u, in, pr);
   wave_blocks_load<L, false>(J, in, min(nx + W, NF - 1), raw);
   const u4u none[1] = {};
-  wave_unpack_store<float, L, 1>(J, sb, SUPER, t, R, S, wb, none);
+  wave_unpack_store<L, 1>(J, sb, SUPER, t, R, S, wb, none);
 }
 
 // The whole superblocks sb, sb + W, ... of an fp32 stream, each one's
@@ -2148,10 +2138,10 @@ __device__ __forceinline__ void wave_decode_whole(const Job& J, const uint8_t* i
 }
 
 template <int L>
-__global__ __launch_bounds__(WaveDec<float>::WAVES * 64)
+__global__ __launch_bounds__(WaveDec::WAVES * 64)
 __attribute__((amdgpu_waves_per_eu(2, 2))) void k_decompress_w(Job J, Ctl C) {
   const uint32_t wid = threadIdx.x >> 6;
-  uint32_t* R = g_stage + wid * WaveDec<float>::REGION;
+  uint32_t* R = g_stage + wid * WaveDec::REGION;
   const uint8_t* in = (const uint8_t*)J.in;
   uint64_t paydw = 0;
   float t = 0;
@@ -2164,7 +2154,7 @@ __attribute__((amdgpu_waves_per_eu(2, 2))) void k_decompress_w(Job J, Ctl C) {
       uint32_t raw[3] = {0u, 0u, 0u};
       if (sb < J.NS) wave_blocks_load<L, false>(J, in, sb, raw);
       for (; sb < J.NS; sb += W)
-        if (!wave_decode_super<float, L>(J, in, sb, paydw, t, R, raw, sb + W)) bad = true;
+        if (!wave_decode_super<L>(J, in, sb, paydw, t, R, raw, sb + W)) bad = true;
     }
   }
   if (bad && __lane_id() == 0) atomicOr(&C.ctrl->err, ERRF_CORRUPT);
@@ -2173,10 +2163,10 @@ __attribute__((amdgpu_waves_per_eu(2, 2))) void k_decompress_w(Job J, Ctl C) {
 // Single-stream decode-and-accumulate by waves (fp32): as k_decompress_w,
 // each superblock added to the accumulator J.out.
 template <int L>
-__global__ __launch_bounds__(WaveDec<float>::WAVES * 64)
+__global__ __launch_bounds__(WaveDec::WAVES * 64)
 __attribute__((amdgpu_waves_per_eu(2, 2))) void k_accum_w(Job J, Ctl C) {
   const uint32_t wid = threadIdx.x >> 6;
-  uint32_t* R = g_stage + wid * WaveDec<float>::REGION;
+  uint32_t* R = g_stage + wid * WaveDec::REGION;
   const uint8_t* in = (const uint8_t*)J.in;
   uint64_t paydw = 0;
   float t = 0;
@@ -2187,15 +2177,15 @@ __attribute__((amdgpu_waves_per_eu(2, 2))) void k_accum_w(Job J, Ctl C) {
     uint32_t raw[3] = {0u, 0u, 0u};
     if (sb0 < J.NS) wave_blocks_load<L, false>(J, in, sb0, raw);
     for (uint64_t sb = sb0; sb < J.NS; sb += W)
-      if (!wave_decode_super<float, L, 3>(J, in, sb, paydw, t, R, raw, sb + W)) bad = true;
+      if (!wave_decode_super<L, 3>(J, in, sb, paydw, t, R, raw, sb + W)) bad = true;
   }
   if (bad && __lane_id() == 0) atomicOr(&C.ctrl->err, ERRF_CORRUPT);
 }
 
-// One superblock of a batch job: the job's stream (at its scatter offset,
-// if any) is checked and the superblock decoded (OP 1) or accumulated (OP 3).
-template <typename T, int L, uint32_t OP>
-__device__ __forceinline__ bool wave_batch_super(const Job& J, uint64_t sb, uint32_t* R) {
+// One superblock of a batch job: the job's stream is checked and the superblock
+// added to the accumulator.
+template <int L>
+__device__ __forceinline__ bool wave_accum_super(const Job& J, uint64_t sb, uint32_t* R) {
   const uint64_t off = J.in_off ? J.in_off[J.job] : 0ull;
   Job Jl = J;
   Jl.in_bytes = off <= J.in_bytes ? J.in_bytes - off : 0ull;
@@ -2203,9 +2193,9 @@ __device__ __forceinline__ bool wave_batch_super(const Job& J, uint64_t sb, uint
   uint32_t raw[3];
   wave_blocks_load<L, true>(Jl, in, sb, raw);  // in flight with the header's words
   uint64_t paydw = 0;
-  T t = 0;
-  if (!wave_header<T>(Jl, in, paydw, t)) return false;
-  return wave_decode_super<T, L, OP>(Jl, in, sb, paydw, t, R, raw, ~0ull);
+  float t = 0;
+  if (!wave_header<float>(Jl, in, paydw, t)) return false;
+  return wave_decode_super<L, 3>(Jl, in, sb, paydw, t, R, raw, ~0ull);
 }
 
 // Superblocks first, first + stride, ... of one fp32 stream (job J, its
@@ -2225,19 +2215,19 @@ __device__ __forceinline__ void wave_job_decode(const Job& J, const uint8_t* in,
   uint32_t raw[3] = {0u, 0u, 0u};
   if (sb < J.NS) wave_blocks_load<L, false>(J, in, sb, raw);
   for (; sb < J.NS; sb += stride)
-    if (!wave_decode_super<float, L>(J, in, sb, paydw, t, R, raw, sb + stride)) bad = true;
+    if (!wave_decode_super<L>(J, in, sb, paydw, t, R, raw, sb + stride)) bad = true;
 }
 
 // Batched decoding of fp32 1D jobs by shares: the map holds jw (job, first
 // superblock, stride) triples, one per wave's share (waves take them
 // statically); each wave decodes superblocks first, first + stride, ... of its
 // job with the pipelined single-stream decoder.
-__global__ __launch_bounds__(WaveDec<float>::WAVES * 64)
+__global__ __launch_bounds__(WaveDec::WAVES * 64)
 __attribute__((amdgpu_waves_per_eu(2, 2))) void k_batch_decode_w(
     const Job* __restrict__ jobs, const uint32_t* __restrict__ map, uint32_t jw, Ctl C) {
-  constexpr uint32_t WAVES = WaveDec<float>::WAVES;
+  constexpr uint32_t WAVES = WaveDec::WAVES;
   const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  uint32_t* R = g_stage + wid * WaveDec<float>::REGION;
+  uint32_t* R = g_stage + wid * WaveDec::REGION;
   bool bad = false;
   for (uint32_t w = blockIdx.x * WAVES + wid; w < jw; w += gridDim.x * WAVES) {
     Job J = jobs[map[3 * (uint64_t)w]];
@@ -2261,13 +2251,13 @@ __attribute__((amdgpu_waves_per_eu(2, 2))) void k_batch_decode_w(
 // superblock map[2i + 1] of job map[2i], or, without a map (jobs of equal
 // superblock counts), superblock i / njobs of job i % njobs; waves take them
 // statically.
-__global__ __launch_bounds__(WaveDec<float>::WAVES * 64)
+__global__ __launch_bounds__(WaveDec::WAVES * 64)
 __attribute__((amdgpu_waves_per_eu(2, 2))) void k_batch_accum_w(
     const Job* __restrict__ jobs, const uint32_t* __restrict__ map, uint32_t njobs,
     uint32_t total, Ctl C) {
-  constexpr uint32_t WAVES = WaveDec<float>::WAVES;
+  constexpr uint32_t WAVES = WaveDec::WAVES;
   const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  uint32_t* R = g_stage + wid * WaveDec<float>::REGION;
+  uint32_t* R = g_stage + wid * WaveDec::REGION;
   bool bad = false;
   const uint32_t W = gridDim.x * WAVES;
   for (uint32_t i = blockIdx.x * WAVES + wid; i < total; i += W) {
@@ -2276,9 +2266,9 @@ __attribute__((amdgpu_waves_per_eu(2, 2))) void k_batch_accum_w(
     const Job J = jobs[j];
     bool ok = false;
     switch ((J.dtype << 3) | J.log2L) {
-      case 5: ok = wave_batch_super<float, 32, 3>(J, sb, R); break;
-      case 6: ok = wave_batch_super<float, 64, 3>(J, sb, R); break;
-      case 7: ok = wave_batch_super<float, 128, 3>(J, sb, R); break;
+      case 5: ok = wave_accum_super<32>(J, sb, R); break;
+      case 6: ok = wave_accum_super<64>(J, sb, R); break;
+      case 7: ok = wave_accum_super<128>(J, sb, R); break;
       default: break;
     }
     if (!ok) bad = true;
@@ -2919,10 +2909,11 @@ __global__ GZ_WAVE_ATTR void k_batch_fused_w(const Job* __restrict__ jobs, uint3
 //
 // Bound by VALU and scalar issue behind the latency of loads and stores, not
 // by the prefix: a copy that did not wait for offsets took the same time.
-// Before (strips; the fused step by superblocks) and after: 2^14 fp32 values
-// 13.9 -> 9.6 us, 1 GiB 408 -> 386 us, 20 M fp64 values 85 -> 55 us, a batch
-// of 512 mixed requests compressed and decompressed 317 -> 270 us, one fused
-// step of 2 M values 24.1 -> 17.4 us, a ring Allreduce of 6 x 4 M 215 -> 175 us.
+// Before (strips; the fused step by superblocks) and now: 2^14 fp32 values
+// 13.9 -> 9.4 us, 20 M fp64 values 85 -> 55.8 us, a batch of 512 mixed requests
+// compressed and decompressed 317 -> 228 us, one fused step of 2 M values 24.1 ->
+// 16.9 us, a ring Allreduce of 6 x 4 M 215 -> 171 us.  Long fp32 streams are left
+// to strips (1 GiB 380 us) and long fused steps to the waves above.
 template <bool FUSED>
 struct UnitEnc {
   static constexpr uint32_t SEGS = 64;
@@ -3501,9 +3492,8 @@ __global__ GZ_UNIT_ATTR(FUSED) void k_unit(Job J, Ctl C) {
 
 // One field of 8x8 tiles: a unit's lanes load their rows straight from the
 // field.  Bound by VALU issue (the selector's features and network, or three
-// predictors).  33 M values with the learned selector, compressed and
-// decompressed: 150 -> 125 us against 256-thread strips (128-131 us with 11
-// workers).
+// predictors).  33 M values with the learned selector: compressed 108 -> 82 us
+// against 256-thread strips (both ways 189 -> 124; 128-131 us with 11 workers).
 __global__ GZ_UNIT_ATTR(false) void k_unit_tiles(Job J, Ctl C) {
   __shared__ USched us;
   __shared__ uint32_t wts[192];
@@ -3592,18 +3582,17 @@ __global__ GZ_UNIT_ATTR(OP == 2) void k_batch_unit(const Job* __restrict__ jobs,
 
 // ------------------------------------------------------------ unit decode
 // Decoding by single waves, a unit of 2048 elements each: 8x8 tiles, batches
-// that hold fp64 jobs, and short streams.  Units are independent (a
+// that hold fp64 jobs, and medium streams.  Units are independent (a
 // superblock's offset is its table entry, its second unit's follows from the
 // header bytes, which both units check whole), so waves take them statically.
 // A unit needs 9 KB of LDS (payload, then rows of values for coalesced stores;
 // fp64 rows 16 values at a time) and 128 registers: four waves per SIMD, where
 // the superblock decoder above has two (fp64, before, one; tiles, before, three
 // in 256-thread strips with barriers).  Bound by HBM for long fp64 streams,
-// by the two dependent loads of a unit for short ones.  20 M fp64 values 37.8
-// -> 30.4 us, 33 M tile values (compressed and decompressed) 188 -> 150 us, 512
-// mixed requests (both ways) 270 -> 234 us; fp32 streams of 2^20 / 2^22 / 2^24 /
-// 2^26 / 2^28 elements 10.1 / 11.2 / 19.5 / 68 / 266 us by superblocks, 9.3 /
-// 10.1 / 18.4 / 75 / 283 us by units.
+// by the two dependent loads of a unit for short ones.  20 M fp64 values 46 ->
+// 37.4 us, 8 M tile values 50.5 -> 20.8 us, 4096 mixed requests 55 -> 34 us;
+// fp32 streams of 2^20 / 2^22 / 2^24 / 2^26 / 2^28 elements 10.1 / 11.2 / 19.5 / 68 /
+// 266 us by superblocks, 9.3 / 10.1 / 18.4 / 75 / 283 us by units.
 struct UnitDec {
   static constexpr uint32_t STR = 36, XW = 64 * STR, WAVES = 4;  // region (dwords), per workgroup
 };
@@ -3790,7 +3779,6 @@ __device__ __forceinline__ void fused_body(const Job& J, uint64_t s, uint64_t gs
                                                v, vcnt, fs.di);
   fs.pay = (const uint32_t*)((const uint8_t*)J.in + J.pay_off);
   fs.t = sm.t32;
-  fs.exists = FULL || (s * blockDim.x + threadIdx.x) / (L / 32) < J.B;
   // The local addend moves through LDS with coalesced loads once the decode
   // is done with the LDS.  (Each lane reading its own 32 values would touch
   // a different 128-byte line in every lane of every load; loading it before
@@ -4096,13 +4084,13 @@ static hipError_t launch_d(const Job& J, const Ctl& C, uint32_t tpb, uint32_t gr
 }
 template <int L>
 static hipError_t launch_dw(const Job& J, const Ctl& C, uint32_t grid, hipStream_t st) {
-  hipLaunchKernelGGL((k_decompress_w<L>), dim3(grid), dim3(WaveDec<float>::WAVES * 64),
+  hipLaunchKernelGGL((k_decompress_w<L>), dim3(grid), dim3(WaveDec::WAVES * 64),
                      wave_decode_lds(), st, J, C);
   return hipGetLastError();
 }
 
 hipError_t launch_decompress_wave(const Job& J, const Ctl& C, uint32_t cus, hipStream_t st) {
-  const uint64_t need = (J.NS + WaveDec<float>::WAVES - 1) / WaveDec<float>::WAVES;
+  const uint64_t need = (J.NS + WaveDec::WAVES - 1) / WaveDec::WAVES;
   const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(cus, need));
   switch (J.log2L) {
     case 5: return launch_dw<32>(J, C, grid, st);
@@ -4270,13 +4258,13 @@ hipError_t launch_batch_unit_decode(const Job* d_jobs, const uint32_t* d_map, ui
 
 template <int L>
 static hipError_t launch_aw(const Job& J, const Ctl& C, uint32_t grid, hipStream_t st) {
-  const size_t lds = (size_t)WaveDec<float>::WAVES * WaveDec<float>::REGION * 4;
-  hipLaunchKernelGGL((k_accum_w<L>), dim3(grid), dim3(WaveDec<float>::WAVES * 64), lds, st, J, C);
+  const size_t lds = (size_t)WaveDec::WAVES * WaveDec::REGION * 4;
+  hipLaunchKernelGGL((k_accum_w<L>), dim3(grid), dim3(WaveDec::WAVES * 64), lds, st, J, C);
   return hipGetLastError();
 }
 
 hipError_t launch_accum_wave(const Job& J, const Ctl& C, uint32_t cus, hipStream_t st) {
-  const uint64_t need = (J.NS + WaveDec<float>::WAVES - 1) / WaveDec<float>::WAVES;
+  const uint64_t need = (J.NS + WaveDec::WAVES - 1) / WaveDec::WAVES;
   const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(cus, need));
   switch (J.log2L) {
     case 5: return launch_aw<32>(J, C, grid, st);
@@ -4288,7 +4276,7 @@ hipError_t launch_accum_wave(const Job& J, const Ctl& C, uint32_t cus, hipStream
 
 hipError_t launch_decode_shares(const Job* d_jobs, const uint32_t* d_map, uint32_t jw,
                                 uint32_t cus, const Ctl& C, hipStream_t st) {
-  constexpr uint32_t WAVES = WaveDec<float>::WAVES;
+  constexpr uint32_t WAVES = WaveDec::WAVES;
   const uint32_t grid =
       (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(cus, (jw + WAVES - 1) / WAVES));
   hipLaunchKernelGGL(k_batch_decode_w, dim3(grid), dim3(WAVES * 64), wave_decode_lds(), st, d_jobs,
@@ -4298,7 +4286,7 @@ hipError_t launch_decode_shares(const Job* d_jobs, const uint32_t* d_map, uint32
 
 hipError_t launch_accum_wave_batch(const Job* d_jobs, const uint32_t* d_map, uint32_t njobs,
                                    uint32_t total, uint32_t cus, const Ctl& C, hipStream_t st) {
-  constexpr uint32_t WAVES = WaveDec<float>::WAVES;
+  constexpr uint32_t WAVES = WaveDec::WAVES;
   const uint64_t need = ((uint64_t)total + WAVES - 1) / WAVES;
   const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(cus, need));
   hipLaunchKernelGGL(k_batch_accum_w, dim3(grid), dim3(WAVES * 64), wave_decode_lds(), st, d_jobs,
@@ -4306,7 +4294,7 @@ hipError_t launch_accum_wave_batch(const Job* d_jobs, const uint32_t* d_map, uin
   return hipGetLastError();
 }
 
-size_t wave_decode_lds() { return (size_t)WaveDec<float>::WAVES * WaveDec<float>::REGION * 4; }
+size_t wave_decode_lds() { return (size_t)WaveDec::WAVES * WaveDec::REGION * 4; }
 
 size_t unit_decode_lds() { return (size_t)UnitDec::WAVES * UnitDec::XW * 4; }
 
